@@ -13,8 +13,8 @@
 // with A_r, B_y the length-P DFTs of the rows (no wrap-around: x + R + dx <= W - 1 < P).
 // The rows are real, so only k = 0 .. P/2 is formed (Z at P - k is the conjugate).
 // Four steps: row spectra (one P/2-point complex FFT per row of two packed real rows,
-// Stockham radix-4 passes in LDS), the contraction Z over template rows (lags in register
-// windows, frame spectra staged in LDS), the inverse at the 2R+1 lags needed, and the
+// Stockham radix-4 passes in LDS), the contraction Z over template rows (itself by
+// transforms along y, block by block), the inverse at the 2R+1 lags needed, and the
 // argmax.  The scores carry rounding of order 1e-13 relative to the largest, so the
 // offsets are taken from exact direct sums: a +-1 window around the spectral argmax
 // (moved while its maximum sits on an inner border), kept when its exact peak exceeds
@@ -40,8 +40,10 @@ void register_scores(const RegPlan &p, const float *ref, const float *frames, in
 
 constexpr int FFT_THREADS = 256;
 constexpr int32_t FFT_P_MAX = 8192;    // longest rows: P/2 = 4096 complex values in LDS (64 KB)
-constexpr int CORR_KW = 64;            // spectrum columns per contraction workgroup (one per lane)
-constexpr int CORR_LDS_MAX = 64 * 1024;
+constexpr int COL_L = 256;             // rows per block of the contraction (transform length along y)
+constexpr int COL_KC = 16;             // spectrum columns per contraction workgroup
+constexpr int COL_LAGS = 144;          // most lags per pass: a block then adds at least 113 template rows
+constexpr size_t SPEC_ROUND_BYTES = size_t(2) << 30;  // spectra and partials of the frames of one round
 constexpr int32_t FFT_MAX_MOVES = 2;   // window moves of the exact refinement (then the full search)
 constexpr size_t FFT_FALLBACK_BYTES = size_t(256) << 20;
 
@@ -50,6 +52,11 @@ __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_doub
 __device__ __forceinline__ double2 cmul(double2 a, double2 b)
 {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+// two roundings per component instead of three
+__device__ __forceinline__ double2 cmulf(double2 a, double2 b)
+{
+    return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 
 // tw[t] = exp(-2 pi i t / P), t in [0, P)
@@ -233,145 +240,207 @@ __global__ __launch_bounds__(FFT_THREADS) void fft_rows(RowSrc src, int32_t rows
 }
 
 // ---- contraction over template rows -------------------------------------------------------
-// Zp[f][band][s][j][k] = sum over template rows y of sub-range s of band `band` of
-// A_f[y + j][k] conj(B[y][k]), lags j in [0, D).  Lane = spectrum column k (CORR_KW per
-// workgroup); wave w = (lag block within the group, sub-range s): a thread owns DY
-// consecutive lags j0 .. j0 + DY - 1 and keeps the DY frame values its next template row
-// needs in a register window (one new value per row).  The frame rows of a chunk of
-// S * DY template rows (and the lags of the group) are staged in LDS; template values are
-// read from the spectrum directly.  Rows beyond the data are zero in both spectra.
-struct CorrArgs {
-    const double2 *A;  // frame spectra: frame f at A + f * a_batch, row r at + r * PS
-    const double2 *B;  // template spectrum [rows][PS]
-    double2 *Zp;       // [F][n_band][S][D][PS]
+// Z_j(k) = sum_y A_{y + j}(k) conj(B_y(k)) is a correlation along y for every column k.  The
+// template rows go in blocks of M = COL_L - Dg + 1 rows, Dg the lags of a pass: block b
+// correlates its M template rows (zero up to COL_L) with the COL_L frame rows from its
+// first one on, and the lags j < Dg of that do not wrap around, so with transforms of
+// length COL_L along y
+//   Z_j = IDFT_j( sum_b DFT(A block b)(q) conj(DFT(B block b)(q)) ).
+// The sum over blocks stays in the transform domain: one inverse per workgroup, and COL_L /
+// M times one transform per frame value instead of Dg multiply-adds (direct sums over the
+// lags in registers took 11.8 of the 21.8 ms of a call over 16 frames of 6144x6160 at R = 65,
+// bound by FP64 issue; the blocks take 3.05, and for the six stacks of 91 frames of 512x512
+// to 4096x4096 at R = 17 0.92 ms instead of 2.15).  Windows of more than COL_LAGS lags take
+// several passes of equal width, pass g on the frame rows g Dg further down.
+//
+// The template's block transforms are made once (spec_tmpl) and read by every frame.  A
+// workgroup takes COL_KC columns (256-byte row pieces) and a band of blocks of one frame; a
+// thread holds 16 of the 256 values of its column, n = 16 a + r: a transform is a
+// 16-point one in registers, the twiddle W^(r c), an exchange over LDS, and a second
+// 16-point one, after which the thread holds q = r + 16 d.  The sums over blocks stay in 16
+// registers pairs in that order, in which the template transforms are stored, and feed the
+// inverse as they are.  Bound by the reads of the spectra: workgroups of the same columns
+// and blocks but other frames run together on one XCD, so that the template's transforms
+// come from its L2.
+constexpr int COL_T = 256;  // threads: COL_KC columns x 16
+static_assert(COL_L == 256 && COL_KC == 16, "16 values per thread, twice");
+
+struct ColArgs {
+    const double2 *A;  // frame spectra: frame f at A + f * a_batch, row r < H at + r * PS
+    double2 *Bt;       // template block transforms [n_blk][n_kt][16][COL_T]
+    double2 *Zp;       // [F][n_band][D][PS]
     int64_t a_batch;
-    int32_t PS, N2, D, NB, NBG, S, BY, n_band, n_kb;  // sub-ranges of DY template rows per chunk
+    int32_t PS, D, Dg, n_grp, M, H, n_blk, n_band, bpb, n_kt, nf;  // bpb: blocks per band
 };
 
-template <int DY>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_corr(CorrArgs a)
+// 4-point transform of v[0], v[S], v[2 S], v[3 S] in place (INV: conjugate kernel)
+template <bool INV, int S>
+__device__ __forceinline__ void dft4(double2 *v)
 {
-    extern __shared__ __align__(16) double2 al[];  // [YC + NBG * DY - 1][CORR_KW]
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int gb = w % a.NBG, s = w / a.NBG;       // lag block within the group, sub-range
-    const int32_t kb = blockIdx.x % a.n_kb, grp = blockIdx.x / a.n_kb;
-    const int32_t band = blockIdx.y, f = blockIdx.z;
-    const int32_t k = kb * CORR_KW + lane;
-    const int32_t blk = grp * a.NBG + gb;           // lag block
-    const bool act = blk < a.NB;
-    const int32_t j0 = blk * DY;                    // first lag of the thread
-    const int32_t jg0 = grp * a.NBG * DY;           // first lag of the group
-    const int32_t YC = a.S * DY;                   // template rows per chunk
-    const int32_t rows = YC + a.NBG * DY - 1;       // staged frame rows per chunk
-    const double2 *A = a.A + (int64_t)f * a.a_batch;
-    const int nthr = blockDim.x;
+    const double2 a = cadd(v[0], v[2 * S]), b = csub(v[0], v[2 * S]);
+    const double2 c = cadd(v[S], v[3 * S]), d = csub(v[S], v[3 * S]);
+    const double2 e = INV ? make_double2(-d.y, d.x) : make_double2(d.y, -d.x);  // -+ i d
+    v[0] = cadd(a, c);
+    v[S] = cadd(b, e);
+    v[2 * S] = csub(a, c);
+    v[3 * S] = csub(b, e);
+}
 
-    double2 acc[DY];
+// 16-point transform in registers, natural order in and out
+template <bool INV>
+__device__ __forceinline__ void dft16(double2 (&v)[16])
+{
+    constexpr double C = 0.92387953251128675613, Sn = 0.38268343236508977173, H = 0.70710678118654752440;
 #pragma unroll
-    for (int i = 0; i < DY; ++i) acc[i] = make_double2(0.0, 0.0);
+    for (int i = 0; i < 4; ++i) dft4<INV, 4>(v + i);  // v[i + 4 k] = term k of the inputs i, i + 4, ...
+    // W16^(i k)
+    constexpr double wr[10] = {1, C, H, Sn, 0, 0, -H, 0, 0, -C}, wi[10] = {0, -Sn, -H, -C, -1, 0, -H, 0, 0, Sn};
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+            const int e = i * k;
+            double2 &z = v[i + 4 * k];
+            if (e == 4)
+                z = INV ? make_double2(-z.y, z.x) : make_double2(z.y, -z.x);
+            else if (e == 2)
+                z = INV ? make_double2(H * (z.x - z.y), H * (z.x + z.y)) : make_double2(H * (z.x + z.y), H * (z.y - z.x));
+            else if (e == 6)
+                z = INV ? make_double2(-H * (z.x + z.y), H * (z.x - z.y))
+                        : make_double2(H * (z.y - z.x), -H * (z.x + z.y));
+            else
+                z = cmulf(z, make_double2(wr[e], INV ? -wi[e] : wi[e]));
+        }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dft4<INV, 1>(v + 4 * k);  // v[4 k + m] = output k + 4 m
+    // output c = k + 4 m sits in v[4 k + m]: transpose the 4 x 4
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int m = k + 1; m < 4; ++m) {
+            const double2 x = v[4 * k + m];
+            v[4 * k + m] = v[4 * m + k];
+            v[4 * m + k] = x;
+        }
+}
 
-    // The staged frame rows are a ring of `rows` LDS rows: frame row y_lo + jg0 + r of the
-    // band sits in LDS row r mod rows.  Chunk y0 needs rows (y0 - y_lo) + [0, rows); from
-    // the second chunk on only the YC rows it adds are staged, into the LDS rows of the YC
-    // rows the previous chunk alone needed.  Those rows (chunk rows rows - YC + wv + u nw of
-    // wave wv) are loaded into registers while the previous chunk is computed and stored
-    // after its barrier, when each wave has at most NPF of them.
-    constexpr int NPF = 4;
-    const int wv = t >> 6, nw = nthr >> 6;
-    const bool pipe = YC <= NPF * nw;  // every wave has at most NPF new rows per chunk
-    double2 pf[NPF];
+// First half of the 256-point transform of a column: thread r of 16 holds n = 16 a + r in
+// v[a]; afterwards z holds the values for the second half, which reads z[r][b][col] and
+// applies dft16.  wl[e] = W256^e.
+template <bool INV>
+__device__ __forceinline__ void col_first_half(double2 (&v)[16], double2 *z, const double2 *wl, int r, int col)
+{
+    dft16<INV>(v);
 #pragma unroll
-    for (int u = 0; u < NPF; ++u) pf[u] = make_double2(0.0, 0.0);
-    const int32_t y_lo = band * a.BY, y_hi = y_lo + a.BY;
-    int32_t ring0 = 0;  // LDS row of the chunk's first frame row
-    for (int32_t y0 = y_lo; y0 < y_hi; y0 += YC) {
-        __syncthreads();
-        if (pipe && y0 != y_lo) {
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) {  // a repeated last row stores the same value again
-                int32_t lr = ring0 + rows - YC + min(wv + u * nw, YC - 1);
-                if (lr >= rows) lr -= rows;
-                al[lr * CORR_KW + lane] = pf[u];
-            }
-        } else {
-            // frame rows y0 + jg0 + [r_lo, rows), columns kb * 64 ..: wave w stages rows
-            // r_lo + w, r_lo + w + nw, ... (lane = column), eight rows loaded together, then
-            // stored; a row index past the last is clamped to it on both sides (the same
-            // value stored to the same place again), so no load waits behind a branch
-            const int32_t r_lo = y0 == y_lo ? 0 : rows - YC;
-            const double2 *src = A + (int64_t)(y0 + jg0) * a.PS + kb * CORR_KW + lane;
-            for (int r0 = r_lo + wv; r0 < rows; r0 += 8 * nw) {
-                double2 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)min(r0 + u * nw, rows - 1) * a.PS];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    int32_t lr = ring0 + min(r0 + u * nw, rows - 1);
-                    if (lr >= rows) lr -= rows;
-                    al[lr * CORR_KW + lane] = v[u];
-                }
-            }
-        }
-        __syncthreads();
-        // the sub-range's template values (one window length, DY rows), then the next
-        // chunk's new frame rows: both issued before any is used, the template values first
-        // (the waits are in issue order).  Both unconditional: the last chunk reloads its own
-        // rows, a wave's rows past its last repeat it, so the loads stay ahead of the compute.
-        const int32_t ys = y0 + s * DY;  // first template row of this sub-range
-        double2 bq[DY];
-        {
-            const double2 *bp = a.B + (int64_t)ys * a.PS + k;
-#pragma unroll
-            for (int q = 0; q < DY; ++q) bq[q] = bp[(int64_t)q * a.PS];
-            __builtin_amdgcn_sched_barrier(0);  // keep the issue order
-            const int32_t y0n = y0 + YC < y_hi ? y0 + YC : y0;
-            const double2 *src = A + (int64_t)(y0n + jg0) * a.PS + kb * CORR_KW + lane;
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) pf[u] = src[(int64_t)(rows - YC + min(wv + u * nw, YC - 1)) * a.PS];
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (act) {
-            // window: chunk row of lag i at template row y is (y - y0) + (j0 - jg0) + i, in
-            // LDS row ring0 + that, wrapped
-            const int32_t c0 = ring0 + (ys - y0) + (j0 - jg0);
-            auto at = [&](int32_t cr) {  // cr = chunk row - (ys - y0) - (j0 - jg0) < rows
-                int32_t lr = c0 + cr;
-                if (lr >= rows) lr -= rows;
-                return al[lr * CORR_KW + lane];
-            };
-            double2 win[DY];
-#pragma unroll
-            for (int i = 0; i < DY - 1; ++i) win[i] = at(i);
-#pragma unroll
-            for (int q = 0; q < DY; ++q) {
-                // row ys + q: the window holds lags 0 .. DY-1 in slots (q + i) mod DY
-                win[(q + DY - 1) % DY] = at(q + DY - 1);
-                const double2 bv = bq[q];
-#pragma unroll
-                for (int i = 0; i < DY; ++i) {
-                    const double2 av = win[(q + i) % DY];
-                    // acc += av * conj(bv)
-                    acc[i].x = fma(av.x, bv.x, acc[i].x);
-                    acc[i].x = fma(av.y, bv.y, acc[i].x);
-                    acc[i].y = fma(av.y, bv.x, acc[i].y);
-                    acc[i].y = fma(-av.x, bv.y, acc[i].y);
-                }
-            }
-        }
-        ring0 += YC % rows;
-        if (ring0 >= rows) ring0 -= rows;
+    for (int c = 0; c < 16; ++c) {
+        double2 w = wl[r * c];
+        if (INV) w.y = -w.y;
+        z[(c * 16 + r) * COL_KC + col] = c == 0 ? v[c] : cmulf(v[c], w);
     }
-    if (act && k <= a.N2) {
-        double2 *zp = a.Zp + ((((int64_t)f * a.n_band + band) * a.S + s) * a.D) * a.PS + k;
+}
+
+__device__ __forceinline__ void col_second_read(double2 (&v)[16], const double2 *z, int r, int col)
+{
 #pragma unroll
-        for (int i = 0; i < DY; ++i)
-            if (j0 + i < a.D) zp[(int64_t)(j0 + i) * a.PS] = acc[i];
+    for (int b = 0; b < 16; ++b) v[b] = z[(r * 16 + b) * COL_KC + col];
+}
+
+__device__ __forceinline__ void col_table(double2 *wl)
+{
+    double s, c;
+    sincospi(-(double)threadIdx.x / (COL_L / 2), &s, &c);
+    wl[threadIdx.x] = make_double2(c, s);
+}
+
+// Transforms of the template's blocks: workgroup (column tile, block); B holds the row
+// spectra of the th template rows.
+__global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_tmpl(ColArgs a, const double2 *__restrict__ B,
+                                                                                     int32_t th)
+{
+    __shared__ double2 z[COL_L * COL_KC], wl[COL_L];
+    const int t = threadIdx.x, col = t & (COL_KC - 1), r = t / COL_KC;
+    const int32_t kt = blockIdx.x, blk = blockIdx.y;
+    col_table(wl);
+    __syncthreads();
+    const int32_t y0 = blk * a.M, ny = min(a.M, th - y0);
+    const double2 *src = B + (int64_t)y0 * a.PS + kt * COL_KC + col;
+    double2 v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int32_t y = 16 * i + r;
+        v[i] = src[(int64_t)min(y, ny - 1) * a.PS];
+        if (y >= ny) v[i] = make_double2(0.0, 0.0);
+    }
+    col_first_half<false>(v, z, wl, r, col);
+    __syncthreads();
+    col_second_read(v, z, r, col);
+    dft16<false>(v);
+    double2 *out = a.Bt + ((int64_t)blk * a.n_kt + kt) * (16 * COL_T) + t;
+#pragma unroll
+    for (int d = 0; d < 16; ++d) out[d * COL_T] = v[d];
+}
+
+__global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_cols(ColArgs a)
+{
+    __shared__ double2 z[COL_L * COL_KC], wl[COL_L];
+    const int t = threadIdx.x, col = t & (COL_KC - 1), r = t / COL_KC;
+    // frame fastest, then lag pass, band, column tile
+    int32_t id = xcd_logical_id((int32_t)blockIdx.x, (int32_t)gridDim.x);
+    const int32_t f = id % a.nf;
+    id /= a.nf;
+    const int32_t g = id % a.n_grp;
+    id /= a.n_grp;
+    const int32_t band = id % a.n_band, kt = id / a.n_band;
+    col_table(wl);
+    __syncthreads();
+    const double2 *A = a.A + (int64_t)f * a.a_batch + kt * COL_KC + col;
+    double2 acc[16];
+#pragma unroll
+    for (int d = 0; d < 16; ++d) acc[d] = make_double2(0.0, 0.0);
+    const int32_t b1 = min((band + 1) * a.bpb, a.n_blk);
+    for (int32_t blk = band * a.bpb; blk < b1; ++blk) {
+        const int32_t y0 = blk * a.M + g * a.Dg;
+        double2 v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = A[(int64_t)min(y0 + 16 * i + r, a.H - 1) * a.PS];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (y0 + 16 * i + r >= a.H) v[i] = make_double2(0.0, 0.0);  // rows past the frame
+        col_first_half<false>(v, z, wl, r, col);
+        // the template's transform is on its way while the exchange is waited for
+        const double2 *bt = a.Bt + ((int64_t)blk * a.n_kt + kt) * (16 * COL_T) + t;
+        double2 b[16];
+#pragma unroll
+        for (int d = 0; d < 16; ++d) b[d] = bt[d * COL_T];
+        __syncthreads();
+        col_second_read(v, z, r, col);
+        __syncthreads();  // before the next block's first half
+        dft16<false>(v);
+#pragma unroll
+        for (int d = 0; d < 16; ++d) {  // acc += v conj(b)
+            acc[d].x = fma(v[d].x, b[d].x, acc[d].x);
+            acc[d].x = fma(v[d].y, b[d].y, acc[d].x);
+            acc[d].y = fma(v[d].y, b[d].x, acc[d].y);
+            acc[d].y = fma(-v[d].x, b[d].y, acc[d].y);
+        }
+    }
+    // inverse: the sums are q = r + 16 d in acc[d], the order its first half takes
+    col_first_half<true>(acc, z, wl, r, col);
+    __syncthreads();
+    col_second_read(acc, z, r, col);
+    dft16<true>(acc);
+    double2 *zp = a.Zp + ((int64_t)f * a.n_band + band) * a.D * a.PS + kt * COL_KC + col;
+#pragma unroll
+    for (int d = 0; d < 16; ++d) {
+        const int32_t i = r + 16 * d, j = g * a.Dg + i;
+        if (i < a.Dg && j < a.D)
+            zp[(int64_t)j * a.PS] = make_double2(acc[d].x * (1.0 / COL_L), acc[d].y * (1.0 / COL_L));
     }
 }
 
 // ---- scores at the lags of the window --------------------------------------------------
 // S[f][j][m] = (1/P) sum_{k=0}^{N2} c_k Re(Z_j(k) e^{+2 pi i k m / P}), c_k = 1 at k = 0 and
-// k = N2, else 2; Z_j(k) the sum of the partials over bands and sub-ranges in order.  One
+// k = N2, else 2; Z_j(k) the sum of the partials over bands in order.  One
 // workgroup per (lag j, frame f); lanes stride over k; the D sums over m are reduced
 // over the workgroup in a fixed order.  The twiddles of a pass over m0 .. m0 + EVAL_M - 1
 // come from one table value and a recurrence, w(k, m + 1) = w(k, m) w(k, 1): scattered
@@ -489,9 +558,12 @@ __global__ void spec_walk(const reduce_offset_t *__restrict__ offs, int32_t N, i
 // Decision per frame, one workgroup each.  Kept: the exact maximum is not on an inner
 // border, and it exceeds the best spectral score outside its +-1 window by more than the
 // bound on the spectral error
-//   bound = factor ||a||_F ||b||_F,  factor = 4 eps (10 log2(P/2) + th + P + 18 + 2 EVAL_M),
+//   bound = factor ||a||_F ||b||_F,  factor = 4 eps (10 log2(P/2) + c (124 + n_blk) + P + 18 + 2 EVAL_M),
 // (eps = 2^-53; ||a||_F over the frame rows, ||b||_F over the template rows; first-order
-// rounding of the row transforms, the contraction, the inverse sums and their twiddles).  A kept frame
+// rounding of the row transforms, the contraction, the inverse sums and their twiddles).
+// The contraction's term: 5 eps per radix-2 level, 8 levels, of the transforms of a frame
+// block, of a template block and back, 4 eps for a product and n_blk additions, against
+// sum_b ||A_b|| ||B_b|| <= c ||a|| ||b||, c = ceil(COL_L / M) the blocks a frame row is in.  A kept frame
 // gets second = the larger of its window's runner-up and that spectral score, the margin
 // and NEAR_TIE from it, and loses CLIPPED (its window is a step of the full search).
 // fb[k] = 1 for the frames that take the full search; info[k] says why (1: inner border,
@@ -571,27 +643,12 @@ __global__ __launch_bounds__(64) void spec_list(const int32_t *__restrict__ fb, 
 // ---- host side ---------------------------------------------------------------------------
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-static int corr_dy(int32_t D)
-{
-    // lags per thread: the least padding of D, the larger block on ties
-    int best = 8;
-    int64_t waste = 1 << 30;
-    for (int dy : {12, 11, 10, 9, 8}) {
-        const int64_t wst = ceil_div(D, dy) * dy - D;
-        if (wst < waste) {
-            waste = wst;
-            best = dy;
-        }
-    }
-    return best;
-}
-
 struct FftLayout {
-    int32_t P, N2, log2n2, PS, D, DY, NB, NBG, n_grp, S, YS, BY, n_band, th_pad, rows_a, F;
-    size_t corr_lds, fft_lds;
+    int32_t P, N2, log2n2, PS, D, Dg, n_grp, M, n_blk, bpb, n_band, n_kt, F;
+    size_t fft_lds;
     RegPlan refine, full;
     int32_t Ffull;
-    size_t tw, mean_parts, mean, B, rowsq_b, A, rowsq_a, Zp, S_fft, cen, map, list, info, fb;
+    size_t tw, mean_parts, mean, Bt, rowsq_b, A, rowsq_a, Zp, S_fft, cen, map, list, info, fb;
     size_t part_r, sc_r, part_f, sc_f, total;
 };
 
@@ -606,39 +663,25 @@ static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
     L->N2 = P / 2;
     L->log2n2 = 0;
     while ((1 << L->log2n2) < L->N2) ++L->log2n2;
-    L->PS = (int32_t)(ceil_div(L->N2 + 1, CORR_KW) * CORR_KW);
+    L->n_kt = (int32_t)ceil_div(L->N2 + 1, COL_KC);
+    L->PS = L->n_kt * COL_KC;
     L->D = 2 * R + 1;
-    L->DY = corr_dy(L->D);
-    L->NB = (int32_t)ceil_div(L->D, L->DY);
-    // lag blocks per workgroup (fewer restagings of the frame rows) and sub-ranges of
-    // template rows (more waves on one chunk), each sub-range one window length per chunk,
-    // with the staged rows within CORR_LDS_MAX
-    L->YS = L->DY;
-    L->NBG = 0;
-    for (int32_t g = std::min<int32_t>(L->NB, 4); g >= 1 && !L->NBG; --g)
-        for (int32_t sr = 4; sr >= 1; --sr) {
-            const size_t lds = sizeof(double2) * CORR_KW * (size_t)(sr * L->YS + g * L->DY - 1);
-            if (lds <= CORR_LDS_MAX && 64 * g * sr <= 512) {
-                L->NBG = g;
-                L->S = sr;
-                L->corr_lds = lds;
-                break;
-            }
-        }
-    if (!L->NBG) return false;
-    L->n_grp = (int32_t)ceil_div(L->NB, L->NBG);
-    const int32_t YC = L->S * L->YS;
-    // template rows in bands of whole chunks: about 16 bands
-    L->BY = (int32_t)(ceil_div(ceil_div(th, 16), YC) * YC);
-    L->n_band = (int32_t)ceil_div(th, L->BY);
-    L->th_pad = L->n_band * L->BY;
-    // >= H: every lag of every padded template row, lag groups padded to whole groups
-    L->rows_a = L->th_pad + L->n_grp * L->NBG * L->DY;
+    // lags in passes of equal width, template rows in blocks of M
+    L->n_grp = (int32_t)ceil_div(L->D, COL_LAGS);
+    L->Dg = (int32_t)ceil_div(L->D, L->n_grp);
+    L->M = COL_L - L->Dg + 1;
+    L->n_blk = (int32_t)ceil_div(th, L->M);
+    // bands of blocks: about 1024 workgroups (two waves of two per compute unit) for four
+    // frames; the number of frames itself stays out of it, so that a frame's scores do not
+    // depend on how many it is searched with
+    const int32_t want = (int32_t)ceil_div(1024, 4 * (int64_t)L->n_kt * L->n_grp);
+    L->bpb = (int32_t)ceil_div(L->n_blk, std::min(want, L->n_blk));
+    L->n_band = (int32_t)ceil_div(L->n_blk, L->bpb);
     L->fft_lds = sizeof(double2) * (size_t)std::max<int32_t>(L->N2, 1024);
-    // frames per round of spectra: their spectra and contraction partials in about 1 GB
-    const size_t per_frame = sizeof(double2) * (size_t)L->PS *
-                             ((size_t)L->rows_a + (size_t)L->n_band * L->S * L->D) + sizeof(double) * L->rows_a;
-    L->F = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)N, (size_t(1) << 30) / per_frame));
+    // frames per round of spectra, the rounds of equal size
+    const size_t per_frame = sizeof(double2) * (size_t)L->PS * ((size_t)H + (size_t)L->n_band * L->D);
+    L->F = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)N, SPEC_ROUND_BYTES / per_frame));
+    L->F = (int32_t)ceil_div(N, ceil_div(N, L->F));
     L->refine = reg_plan(W, H, 1, R);
     L->full = reg_plan(W, H, R, R);
     if (L->refine.D == 0 || L->full.D == 0) return false;
@@ -653,11 +696,11 @@ static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
     L->tw = take(sizeof(double2) * P);
     L->mean_parts = take(sizeof(double) * (size_t)ceil_div(th, MEAN_ROWS));
     L->mean = take(sizeof(double));
-    L->B = take(sizeof(double2) * (size_t)L->PS * L->th_pad);
-    L->rowsq_b = take(sizeof(double) * (size_t)L->th_pad);
-    L->A = take(sizeof(double2) * (size_t)L->PS * L->rows_a * L->F);
-    L->rowsq_a = take(sizeof(double) * (size_t)L->rows_a * N);  // every frame's, for the decisions
-    L->Zp = take(sizeof(double2) * (size_t)L->PS * L->n_band * L->S * L->D * L->F);
+    L->Bt = take(sizeof(double2) * 16 * COL_T * (size_t)L->n_kt * L->n_blk);
+    L->rowsq_b = take(sizeof(double) * (size_t)th);
+    L->A = take(sizeof(double2) * (size_t)L->PS * H * L->F);  // the template's row spectra before the frames'
+    L->rowsq_a = take(sizeof(double) * (size_t)H * N);  // every frame's, for the decisions
+    L->Zp = take(sizeof(double2) * (size_t)L->PS * L->n_band * L->D * L->F);
     L->S_fft = take(sizeof(double) * (size_t)N * L->D * L->D);
     L->cen = take(sizeof(int32_t) * 2 * (size_t)N);
     L->map = take(sizeof(int32_t) * (size_t)N);
@@ -712,13 +755,6 @@ static void launch_fft_rows(const FftLayout &L, const RowSrc &src, int32_t rows_
     });
 }
 
-template <int DY>
-static void launch_corr(const CorrArgs &c, const FftLayout &L, int32_t nf, hipStream_t s)
-{
-    const dim3 grid((unsigned)(c.n_kb * L.n_grp), (unsigned)L.n_band, (unsigned)nf);
-    hipLaunchKernelGGL(spec_corr<DY>, grid, dim3((unsigned)(64 * L.NBG * L.S)), L.corr_lds, s, c);
-}
-
 }  // namespace rd
 
 using namespace rd;
@@ -749,7 +785,6 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
     auto at = [&](size_t off) { return static_cast<void *>(b + off); };
     double2 *tw = static_cast<double2 *>(at(L.tw));
     double *mean = static_cast<double *>(at(L.mean));
-    double2 *Bs = static_cast<double2 *>(at(L.B));
     double *rowsq_b = static_cast<double *>(at(L.rowsq_b));
     double2 *As = static_cast<double2 *>(at(L.A));
     double *rowsq_a = static_cast<double *>(at(L.rowsq_a));
@@ -761,7 +796,7 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
     int32_t *inf = info ? info : static_cast<int32_t *>(at(L.info));
     const int32_t R = radius, D = L.D;
     const int32_t tx0 = R, ty0 = R, tw_ = W - 2 * R, th = H - 2 * R;
-    const int64_t a_batch = (int64_t)L.PS * L.rows_a;
+    const int64_t a_batch = (int64_t)L.PS * H;
     ProfScope prof("register_fft", s);
 
     hipLaunchKernelGGL(fft_twiddles, dim3((unsigned)ceil_div(L.P, 256)), dim3(256), 0, s, tw, L.P);
@@ -769,50 +804,50 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
     {
         ProfScope p2("fft_rows", s);
         const RowSrc tsrc{ref + (int64_t)ty0 * W + tx0, 0, W, tw_, th, mean};
-        launch_fft_rows(L, tsrc, L.th_pad, 1, tw, Bs, 0, rowsq_b, s);
+        launch_fft_rows(L, tsrc, th, 1, tw, As, 0, rowsq_b, s);
     }
-    CorrArgs ca;
+    ColArgs ca;
     ca.A = As;
-    ca.B = Bs;
+    ca.Bt = static_cast<double2 *>(at(L.Bt));
     ca.Zp = Zp;
     ca.a_batch = a_batch;
     ca.PS = L.PS;
-    ca.N2 = L.N2;
     ca.D = D;
-    ca.NB = L.NB;
-    ca.NBG = L.NBG;
-    ca.S = L.S;
-    ca.BY = L.BY;
+    ca.Dg = L.Dg;
+    ca.n_grp = L.n_grp;
+    ca.M = L.M;
+    ca.H = H;
+    ca.n_blk = L.n_blk;
     ca.n_band = L.n_band;
-    ca.n_kb = (int32_t)ceil_div(L.N2 + 1, CORR_KW);
+    ca.bpb = L.bpb;
+    ca.n_kt = L.n_kt;
+    ca.nf = 0;
+    {
+        ProfScope p2("spec_corr", s);
+        hipLaunchKernelGGL(spec_tmpl, dim3((unsigned)L.n_kt, (unsigned)L.n_blk), dim3(COL_T), 0, s, ca, As, th);
+    }
     for (int32_t f0 = 0; f0 < N; f0 += L.F) {
         const int32_t nf = std::min(L.F, N - f0);
         {
             ProfScope p2("fft_rows", s);
             const RowSrc fsrc{frames + (int64_t)f0 * W * H, (int64_t)W * H, W, W, H, nullptr};
-            launch_fft_rows(L, fsrc, L.rows_a, nf, tw, As, a_batch, rowsq_a + (int64_t)f0 * L.rows_a, s);
+            launch_fft_rows(L, fsrc, H, nf, tw, As, a_batch, rowsq_a + (int64_t)f0 * H, s);
         }
         {
             ProfScope p2("spec_corr", s);
-            switch (L.DY) {
-            case 8: launch_corr<8>(ca, L, nf, s); break;
-            case 9: launch_corr<9>(ca, L, nf, s); break;
-            case 10: launch_corr<10>(ca, L, nf, s); break;
-            case 11: launch_corr<11>(ca, L, nf, s); break;
-            default: launch_corr<12>(ca, L, nf, s); break;
-            }
+            ca.nf = nf;
+            hipLaunchKernelGGL(spec_cols, dim3((unsigned)(L.n_kt * L.n_band * L.n_grp * nf)), dim3(COL_T), 0, s, ca);
         }
         {
             ProfScope p2("spec_eval", s);
             log2_dispatch(L.log2n2, [&](auto Lc) {
                 hipLaunchKernelGGL(spec_eval<decltype(Lc)::value>, dim3((unsigned)D, (unsigned)nf),
-                                   dim3(FFT_THREADS), sizeof(double2) * (L.N2 + 1), s, Zp, L.n_band * L.S, D, L.PS,
+                                   dim3(FFT_THREADS), sizeof(double2) * (L.N2 + 1), s, Zp, L.n_band, D, L.PS,
                                    tw, Sf + (int64_t)f0 * D * D);
             });
         }
-        hipLaunchKernelGGL(spec_pick, dim3((unsigned)nf), dim3(256), 0, s, Sf + (int64_t)f0 * D * D, D, R, out + f0,
-                           cen + 2 * f0);
     }
+    hipLaunchKernelGGL(spec_pick, dim3((unsigned)N), dim3(256), 0, s, Sf, D, R, out, cen);
     // exact +-1 windows around the spectral maxima, moved while their maximum lies on an
     // inner border; the decisions; the full direct search for the frames not settled
     {
@@ -827,10 +862,11 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
                             out, s);
         }
         const double eps = 1.1102230246251565e-16;  // 2^-53
-        const double factor = 4.0 * eps * (10.0 * L.log2n2 + (double)th + (double)L.P + 18.0 + 2.0 * EVAL_M);
+        const double factor = 4.0 * eps * (10.0 * L.log2n2 + (double)ceil_div(COL_L, L.M) * (124.0 + L.n_blk) + (double)L.P +
+                                            18.0 + 2.0 * EVAL_M);
         int32_t *fb = static_cast<int32_t *>(at(L.fb));
-        hipLaunchKernelGGL(spec_settle, dim3((unsigned)N), dim3(256), 0, s, out, Sf, D, R, rowsq_a, L.rows_a, rowsq_b,
-                           L.th_pad, factor, fb, inf);
+        hipLaunchKernelGGL(spec_settle, dim3((unsigned)N), dim3(256), 0, s, out, Sf, D, R, rowsq_a, H, rowsq_b, th,
+                           factor, fb, inf);
         hipLaunchKernelGGL(spec_list, dim3(1), dim3(64), 0, s, fb, N, list);
     }
     {
