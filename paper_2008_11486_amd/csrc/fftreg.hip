@@ -12,8 +12,8 @@
 //
 // with A_r, B_y the length-P DFTs of the rows (no wrap-around: x + R + dx <= W - 1 < P).
 // The rows are real, so only k = 0 .. P/2 is formed (Z at P - k is the conjugate).
-// Four steps: row spectra (one P/2-point complex FFT per row of two packed real rows,
-// Stockham radix-4 passes in LDS), the contraction Z over template rows (itself by
+// Four steps: row spectra (one P/2-point complex FFT per row of packed real values,
+// Stockham radix-16 passes in registers), the contraction Z over template rows (itself by
 // transforms along y, block by block), the inverse at the 2R+1 lags needed, and the
 // argmax.  The scores carry rounding of order 1e-13 relative to the largest, so the
 // offsets are taken from exact direct sums: a +-1 window around the spectral argmax
@@ -69,15 +69,115 @@ __global__ void fft_twiddles(double2 *__restrict__ tw, int32_t P)
     tw[t] = make_double2(c, s);
 }
 
+// 4-point transform of v[0], v[S], v[2 S], v[3 S] in place (INV: conjugate kernel)
+template <bool INV, int S>
+__device__ __forceinline__ void dft4(double2 *v)
+{
+    const double2 a = cadd(v[0], v[2 * S]), b = csub(v[0], v[2 * S]);
+    const double2 c = cadd(v[S], v[3 * S]), d = csub(v[S], v[3 * S]);
+    const double2 e = INV ? make_double2(-d.y, d.x) : make_double2(d.y, -d.x);  // -+ i d
+    v[0] = cadd(a, c);
+    v[S] = cadd(b, e);
+    v[2 * S] = csub(a, c);
+    v[3 * S] = csub(b, e);
+}
+
+// W16^e for the exponents that the register transforms need
+__device__ __forceinline__ double2 w16(int e)
+{
+    constexpr double C = 0.92387953251128675613, Sn = 0.38268343236508977173, H = 0.70710678118654752440;
+    constexpr double wr[10] = {1, C, H, Sn, 0, -Sn, -H, -C, -1, -C}, wi[10] = {0, -Sn, -H, -C, -1, -C, -H, -Sn, 0, Sn};
+    return make_double2(wr[e], wi[e]);
+}
+
+// 2-, 4- or 8-point transform of v[0], v[S], ..., v[(X - 1) S] in place, natural order
+template <int X, int S>
+__device__ __forceinline__ void dft_small(double2 *v)
+{
+    if constexpr (X == 2) {
+        const double2 a = v[0];
+        v[0] = cadd(a, v[S]);
+        v[S] = csub(a, v[S]);
+    } else if constexpr (X == 4) {
+        dft4<false, S>(v);
+    } else {
+        static_assert(X == 8, "radix");
+        constexpr double H = 0.70710678118654752440;
+        dft4<false, 2 * S>(v);          // even inputs: terms k at v[2 k S]
+        dft4<false, 2 * S>(v + S);      // odd inputs
+        double2 e[4], o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            e[k] = v[2 * k * S];
+            o[k] = v[(2 * k + 1) * S];
+        }
+        o[1] = make_double2(H * (o[1].x + o[1].y), H * (o[1].y - o[1].x));   // W8
+        o[2] = make_double2(o[2].y, -o[2].x);                                // -i
+        o[3] = make_double2(H * (o[3].y - o[3].x), -H * (o[3].x + o[3].y));  // W8^3
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k * S] = cadd(e[k], o[k]);
+            v[(k + 4) * S] = csub(e[k], o[k]);
+        }
+    }
+}
+
+// 16-point transform in registers, natural order in and out
+template <bool INV>
+__device__ __forceinline__ void dft16(double2 (&v)[16])
+{
+    constexpr double H = 0.70710678118654752440;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dft4<INV, 4>(v + i);  // v[i + 4 k] = term k of the inputs i, i + 4, ...
+    // W16^(i k)
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+            const int e = i * k;
+            double2 &z = v[i + 4 * k];
+            if (e == 4)
+                z = INV ? make_double2(-z.y, z.x) : make_double2(z.y, -z.x);
+            else if (e == 2)
+                z = INV ? make_double2(H * (z.x - z.y), H * (z.x + z.y)) : make_double2(H * (z.x + z.y), H * (z.y - z.x));
+            else if (e == 6)
+                z = INV ? make_double2(-H * (z.x + z.y), H * (z.x - z.y))
+                        : make_double2(H * (z.y - z.x), -H * (z.x + z.y));
+            else
+                z = cmulf(z, make_double2(w16(e).x, INV ? -w16(e).y : w16(e).y));
+        }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dft4<INV, 1>(v + 4 * k);  // v[4 k + m] = output k + 4 m
+    // output c = k + 4 m sits in v[4 k + m]: transpose the 4 x 4
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int m = k + 1; m < 4; ++m) {
+            const double2 x = v[4 * k + m];
+            v[4 * k + m] = v[4 * m + k];
+            v[4 * m + k] = x;
+        }
+}
+
 // ---- row spectra -------------------------------------------------------------------------
 // Rows of batch b: row r (r < nrows) holds x(u) = base[b * batch + r * pitch + u] - sub for
 // u < ncols, 0 for ncols <= u < P; rows nrows <= r < rows_out are zero.  Output: the
 // half spectrum X(k), k = 0 .. P/2, at spec + b * spec_batch + r * PS, and the sum of
 // squares of each row at rowsq[b * rows_out + r].  A row of P real values is packed as
-// z(n) = x(2n) + i x(2n+1), transformed with P/2-point Stockham passes (one radix-2 pass
-// first when log2(P/2) is odd, then radix-4), and unpacked:
+// z(n) = x(2n) + i x(2n+1), transformed over N2 = P/2 points, and unpacked:
 //   X(k) = E(k) - i w^k O(k),  E = (Z(k) + conj Z(N2-k)) / 2,  O = (Z(k) - conj Z(N2-k)) / 2,
-// w = exp(-2 pi i / P).  Small rows share a workgroup (1024 / (P/2) rows each).
+// w = exp(-2 pi i / P).
+//
+// A thread holds 16 of a row's values, so a row takes N2 / 16 threads and a workgroup of
+// 256 takes 4096 / N2 rows.  Stockham passes of radix 16 in registers: the first takes the
+// values as they are loaded, so N2 points pass through LDS twice (16 x 16 x N2/256; once for
+// N2 <= 256) and a third time for the partners of the unpacking.  Radix-4 passes moved a row
+// of 4096 through LDS seven times and read 18 thousand twiddles for it, which bound the
+// kernel at half the copy rate (3.45 ms for 16 frames of 6144x6160 and their template, 9.4 GB
+// moved, now 2.20; 11 frames of 4096x4096 0.79 -> 0.50 ms, at the copy rate); here the
+// second pass's twiddles come from a table of 256 in LDS, the last one's are products of
+// four table values.  LDS index i sits at i + i / 16: a
+// pass's stores are 16 values apart from lane to lane, which would fall on one bank.
 struct RowSrc {
     const float *base;
     int64_t batch, pitch;
@@ -85,157 +185,147 @@ struct RowSrc {
     const double *sub;  // device scalar subtracted from every value, or NULL
 };
 
+constexpr int FFT_V = 16;                                   // values per thread
+constexpr int FFT_POINTS = FFT_V * FFT_THREADS;             // complex values per workgroup
+constexpr int FFT_LDS = FFT_POINTS + FFT_POINTS / 16;       // padded
+static_assert(FFT_P_MAX / 2 <= FFT_POINTS, "a row fits one workgroup");
+
 template <int LOG2N2>
-__global__ __launch_bounds__(FFT_THREADS) void fft_rows(RowSrc src, int32_t rows_out, const double2 *__restrict__ tw,
-                                                        double2 *__restrict__ spec, int64_t spec_batch, int32_t PS,
-                                                        double *__restrict__ rowsq)
+__global__ __launch_bounds__(FFT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void fft_rows(
+    RowSrc src, int32_t rows_out, const double2 *__restrict__ tw, double2 *__restrict__ spec, int64_t spec_batch,
+    int32_t PS, double *__restrict__ rowsq)
 {
-    extern __shared__ __align__(16) double2 zl[];
     constexpr int32_t N2 = 1 << LOG2N2, P = 2 * N2;
-    constexpr int rpw = N2 >= 1024 ? 1 : 1024 / N2;  // rows per workgroup
-    constexpr int tpr = FFT_THREADS / rpw;           // threads per row
+    constexpr int tpr = N2 / FFT_V;                  // threads per row
+    constexpr int rpw = FFT_THREADS / tpr;           // rows per workgroup
+    constexpr int XL = N2 >= 256 ? N2 / 256 : N2 / 16;  // radix of the last pass (1: none)
+    static_assert(N2 >= 32, "rows of at least 64 values");
+    __shared__ double2 zl[FFT_LDS], w256[256];
     const int t = threadIdx.x, lr = t / tpr, lt = t - lr * tpr;
     const int32_t b = blockIdx.y;
     const int32_t r = blockIdx.x * rpw + lr;
-    double2 *z = zl + lr * N2;
+    double2 *z = zl + lr * (N2 + N2 / 16);
     const bool live = r < rows_out;
     const bool data = r < src.nrows;
     const double sub = src.sub ? *src.sub : 0.0;
     const float *row = src.base + (int64_t)b * src.batch + (int64_t)(data ? r : 0) * src.pitch;
 
-    // packed load and the row's sum of squares: the thread's NPT value pairs are loaded
-    // together (addresses clamped into the row, values past it replaced by zero), then
-    // converted and summed in the order of n
-    constexpr int NPT = N2 / tpr;
-    float f0[NPT], f1[NPT];
-    if (data) {
-        const int32_t last = src.ncols - 1;
+    // packed load: value pair n = lt + i tpr, as one 8-byte load where the row allows it
+    // (addresses clamped into the row, values past it replaced by zero)
+    float f0[FFT_V], f1[FFT_V];
+    const int32_t last = src.ncols - 1;
+    if ((reinterpret_cast<uintptr_t>(row) & 7u) == 0 && src.ncols >= 2) {
+        const int32_t lastp = (src.ncols >> 1) - 1;
 #pragma unroll
-        for (int i = 0; i < NPT; ++i) {
+        for (int i = 0; i < FFT_V; ++i) {
+            const float2 v = reinterpret_cast<const float2 *>(row)[min(lt + i * tpr, lastp)];
+            f0[i] = v.x;
+            f1[i] = v.y;
+        }
+        if (src.ncols & 1) {  // the odd last value has no pair
+            const float v = row[last];
+#pragma unroll
+            for (int i = 0; i < FFT_V; ++i)
+                if (2 * (lt + i * tpr) == last) f0[i] = v;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < FFT_V; ++i) {
             const int32_t u = 2 * (lt + i * tpr);
             f0[i] = row[min(u, last)];
             f1[i] = row[min(u + 1, last)];
         }
     }
-    // twiddles of a radix-4 pass (see below): w[c][q - 1] = w_{4L}^{q k}, k = j mod L of the
-    // thread's butterfly c.  Each pass's are loaded one pass ahead (the first pass's with
-    // the row), so no pass waits on them.
-    constexpr int32_t m4 = N2 >> 2;
-    constexpr int NB4 = m4 / tpr;                   // radix-4 butterflies per thread
-    constexpr int NP4 = LOG2N2 / 2;                 // radix-4 passes
-    constexpr int32_t L0 = (LOG2N2 & 1) ? 2 : 1;    // L of the first of them
-    static_assert(NP4 >= 1 && NB4 >= 1, "rows of at least 64 values");
-    auto tw_pass = [&](int32_t Lp, double2(&w)[NB4][3]) {
-#pragma unroll
-        for (int c = 0; c < NB4; ++c) {
-            const int32_t step = (P / 4 / Lp) * ((lt + c * tpr) & (Lp - 1));  // w_{4L}^k = tw[k P / (4L)]
-#pragma unroll
-            for (int q = 1; q < 4; ++q) w[c][q - 1] = tw[q * step];
-        }
-    };
-    double2 wn[NB4][3];
-    tw_pass(L0, wn);
+    if constexpr (N2 >= 256) w256[t] = tw[t * (P / 256)];
+    double2 v[FFT_V];
     double sq = 0.0;
 #pragma unroll
-    for (int i = 0; i < NPT; ++i) {
-        const int32_t n = lt + i * tpr, u = 2 * n;
+    for (int i = 0; i < FFT_V; ++i) {
+        const int32_t u = 2 * (lt + i * tpr);
         const double x0 = (data && u < src.ncols) ? (double)f0[i] - sub : 0.0;
         const double x1 = (data && u + 1 < src.ncols) ? (double)f1[i] - sub : 0.0;
         sq = fma(x0, x0, sq);
         sq = fma(x1, x1, sq);
-        z[n] = make_double2(x0, x1);
+        v[i] = make_double2(x0, x1);
     }
-    // the row's sum of squares: over the row's threads in a fixed order
+    // the row's sum of squares: over the row's lanes of a wave, then over its waves in order
     {
-        __shared__ double part[FFT_THREADS];
-        part[t] = sq;
-        __syncthreads();
-        if (lt == 0 && live) {
-            double s = 0.0;
-            for (int i = 0; i < tpr; ++i) s += part[lr * tpr + i];
-            rowsq[(int64_t)b * rows_out + r] = s;
+        __shared__ double part[FFT_THREADS / 64];
+#pragma unroll
+        for (int off = (tpr < 64 ? tpr : 64) / 2; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+        if constexpr (tpr > 64) {
+            if ((t & 63) == 0) part[t >> 6] = sq;
+            __syncthreads();
+            if (lt == 0) {
+                sq = 0.0;
+                for (int i = 0; i < tpr / 64; ++i) sq += part[t / 64 + i];
+            }
         }
+        if (lt == 0 && live) rowsq[(int64_t)b * rows_out + r] = sq;
     }
+
+    // pass L = 1: butterfly j = lt, output q at 16 j + q
+    dft16<false>(v);
+#pragma unroll
+    for (int q = 0; q < FFT_V; ++q) z[17 * lt + q] = v[q];
     __syncthreads();
-
-    // Stockham passes: L = product of the radices done so far; butterfly j reads
-    // z[j + q m] (m = N2 / radix), twiddles input q by w_{L radix}^{q (j mod L)}, and writes
-    // output q at (j / L) L radix + (j mod L) + q L.  Twiddle w_M^e = tw[e P / M].
-    if (LOG2N2 & 1) {  // radix 2
-        constexpr int32_t m = N2 >> 1;
-        constexpr int NB2 = m / tpr;  // butterflies per thread
-        double2 v[NB2][2];
+    // every later pass reads its values at lt + i tpr
+    const double2 *zr = z + lt;
+    auto at = [&](int i) { return zr[((lt + i * tpr) >> 4) + i * tpr]; };
+    if constexpr (N2 >= 256) {
+        // pass L = 16: output q at (j - k) 16 + k + 16 q, k = j mod 16, twiddles W256^(q k)
+        const int k = lt & 15;
 #pragma unroll
-        for (int c = 0; c < NB2; ++c) {
-            const int32_t j = lt + c * tpr;
-            v[c][0] = z[j];
-            v[c][1] = z[j + m];
-        }
+        for (int q = 0; q < FFT_V; ++q) v[q] = q == 0 ? at(q) : cmulf(at(q), w256[q * k]);
+        dft16<false>(v);
         __syncthreads();
+        if constexpr (XL > 1) {
+            double2 *zo = z + (lt - k) * 17 + k;
 #pragma unroll
-        for (int c = 0; c < NB2; ++c) {
-            const int32_t j = lt + c * tpr;
-            z[2 * j] = cadd(v[c][0], v[c][1]);  // L = 1: output q at 2 j + q
-            z[2 * j + 1] = csub(v[c][0], v[c][1]);
+            for (int q = 0; q < FFT_V; ++q) zo[17 * q] = v[q];
+            __syncthreads();
         }
-        __syncthreads();
     }
-    // the unpacking twiddles tw[k], k = lt, lt + tpr, ... <= N2, are loaded with the last
-    // pass's LDS reads
-    constexpr int NK = N2 / tpr + 1;
-    double2 wk[NK];
+    if constexpr (XL > 1) {
+        // last pass, radix XL: butterflies j = lt + c tpr, inputs q at value c + q (16 / XL),
+        // twiddles W_N2^(q j) from W^j, W^2j, W^4j, W^8j; outputs where the inputs were
+        constexpr int C = FFT_V / XL;
 #pragma unroll
-    for (int p = 0; p < NP4; ++p) {
-        const int32_t L = L0 << (2 * p);
-        double2 w[NB4][3];
-#pragma unroll
-        for (int c = 0; c < NB4; ++c)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) w[c][q] = wn[c][q];
-        if (p + 1 < NP4) {
-            tw_pass(4 * L, wn);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NK; ++i) wk[i] = tw[min(lt + i * tpr, N2)];
-        }
-        double2 v[NB4][4];
-#pragma unroll
-        for (int c = 0; c < NB4; ++c) {
-            const int32_t j = lt + c * tpr;
-            v[c][0] = z[j];
-#pragma unroll
-            for (int q = 1; q < 4; ++q) v[c][q] = cmul(z[j + q * m4], w[c][q - 1]);
-        }
+        for (int i = 0; i < FFT_V; ++i) v[i] = at(i);
         __syncthreads();
 #pragma unroll
-        for (int c = 0; c < NB4; ++c) {
-            const int32_t j = lt + c * tpr;
-            const int32_t k = j & (L - 1);
-            const double2 a = cadd(v[c][0], v[c][2]), bb = csub(v[c][0], v[c][2]);
-            const double2 cc = cadd(v[c][1], v[c][3]), d = csub(v[c][1], v[c][3]);
-            const int32_t o = (j - k) * 4 + k;  // (j / L) L 4 + k
-            z[o] = cadd(a, cc);
-            z[o + L] = make_double2(bb.x + d.y, bb.y - d.x);      // b - i d
-            z[o + 2 * L] = csub(a, cc);
-            z[o + 3 * L] = make_double2(bb.x - d.y, bb.y + d.x);  // b + i d
+        for (int c = 0; c < C; ++c) {
+            const int32_t j2 = 2 * (lt + c * tpr);  // W_N2^e = tw[2 e]
+            double2 w[XL];
+#pragma unroll
+            for (int q = 1; q < XL; ++q) {
+                const int hi = 1 << (31 - __builtin_clz(q));
+                w[q] = q == hi ? tw[q * j2] : cmulf(w[hi], w[q - hi]);
+            }
+#pragma unroll
+            for (int q = 1; q < XL; ++q) v[c + q * C] = cmulf(v[c + q * C], w[q]);
+            if constexpr (XL == 16)
+                dft16<false>(v);
+            else
+                dft_small<XL, C>(v + c);
         }
-        __syncthreads();
     }
-
-    // unpack the two real transforms into the half spectrum of the row
+    // unpack the two real transforms into the half spectrum of the row: v[i] = Z(lt + i tpr)
+#pragma unroll
+    for (int i = 0; i < FFT_V; ++i) z[lt + i * tpr + ((lt + i * tpr) >> 4)] = v[i];
+    __syncthreads();
     if (live) {
         double2 *out = spec + (int64_t)b * spec_batch + (int64_t)r * PS;
 #pragma unroll
-        for (int i = 0; i < NK; ++i) {
-            const int32_t k = lt + i * tpr;
-            if (k > N2) break;
-            const double2 zk = z[k & (N2 - 1)];
-            const double2 zc = z[(N2 - k) & (N2 - 1)];
+        for (int i = 0; i < FFT_V; ++i) {
+            const int32_t k = lt + i * tpr, kc = (N2 - k) & (N2 - 1);
+            const double2 zk = v[i], zc = z[kc + (kc >> 4)];
             const double2 e = make_double2(0.5 * (zk.x + zc.x), 0.5 * (zk.y - zc.y));
             const double2 o = make_double2(0.5 * (zk.x - zc.x), 0.5 * (zk.y + zc.y));
-            const double2 wo = cmul(wk[i], o);  // wk[i] = tw[k], k <= N2 < P
+            const double2 wo = cmulf(tw[k], o);
             out[k] = make_double2(e.x + wo.y, e.y - wo.x);  // E - i w O
         }
+        if (lt == 0) out[N2] = make_double2(v[0].x - v[0].y, 0.0);
     }
 }
 
@@ -272,57 +362,6 @@ struct ColArgs {
     int64_t a_batch;
     int32_t PS, D, Dg, n_grp, M, H, n_blk, n_band, bpb, n_kt, nf;  // bpb: blocks per band
 };
-
-// 4-point transform of v[0], v[S], v[2 S], v[3 S] in place (INV: conjugate kernel)
-template <bool INV, int S>
-__device__ __forceinline__ void dft4(double2 *v)
-{
-    const double2 a = cadd(v[0], v[2 * S]), b = csub(v[0], v[2 * S]);
-    const double2 c = cadd(v[S], v[3 * S]), d = csub(v[S], v[3 * S]);
-    const double2 e = INV ? make_double2(-d.y, d.x) : make_double2(d.y, -d.x);  // -+ i d
-    v[0] = cadd(a, c);
-    v[S] = cadd(b, e);
-    v[2 * S] = csub(a, c);
-    v[3 * S] = csub(b, e);
-}
-
-// 16-point transform in registers, natural order in and out
-template <bool INV>
-__device__ __forceinline__ void dft16(double2 (&v)[16])
-{
-    constexpr double C = 0.92387953251128675613, Sn = 0.38268343236508977173, H = 0.70710678118654752440;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) dft4<INV, 4>(v + i);  // v[i + 4 k] = term k of the inputs i, i + 4, ...
-    // W16^(i k)
-    constexpr double wr[10] = {1, C, H, Sn, 0, 0, -H, 0, 0, -C}, wi[10] = {0, -Sn, -H, -C, -1, 0, -H, 0, 0, Sn};
-#pragma unroll
-    for (int i = 1; i < 4; ++i)
-#pragma unroll
-        for (int k = 1; k < 4; ++k) {
-            const int e = i * k;
-            double2 &z = v[i + 4 * k];
-            if (e == 4)
-                z = INV ? make_double2(-z.y, z.x) : make_double2(z.y, -z.x);
-            else if (e == 2)
-                z = INV ? make_double2(H * (z.x - z.y), H * (z.x + z.y)) : make_double2(H * (z.x + z.y), H * (z.y - z.x));
-            else if (e == 6)
-                z = INV ? make_double2(-H * (z.x + z.y), H * (z.x - z.y))
-                        : make_double2(H * (z.y - z.x), -H * (z.x + z.y));
-            else
-                z = cmulf(z, make_double2(wr[e], INV ? -wi[e] : wi[e]));
-        }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) dft4<INV, 1>(v + 4 * k);  // v[4 k + m] = output k + 4 m
-    // output c = k + 4 m sits in v[4 k + m]: transpose the 4 x 4
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int m = k + 1; m < 4; ++m) {
-            const double2 x = v[4 * k + m];
-            v[4 * k + m] = v[4 * m + k];
-            v[4 * m + k] = x;
-        }
-}
 
 // First half of the 256-point transform of a column: thread r of 16 holds n = 16 a + r in
 // v[a]; afterwards z holds the values for the second half, which reads z[r][b][col] and
@@ -645,7 +684,6 @@ static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct FftLayout {
     int32_t P, N2, log2n2, PS, D, Dg, n_grp, M, n_blk, bpb, n_band, n_kt, F;
-    size_t fft_lds;
     RegPlan refine, full;
     int32_t Ffull;
     size_t tw, mean_parts, mean, Bt, rowsq_b, A, rowsq_a, Zp, S_fft, cen, map, list, info, fb;
@@ -677,7 +715,6 @@ static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
     const int32_t want = (int32_t)ceil_div(1024, 4 * (int64_t)L->n_kt * L->n_grp);
     L->bpb = (int32_t)ceil_div(L->n_blk, std::min(want, L->n_blk));
     L->n_band = (int32_t)ceil_div(L->n_blk, L->bpb);
-    L->fft_lds = sizeof(double2) * (size_t)std::max<int32_t>(L->N2, 1024);
     // frames per round of spectra, the rounds of equal size
     const size_t per_frame = sizeof(double2) * (size_t)L->PS * ((size_t)H + (size_t)L->n_band * L->D);
     L->F = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)N, SPEC_ROUND_BYTES / per_frame));
@@ -747,10 +784,10 @@ static void log2_dispatch(int32_t log2n2, F &&f)
 static void launch_fft_rows(const FftLayout &L, const RowSrc &src, int32_t rows_out, int32_t batches,
                             const double2 *tw, double2 *spec, int64_t spec_batch, double *rowsq, hipStream_t s)
 {
-    const int rpw = L.N2 >= 1024 ? 1 : 1024 / L.N2;
+    const int rpw = FFT_POINTS / L.N2;
     const dim3 grid((unsigned)ceil_div(rows_out, rpw), (unsigned)batches);
     log2_dispatch(L.log2n2, [&](auto Lc) {
-        hipLaunchKernelGGL(fft_rows<decltype(Lc)::value>, grid, dim3(FFT_THREADS), L.fft_lds, s, src, rows_out, tw,
+        hipLaunchKernelGGL(fft_rows<decltype(Lc)::value>, grid, dim3(FFT_THREADS), 0, s, src, rows_out, tw,
                            spec, spec_batch, L.PS, rowsq);
     });
 }

@@ -12,7 +12,9 @@ import torch
 pytestmark = pytest.mark.gpu
 
 # (R, N, W, H): template rows th = H - 2R, blocks of M = 257 - lags of a pass
-CASES = [(1, 2, 64, 3),        # th = 1
+# and the row transform at every length, with odd and even widths and row starts
+CASES = [(4, 2, w, 24) for w in (60, 128, 255, 512, 1001, 2048, 4095, 8192)] + [(5, 2, 513, 25)] + [
+         (1, 2, 64, 3),        # th = 1
          (8, 2, 70, 256),      # M = 240, th = M
          (8, 3, 70, 257),      # th = M + 1
          (17, 2, 96, 700),     # three blocks, the last ragged
