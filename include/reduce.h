@@ -129,7 +129,7 @@ int reduce_register(const float *ref, const float *frames, int32_t W, int32_t H,
  * half spectrum of real rows), Z_j(k) = sum_y A_{y+j}(k) conj(B_y(k)) is formed for the
  * 2R+1 row lags j, and S at the 2R+1 column lags is the inverse transform there.  The
  * offsets then come from exact direct sums: a +-1 window around the spectral argmax
- * (moved while its maximum lies on an inner border) is kept when its exact peak
+ * is kept when its maximum is not on an inner border of it and its exact peak
  * exceeds every spectral score outside it by more than a bound on the spectral
  * rounding error, 4 eps (10 log2(P/2) + c (124 + n_blk) + P + 50) ||frame rows||
  * ||template rows|| (eps = 2^-53, Frobenius norms; n_blk blocks of the template rows, c of
@@ -140,8 +140,8 @@ int reduce_register(const float *ref, const float *frames, int32_t W, int32_t H,
  *   ref, frames, out as reduce_register (radius_max = radius);
  *   scores  device double [N][2R+1][2R+1] or NULL: the spectral scores (layout of
  *           reduce_register's), before the exact refinement;
- *   info    device int32 [N] or NULL: per frame 0 (kept), or 1 (maximum still on an
- *           inner border) | 2 (not clear of the error bound): the full search ran;
+ *   info    device int32 [N] or NULL: per frame 0 (kept), or 1 (maximum on an inner
+ *           border) | 2 (not clear of the error bound): the full search ran;
  *   ws      device workspace of reduce_register_fft_ws(W, H, N, radius) bytes.
  * Errors: radius < 1 or no template -> RANGE; W > 8192, N > 65535 or radius > 511 ->
  * UNSUPPORTED; small ws -> WORKSPACE. */

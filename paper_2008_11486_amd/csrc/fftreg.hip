@@ -15,12 +15,12 @@
 // Four steps: row spectra (one P/2-point complex FFT per row of packed real values,
 // Stockham radix-16 passes in registers), the contraction Z over template rows (itself by
 // transforms along y, block by block), the inverse at the 2R+1 lags needed, and the
-// argmax.  The scores carry rounding of order 1e-13 relative to the largest, so the
-// offsets are taken from exact direct sums: a +-1 window around the spectral argmax
-// (moved while its maximum sits on an inner border), kept when its exact peak exceeds
-// every spectral score outside the window by more than a bound on the spectral error,
-// and otherwise the full direct search for that frame.  The results (integer and
-// sub-pixel offsets, peak, flags) are therefore those of the direct search.
+// argmax.  The scores carry rounding of order 1e-14 relative to the largest, so the
+// offsets are taken from exact direct sums: a +-1 window around the spectral argmax, kept
+// when its maximum is not on an inner border of it and its exact peak exceeds every
+// spectral score outside the window by more than a bound on the spectral error, and
+// otherwise the full direct search for that frame.  The results (integer and sub-pixel
+// offsets, peak, flags) are therefore those of the direct search.
 #include <algorithm>
 #include <string>
 #include <type_traits>
@@ -31,8 +31,10 @@
 
 namespace rd {
 
-void register_mean(const float *ref, int32_t W, int32_t tx0, int32_t ty0, int32_t tw, int32_t th,
-                   double *mean_parts, double *mean, hipStream_t s);
+void register_mean_final(const double *mean_parts, int32_t nparts, double count, double *mean, hipStream_t s);
+int32_t register_small_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
+                              int32_t R, int32_t Rmax, const int32_t *centers, int32_t tx0, int32_t ty0, int32_t tw,
+                              int32_t th, const double *mean, double *partial, hipStream_t s);
 void register_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
                      int32_t R, int32_t Rmax, const int32_t *centers, const int32_t *map, int32_t tx0, int32_t ty0,
                      int32_t tw, int32_t th, const double *mean, double *partial, double *sc, reduce_offset_t *out,
@@ -44,7 +46,6 @@ constexpr int COL_L = 256;             // rows per block of the contraction (tra
 constexpr int COL_KC = 16;             // spectrum columns per contraction workgroup
 constexpr int COL_LAGS = 144;          // most lags per pass: a block then adds at least 113 template rows
 constexpr size_t SPEC_ROUND_BYTES = size_t(2) << 30;  // spectra and partials of the frames of one round
-constexpr int32_t FFT_MAX_MOVES = 2;   // window moves of the exact refinement (then the full search)
 constexpr size_t FFT_FALLBACK_BYTES = size_t(256) << 20;
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
@@ -59,10 +60,20 @@ __device__ __forceinline__ double2 cmulf(double2 a, double2 b)
     return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 
-// tw[t] = exp(-2 pi i t / P), t in [0, P)
-__global__ void fft_twiddles(double2 *__restrict__ tw, int32_t P)
+// The first n_parts workgroups: the sums of the template's mean (register_mean's parts); the
+// others: tw[t] = exp(-2 pi i t / P), t in [0, P).
+__global__ __launch_bounds__(MEAN_THREADS) void spec_prepare(const float *__restrict__ ref, int32_t W, int32_t tx0,
+                                                             int32_t ty0, int32_t tw_, int32_t th, int32_t n_parts,
+                                                             double *__restrict__ part, double2 *__restrict__ tw,
+                                                             int32_t P)
 {
-    const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double scratch[MEAN_THREADS / 64];
+    if ((int32_t)blockIdx.x < n_parts) {
+        const double s = tmpl_part_sum(ref, W, tx0, ty0, tw_, th, blockIdx.x, scratch);
+        if (threadIdx.x == 0) part[blockIdx.x] = s;
+        return;
+    }
+    const int32_t t = (blockIdx.x - n_parts) * MEAN_THREADS + threadIdx.x;
     if (t >= P) return;
     double s, c;
     sincospi(-2.0 * (double)t / (double)P, &s, &c);
@@ -560,37 +571,29 @@ __global__ __launch_bounds__(FFT_THREADS) void spec_eval(const double2 *__restri
     }
 }
 
-// Argmax of the spectral scores (full window, centre 0) and the window centre of the
-// exact refinement.
-__global__ __launch_bounds__(256) void spec_pick(const double *__restrict__ S, int32_t D, int32_t R,
-                                                 reduce_offset_t *__restrict__ off, int32_t *__restrict__ centres)
-{
-    __shared__ Best scratch[4];
-    const int32_t f = blockIdx.x;
-    pick_frame(S + (int64_t)f * D * D, D, R, R, 0, 0, off + f, scratch);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        centres[2 * f] = off[f].dx;
-        centres[2 * f + 1] = off[f].dy;
-    }
-}
+// Argmax of the spectral scores (full window, centre 0): the window centre of the exact
+// refinement.  Equal scores go to the smaller index, as in pick_frame.
+constexpr int PICK_THREADS = 1024;
 
-// One window move of the refinement: a frame whose exact maximum lies on a border of its
-// +-1 window strictly inside +-R gets its centre on that maximum and its slot.
-__global__ void spec_walk(const reduce_offset_t *__restrict__ offs, int32_t N, int32_t R, int32_t *__restrict__ centres,
-                          int32_t *__restrict__ map)
+__global__ __launch_bounds__(PICK_THREADS) void spec_pick(const double *__restrict__ S, int32_t D, int32_t R,
+                                                          int32_t *__restrict__ centres)
 {
-    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    const reduce_offset_t o = offs[k];
-    const bool bx = (o.flags & REDUCE_EDGE_X) && o.dx > -R && o.dx < R;
-    const bool by = (o.flags & REDUCE_EDGE_Y) && o.dy > -R && o.dy < R;
-    if (bx || by) {
-        centres[2 * k] = o.dx;
-        centres[2 * k + 1] = o.dy;
-        map[k] = k;
-    } else {
-        map[k] = -1;
+    __shared__ Best scratch[PICK_THREADS / 64];
+    const int32_t f = blockIdx.x, n = D * D;
+    const double *Sf = S + (int64_t)f * n;
+    Best b{-INFINITY, 0x7fffffff};
+    for (int32_t c0 = threadIdx.x; c0 < n; c0 += 4 * PICK_THREADS) {
+        double v[4];  // loaded together
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = Sf[min(c0 + u * PICK_THREADS, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) b = better_of(b, Best{v[u], min(c0 + u * PICK_THREADS, n - 1)});
+    }
+    b = block_best(b, scratch);
+    if (threadIdx.x == 0) {
+        const int32_t i = b.i < n ? b.i : 0;  // no score above -inf (NaN): any window, the bound settles nothing
+        centres[2 * f] = i % D - R;
+        centres[2 * f + 1] = i / D - R;
     }
 }
 
@@ -605,28 +608,63 @@ __global__ void spec_walk(const reduce_offset_t *__restrict__ offs, int32_t N, i
 // sum_b ||A_b|| ||B_b|| <= c ||a|| ||b||, c = ceil(COL_L / M) the blocks a frame row is in.  A kept frame
 // gets second = the larger of its window's runner-up and that spectral score, the margin
 // and NEAR_TIE from it, and loses CLIPPED (its window is a step of the full search).
-// fb[k] = 1 for the frames that take the full search; info[k] says why (1: inner border,
-// 2: not clear of the bound).
-__global__ __launch_bounds__(256) void spec_settle(reduce_offset_t *__restrict__ offs, const double *__restrict__ S,
-                                                   int32_t D, int32_t R, const double *__restrict__ rowsq_a,
-                                                   int32_t rows_a, const double *__restrict__ rowsq_b,
-                                                   int32_t rows_b, double factor, int32_t *__restrict__ fb,
-                                                   int32_t *__restrict__ info)
+// fb[k] = k for the frames that take the full search, else -1 (the slots of that search);
+// info[k] says why (1: inner border, 2: not clear of the bound).
+// The exact scores of the window come as the tile partials of score_small<3>.
+__global__ __launch_bounds__(PICK_THREADS) void spec_settle(const double *__restrict__ partial, int32_t n_tiles,
+                                                            const int32_t *__restrict__ centres,
+                                                            const double *__restrict__ S, int32_t D, int32_t R,
+                                                            const double *__restrict__ rowsq_a, int32_t rows_a,
+                                                            const double *__restrict__ rowsq_b, int32_t rows_b,
+                                                            double factor, reduce_offset_t *__restrict__ offs,
+                                                            int32_t *__restrict__ fb, int32_t *__restrict__ info)
 {
-    __shared__ double red[4];
+    constexpr int NW = PICK_THREADS / 64;
+    __shared__ double red[NW][9];
+    __shared__ double win[9];
+    __shared__ Best scratch[NW];
+    __shared__ reduce_offset_t o_sh;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int32_t k = blockIdx.x;
-    const reduce_offset_t o0 = offs[k];
-    // ||a||^2, ||b||^2: threads stride over rows, then the waves in order
+    const int32_t cx = centres[2 * k], cy = centres[2 * k + 1];
+    // the 3 x 3 exact scores: threads stride over tiles, lanes by a fixed butterfly, waves in order
+    {
+        double s[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) s[q] = 0.0;
+        const double *pk = partial + (int64_t)k * n_tiles * 9;
+        for (int32_t i = t; i < n_tiles; i += PICK_THREADS)
+#pragma unroll
+            for (int q = 0; q < 9; ++q) s[q] += pk[(int64_t)i * 9 + q];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) s[q] += __shfl_xor(s[q], off, 64);
+            if (lane == q) red[wv][q] = s[q];
+        }
+        __syncthreads();
+        if (t < 9) {
+            double v = 0.0;
+            for (int w = 0; w < NW; ++w) v += red[w][t];
+            const int32_t dx = cx - 1 + t % 3, dy = cy - 1 + t / 3;
+            win[t] = dx >= -R && dx <= R && dy >= -R && dy <= R ? v : -INFINITY;
+        }
+        __syncthreads();
+        pick_frame(win, 3, 1, R, cx, cy, &o_sh, scratch);
+        __syncthreads();
+    }
+    const reduce_offset_t o0 = o_sh;
+    // over the workgroup: lanes by a fixed butterfly, then the waves in order
     auto block_sum = [&](const double *v, int32_t n) {
         double s = 0.0;
-        for (int32_t r = t; r < n; r += 256) s += v[r];
+        for (int32_t r = t; r < n; r += PICK_THREADS) s += v[r];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        if (lane == 0) red[wv] = s;
         __syncthreads();
-        const double tot = red[0] + red[1] + red[2] + red[3];
+        if (lane == 0) red[wv][0] = s;
         __syncthreads();
+        double tot = 0.0;
+        for (int w = 0; w < NW; ++w) tot += red[w][0];
         return tot;
     };
     const double aa = block_sum(rowsq_a + (int64_t)k * rows_a, rows_a);
@@ -634,23 +672,31 @@ __global__ __launch_bounds__(256) void spec_settle(reduce_offset_t *__restrict__
     // best spectral score outside the +-1 window around the exact maximum
     const double *Sk = S + (int64_t)k * D * D;
     double best = -INFINITY;
-    for (int32_t c = t; c < D * D; c += 256) {
-        const int32_t jj = c / D, ii = c - jj * D;
-        if (abs(ii - R - o0.dx) <= 1 && abs(jj - R - o0.dy) <= 1) continue;
-        best = fmax(best, Sk[c]);
+    for (int32_t c0 = t; c0 < D * D; c0 += 4 * PICK_THREADS) {
+        double v[4];  // loaded together
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = Sk[min(c0 + u * PICK_THREADS, D * D - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t c = min(c0 + u * PICK_THREADS, D * D - 1);
+            const int32_t jj = c / D, ii = c - jj * D;
+            if (abs(ii - R - o0.dx) > 1 || abs(jj - R - o0.dy) > 1) best = fmax(best, v[u]);
+        }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off, 64));
-    if (lane == 0) red[wv] = best;
+    __syncthreads();
+    if (lane == 0) red[wv][0] = best;
     __syncthreads();
     if (t != 0) return;
-    const double out_best = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    double out_best = red[0][0];
+    for (int w = 1; w < NW; ++w) out_best = fmax(out_best, red[w][0]);
     const double bound = factor * sqrt(aa) * sqrt(bb);
     reduce_offset_t o = o0;
     const bool border = ((o.flags & REDUCE_EDGE_X) && o.dx > -R && o.dx < R) ||
                         ((o.flags & REDUCE_EDGE_Y) && o.dy > -R && o.dy < R);
     const bool unsure = !(o.peak > out_best + bound);
-    fb[k] = (border || unsure) ? 1 : 0;
+    fb[k] = border || unsure ? k : -1;
     if (info) info[k] = (border ? 1 : 0) | (unsure ? 2 : 0);
     if (!border && !unsure) {
         o.second = fmax(o.second, out_best);
@@ -663,22 +709,6 @@ __global__ __launch_bounds__(256) void spec_settle(reduce_offset_t *__restrict__
     }
 }
 
-// The frames with fb[k] = 1 in increasing order: list[0, n) = those frames, list[n, N) = -1.
-// One wave.
-__global__ __launch_bounds__(64) void spec_list(const int32_t *__restrict__ fb, int32_t N, int32_t *__restrict__ list)
-{
-    const int lane = threadIdx.x;
-    int32_t base = 0;
-    for (int32_t c0 = 0; c0 < N; c0 += 64) {
-        const int32_t k = c0 + lane;
-        const bool f = k < N && fb[k] != 0;
-        const uint64_t m = __ballot(f);
-        if (f) list[base + __popcll(m & ((1ull << lane) - 1ull))] = k;
-        base += __popcll(m);
-    }
-    for (int32_t k = base + lane; k < N; k += 64) list[k] = -1;
-}
-
 // ---- host side ---------------------------------------------------------------------------
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -686,8 +716,8 @@ struct FftLayout {
     int32_t P, N2, log2n2, PS, D, Dg, n_grp, M, n_blk, bpb, n_band, n_kt, F;
     RegPlan refine, full;
     int32_t Ffull;
-    size_t tw, mean_parts, mean, Bt, rowsq_b, A, rowsq_a, Zp, S_fft, cen, map, list, info, fb;
-    size_t part_r, sc_r, part_f, sc_f, total;
+    size_t tw, mean_parts, mean, Bt, rowsq_b, A, rowsq_a, Zp, S_fft, cen, info, fb;
+    size_t part_r, part_f, sc_f, total;
 };
 
 static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
@@ -740,13 +770,10 @@ static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
     L->Zp = take(sizeof(double2) * (size_t)L->PS * L->n_band * L->D * L->F);
     L->S_fft = take(sizeof(double) * (size_t)N * L->D * L->D);
     L->cen = take(sizeof(int32_t) * 2 * (size_t)N);
-    L->map = take(sizeof(int32_t) * (size_t)N);
-    L->list = take(sizeof(int32_t) * (size_t)N);
     L->info = take(sizeof(int32_t) * (size_t)N);
     L->fb = take(sizeof(int32_t) * (size_t)N);
     const RegPlan &pr = L->refine, &pf = L->full;
     L->part_r = take(sizeof(double) * (size_t)N * pr.n_tiles * pr.D * pr.D);
-    L->sc_r = take(sizeof(double) * (size_t)N * pr.D * pr.D);
     L->part_f = take(per_full * (size_t)L->Ffull);
     L->sc_f = take(sizeof(double) * (size_t)L->Ffull * pf.D * pf.D);
     L->total = o;
@@ -828,16 +855,18 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
     double2 *Zp = static_cast<double2 *>(at(L.Zp));
     double *Sf = scores ? scores : static_cast<double *>(at(L.S_fft));
     int32_t *cen = static_cast<int32_t *>(at(L.cen));
-    int32_t *map = static_cast<int32_t *>(at(L.map));
-    int32_t *list = static_cast<int32_t *>(at(L.list));
     int32_t *inf = info ? info : static_cast<int32_t *>(at(L.info));
+    int32_t *fb = static_cast<int32_t *>(at(L.fb));
     const int32_t R = radius, D = L.D;
     const int32_t tx0 = R, ty0 = R, tw_ = W - 2 * R, th = H - 2 * R;
     const int64_t a_batch = (int64_t)L.PS * H;
     ProfScope prof("register_fft", s);
 
-    hipLaunchKernelGGL(fft_twiddles, dim3((unsigned)ceil_div(L.P, 256)), dim3(256), 0, s, tw, L.P);
-    register_mean(ref, W, tx0, ty0, tw_, th, static_cast<double *>(at(L.mean_parts)), mean, s);
+    const int32_t n_parts = (int32_t)ceil_div(th, MEAN_ROWS);
+    double *mean_parts = static_cast<double *>(at(L.mean_parts));
+    hipLaunchKernelGGL(spec_prepare, dim3((unsigned)(n_parts + ceil_div(L.P, MEAN_THREADS))), dim3(MEAN_THREADS), 0, s,
+                       ref, W, tx0, ty0, tw_, th, n_parts, mean_parts, tw, L.P);
+    register_mean_final(mean_parts, n_parts, (double)tw_ * (double)th, mean, s);
     {
         ProfScope p2("fft_rows", s);
         const RowSrc tsrc{ref + (int64_t)ty0 * W + tx0, 0, W, tw_, th, mean};
@@ -884,33 +913,25 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
             });
         }
     }
-    hipLaunchKernelGGL(spec_pick, dim3((unsigned)N), dim3(256), 0, s, Sf, D, R, out, cen);
-    // exact +-1 windows around the spectral maxima, moved while their maximum lies on an
-    // inner border; the decisions; the full direct search for the frames not settled
+    hipLaunchKernelGGL(spec_pick, dim3((unsigned)N), dim3(PICK_THREADS), 0, s, Sf, D, R, cen);
+    // exact +-1 windows around the spectral maxima and the decisions
     {
         ProfScope p2("fft_refine", s);
         double *part_r = static_cast<double *>(at(L.part_r));
-        double *sc_r = static_cast<double *>(at(L.sc_r));
-        register_scores(L.refine, ref, frames, W, H, N, 1, R, cen, nullptr, tx0, ty0, tw_, th, mean, part_r, sc_r,
-                        out, s);
-        for (int32_t mv = 0; mv < FFT_MAX_MOVES; ++mv) {
-            hipLaunchKernelGGL(spec_walk, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, s, out, N, R, cen, map);
-            register_scores(L.refine, ref, frames, W, H, N, 1, R, cen, map, tx0, ty0, tw_, th, mean, part_r, sc_r,
-                            out, s);
-        }
+        const int32_t n_tiles = register_small_scores(L.refine, ref, frames, W, H, N, 1, R, cen, tx0, ty0, tw_, th,
+                                                      mean, part_r, s);
         const double eps = 1.1102230246251565e-16;  // 2^-53
-        const double factor = 4.0 * eps * (10.0 * L.log2n2 + (double)ceil_div(COL_L, L.M) * (124.0 + L.n_blk) + (double)L.P +
-                                            18.0 + 2.0 * EVAL_M);
-        int32_t *fb = static_cast<int32_t *>(at(L.fb));
-        hipLaunchKernelGGL(spec_settle, dim3((unsigned)N), dim3(256), 0, s, out, Sf, D, R, rowsq_a, H, rowsq_b, th,
-                           factor, fb, inf);
-        hipLaunchKernelGGL(spec_list, dim3(1), dim3(64), 0, s, fb, N, list);
+        const double factor = 4.0 * eps * (10.0 * L.log2n2 + (double)ceil_div(COL_L, L.M) * (124.0 + L.n_blk) +
+                                           (double)L.P + 18.0 + 2.0 * EVAL_M);
+        hipLaunchKernelGGL(spec_settle, dim3((unsigned)N), dim3(PICK_THREADS), 0, s, part_r, n_tiles, cen, Sf, D, R,
+                           rowsq_a, H, rowsq_b, th, factor, out, fb, inf);
     }
+    // the full direct search for the frames not settled (nothing, for most calls)
     {
         ProfScope p2("fft_fallback", s);
         for (int32_t r0 = 0; r0 < N; r0 += L.Ffull) {
             const int32_t n = std::min(L.Ffull, N - r0);
-            register_scores(L.full, ref, frames, W, H, n, R, R, nullptr, list + r0, tx0, ty0, tw_, th, mean,
+            register_scores(L.full, ref, frames, W, H, n, R, R, nullptr, fb + r0, tx0, ty0, tw_, th, mean,
                             static_cast<double *>(at(L.part_f)), static_cast<double *>(at(L.sc_f)), out, s);
         }
     }

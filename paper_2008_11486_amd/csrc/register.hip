@@ -127,14 +127,43 @@ static void launch_score(const ScoreArgs &a, const RegPlan &p, hipStream_t s)
                        a);
 }
 
+static void launch_score_small(const ScoreArgs &a, const RegPlan &p, hipStream_t s)
+{
+    ProfScope prof("score_tiles", s);
+    // workgroups for this call's template (at most the plan's, which is sized for the largest)
+    const dim3 grid((unsigned)((int64_t)a.n_tiles * a.N));
+    switch (p.D) {
+    case 1: hipLaunchKernelGGL(score_small<1>, grid, dim3(SMALL_COLS), 0, s, a); break;
+    case 3: hipLaunchKernelGGL(score_small<3>, grid, dim3(SMALL_COLS), 0, s, a); break;
+    default: hipLaunchKernelGGL(score_small<5>, grid, dim3(SMALL_COLS), 0, s, a); break;
+    }
+}
+
+// Template mean from its parts.
+void register_mean_final(const double *mean_parts, int32_t nparts, double count, double *mean, hipStream_t s)
+{
+    hipLaunchKernelGGL(tmpl_mean_final, dim3(1), dim3(MEAN_THREADS), 0, s, mean_parts, nparts, count, mean);
+}
+
 // Template mean of the reference (two launches): parts [ceil(th / MEAN_ROWS)], mean [1].
 void register_mean(const float *ref, int32_t W, int32_t tx0, int32_t ty0, int32_t tw, int32_t th,
                    double *mean_parts, double *mean, hipStream_t s)
 {
     const int32_t nparts = (int32_t)ceil_div(th, MEAN_ROWS);
     hipLaunchKernelGGL(tmpl_sum_rows, dim3(nparts), dim3(MEAN_THREADS), 0, s, ref, W, tx0, ty0, tw, th, mean_parts);
-    hipLaunchKernelGGL(tmpl_mean_final, dim3(1), dim3(MEAN_THREADS), 0, s, mean_parts, nparts,
-                       (double)tw * (double)th, mean);
+    register_mean_final(mean_parts, nparts, (double)tw * (double)th, mean, s);
+}
+
+// Tile partials of small windows (side <= 5) around the frames' centres, without the sums;
+// returns the tiles per frame.  partial holds [N][n_tiles][D*D] doubles.
+int32_t register_small_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
+                              int32_t R, int32_t Rmax, const int32_t *centers, int32_t tx0, int32_t ty0, int32_t tw,
+                              int32_t th, const double *mean, double *partial, hipStream_t s)
+{
+    const ScoreArgs a =
+        make_score_args(p, ref, frames, centers, mean, partial, W, H, N, R, Rmax, tx0, ty0, tw, th, 0x7fffffff);
+    launch_score_small(a, p, s);
+    return a.n_tiles;
 }
 
 // Score tiles, tile sums and argmax for N work slots with a known template mean.
@@ -149,14 +178,7 @@ void register_scores(const RegPlan &p, const float *ref, const float *frames, in
         make_score_args(p, ref, frames, centers, mean, partial, W, H, N, R, Rmax, tx0, ty0, tw, th, 0x7fffffff);
     a.map = map;
     if (p.K == 0) {
-        ProfScope prof("score_tiles", s);
-        // workgroups for this call's template (at most the plan's, which is sized for the largest)
-        const dim3 grid((unsigned)((int64_t)a.n_tiles * N));
-        switch (p.D) {
-        case 1: hipLaunchKernelGGL(score_small<1>, grid, dim3(SMALL_COLS), 0, s, a); break;
-        case 3: hipLaunchKernelGGL(score_small<3>, grid, dim3(SMALL_COLS), 0, s, a); break;
-        default: hipLaunchKernelGGL(score_small<5>, grid, dim3(SMALL_COLS), 0, s, a); break;
-        }
+        launch_score_small(a, p, s);
     } else {
     switch (p.K) {
     case 5: launch_score<5>(a, p, s); break;
