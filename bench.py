@@ -358,6 +358,18 @@ def tuning_hook(store, limit=32):
     return hook
 
 
+def spectra_bytes(specs):
+    """Algorithmic bytes of the row spectra of every stack's searched frames and template:
+    4 B read per pixel, 16 B written per value of the half spectrum."""
+    total = 0
+    for sp in specs:
+        P = max(64, 1 << (sp.W - 1).bit_length())
+        frame = 4 * sp.W * sp.H + 16 * (P // 2 + 1) * sp.H
+        th, tw = sp.H - 2 * sp.radius, sp.W - 2 * sp.radius
+        total += (sp.N - 1) * frame + 4 * tw * th + 16 * (P // 2 + 1) * th
+    return total
+
+
 def search_flops(specs):
     """Algorithmic flops of the full-window search of every non-reference frame: one FMA
     (2 flop) per template pixel (the interior shrunk by the radius) per candidate offset."""
@@ -626,11 +638,11 @@ def sweep(torch, rd, reps=3):
             batch.run()
         torch.cuda.synchronize()
         dt = (time.perf_counter() - t0) / reps
-        ms, n = rd.prof_query("batch_score")
+        ms = rd.prof_query("batch_score")[0] + rd.prof_query("batch_spectral")[0]
         rd.prof_enable(False)
         pix = sum(c * side * side for c in counts)
         res = {"N": side, "n": sum(counts), "stacks": len(counts), "ms_per_call": round(dt * 1e3, 3),
-               "Mpix/s": round(pix / dt / 1e6, 1), "search_share": round(ms / n / 1e3 / dt, 3)}
+               "Mpix/s": round(pix / dt / 1e6, 1), "search_share": round(ms / reps / 1e3 / dt, 3)}
         del batch, stacks
         torch.cuda.empty_cache()
         return res
@@ -982,26 +994,38 @@ def main():
     log(f"timed {args.steps} steps: {ms_per_step:.3f} ms per step")
 
     kern = {name: rd.prof_query(name) for name in ("score_tiles", "calibrate", "shift", "combine", "batch_score",
-                                                   "batch_fused", "batch_comb", "batch_shift")}
+                                                   "batch_fused", "batch_comb", "batch_shift", "batch_spectral",
+                                                   "fft_rows", "spec_corr", "spec_eval", "fft_refine")}
     batched = args.path == "batched"
     rd.prof_enable(False)
 
     score_ms, score_n = kern["batch_score" if batched else "score_tiles"]
-    score_avg_s = score_ms / score_n / 1e3
-    launches_per_step = score_n / args.steps
-    # batched: the flops of the step's searches spread over its search dispatches (one per
-    # group of stacks that share a launch shape); stage-wise: one stack's search per launch
-    flops = search_flops(specs) / launches_per_step if batched else search_flops(specs[:1])
-    achieved = flops / score_avg_s / 1e12
-    kname = "batch_score" if batched else "score_tiles"
-    traffic = recorded_traffic(args.traffic, kname, "many" if args.workload == 2 else None)
-    roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": round(FP64_VALU_PEAK_TFLOPS, 3),
-                "unit": "TFLOP/s", "frac": round(achieved / FP64_VALU_PEAK_TFLOPS, 4), "traffic": traffic,
-                "kernel": kname, "avg_launch_ms": round(score_avg_s * 1e3, 4),
-                "launches_per_step": round(launches_per_step, 3), "flops_per_launch": flops,
-                "search_share_of_step": round(score_ms / args.steps / ms_per_step, 4)}
+    if batched and score_n == 0:
+        # the searches went through row spectra: the position of their largest kernel
+        ms, n = kern["fft_rows"]
+        gbs = spectra_bytes(specs) / (ms / args.steps / 1e3) / 1e9
+        roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "fft_rows",
+                    "avg_launch_ms": round(ms / n, 4), "launches_per_step": round(n / args.steps, 3),
+                    "bytes_per_step": spectra_bytes(specs),
+                    "search_share_of_step": round(kern["batch_spectral"][0] / args.steps / ms_per_step, 4)}
+    else:
+        score_avg_s = score_ms / score_n / 1e3
+        launches_per_step = score_n / args.steps
+        # batched: the flops of the step's searches spread over its search dispatches (one per
+        # group of stacks that share a launch shape); stage-wise: one stack's search per launch
+        flops = search_flops(specs) / launches_per_step if batched else search_flops(specs[:1])
+        achieved = flops / score_avg_s / 1e12
+        kname = "batch_score" if batched else "score_tiles"
+        traffic = recorded_traffic(args.traffic, kname, "many" if args.workload == 2 else None)
+        roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": round(FP64_VALU_PEAK_TFLOPS, 3),
+                    "unit": "TFLOP/s", "frac": round(achieved / FP64_VALU_PEAK_TFLOPS, 4), "traffic": traffic,
+                    "kernel": kname, "avg_launch_ms": round(score_avg_s * 1e3, 4),
+                    "launches_per_step": round(launches_per_step, 3), "flops_per_launch": flops,
+                    "search_share_of_step": round(score_ms / args.steps / ms_per_step, 4)}
     # the other timed phases of a batched step (HIP events, ms per step)
-    phases = {k: round(kern[k][0] / args.steps, 3) for k in ("batch_fused", "batch_comb", "batch_shift")
+    phases = {k: round(kern[k][0] / args.steps, 3) for k in ("batch_fused", "batch_comb", "batch_shift", "batch_spectral",
+                                                             "fft_rows", "spec_corr", "spec_eval", "fft_refine")
               if batched and kern[k][1]}
 
     streaming = {}

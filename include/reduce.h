@@ -106,6 +106,11 @@ int reduce_calibrate(const uint16_t *raw, int64_t raw_row_pitch, int64_t raw_fra
  *   scores  device double [N][2R+1][2R+1] or NULL: S_k at (dy-cy+R, dx-cx+R), -inf
  *           outside the clipped window
  *   ws      device workspace of at least reduce_register_ws(W, H, N, R, Rmax) bytes
+ * A large full-window search (scores, centers and tmpl NULL, R = Rmax, no launch shape
+ * tuned for these sizes) evaluates the score plane from row spectra, as
+ * reduce_register_fft does, when that is faster and ws is 16-byte aligned and holds it; a
+ * workspace that holds the direct sums only is accepted and searched directly.  The
+ * offsets, peak and flags come from direct sums either way (`second` as there).
  * Errors: R < 0, Rmax < 0 or an invalid template -> RANGE; small ws -> WORKSPACE. */
 size_t reduce_register_ws(int32_t W, int32_t H, int32_t N, int32_t radius, int32_t radius_max);
 
@@ -265,8 +270,8 @@ int reduce_combine(const float *aligned, int32_t w, int32_t h, int32_t N, float 
  * A stack with a bias frame calibrates as reduce_calibrate with it; a stack with a
  * bad-pixel map masks its aligned values as reduce_mask_shifted and combines with
  * missing = 1.  A stack with search = REDUCE_SEARCH_SPECTRAL (radius >= 1, W <= 8192)
- * registers as reduce_register_fft of its calibrated frames instead of
- * reduce_register (the same offsets; the choice is the caller's or the tuner's).  The stack
+ * registers as reduce_register_fft of its calibrated frames, whatever its size, instead of
+ * as reduce_register (the same offsets; the choice is the caller's or the tuner's).  The stack
  * descriptors are copied into the workspace at every call (the host image is kept
  * per workspace and rebuilt, after synchronising `stream`, when the descriptors
  * change).  Calls sharing one workspace must not overlap.  Errors: as the stage-wise
@@ -288,7 +293,7 @@ typedef struct {
     int32_t search;         /* REDUCE_SEARCH_DIRECT (0) or REDUCE_SEARCH_SPECTRAL (1) */
     int32_t pad;
 } reduce_stack_t;
-#define REDUCE_SEARCH_DIRECT   0  /* scores by direct sums (reduce_register) */
+#define REDUCE_SEARCH_DIRECT   0  /* as reduce_register of the N - 1 searched frames */
 #define REDUCE_SEARCH_SPECTRAL 1  /* scores from row spectra, offsets from exact sums (reduce_register_fft) */
 
 size_t reduce_stack_batch_ws(const reduce_stack_t *stacks, int32_t n);

@@ -39,6 +39,7 @@
 #include "calibrate_core.h"
 #include "combine_core.h"
 #include "common.h"
+#include "fftreg.h"
 #include "register_core.h"
 #include "register_plan.h"
 #include "shift_core.h"
@@ -509,8 +510,13 @@ static int validate(const reduce_stack_t *stacks, int32_t n)
     return REDUCE_OK;
 }
 
-// The stack registers through row spectra (a stack of one frame has nothing to register).
-static bool spectral(const reduce_stack_t &s) { return s.search == REDUCE_SEARCH_SPECTRAL && s.N > 1; }
+// The stack registers through row spectra (a stack of one frame has nothing to register):
+// asked for, or where reduce_register takes them for its N - 1 searched frames.
+static bool spectral(const reduce_stack_t &s)
+{
+    return s.N > 1 && (s.search == REDUCE_SEARCH_SPECTRAL || (spectra_pay(s.W, s.H, s.N - 1, s.radius) &&
+                                                              spectral_ws(s.W, s.H, s.N - 1, s.radius, SPEC_ROUND_BYTES) != 0));
+}
 
 // Dark subtraction takes 8-pixel groups when rows, pitches and pointers allow it.
 static bool cal_vec_ok(const reduce_stack_t &s)
@@ -551,14 +557,14 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
         off += al(sizeof(double) * (size_t)std::max(ndir, 0) * p.n_tiles * p.D * p.D);
         sl.scores = off;
         off += al(sizeof(double) * (size_t)std::max(ndir, 0) * p.D * p.D);
-        if (spec) L.spec_ws = std::max(L.spec_ws, reduce_register_fft_ws(s.W, s.H, s.N, s.radius));
+        if (spec) L.spec_ws = std::max(L.spec_ws, spectral_ws(s.W, s.H, s.N - 1, s.radius, SPEC_ROUND_BYTES));
         sl.soffs = off;
         off += al(sizeof(float) * 2 * s.N);
         sl.rect = off;
         off += 256;
         sl.count[IT_CAL] = (int32_t)ceil_div(cal_vec_ok(s) ? fp / CAL_VEC : fp, CAL_BLOCK);
-        sl.count[IT_MEANPART] = n_mean_parts;
-        sl.count[IT_MEANFINAL] = 1;
+        sl.count[IT_MEANPART] = ndir > 0 ? n_mean_parts : 0;
+        sl.count[IT_MEANFINAL] = ndir > 0 ? 1 : 0;
         sl.count[IT_SCORE] = p.K != 0 ? ndir * p.wg_per_frame : 0;
         sl.count[IT_SSCORE] = p.K == 0 ? ndir * p.wg_per_frame : 0;
         sl.count[IT_SUM] = ndir * (int32_t)ceil_div((int64_t)p.D * p.D, 64);
@@ -695,7 +701,7 @@ static int build_descriptors(const reduce_stack_t *stacks, int32_t n, void *ws, 
         d.scores = reinterpret_cast<double *>(base + sl.scores);
         d.soffs = reinterpret_cast<float *>(base + sl.soffs);
         d.rect = reinterpret_cast<int32_t *>(base + sl.rect);
-        d.n_mean_parts = sl.count[IT_MEANPART];
+        d.n_mean_parts = (int32_t)ceil_div(st.H - 2 * st.radius, MEAN_ROWS);
         const int32_t R = st.radius;
         const float *ref = d.cal + (int64_t)d.ref * st.W * st.H;
         d.sa = make_score_args(sl.plan, ref, d.cal, nullptr, d.mean, d.partial, st.W, st.H, std::max(st.N - 1, 1), R,
@@ -759,8 +765,9 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
     if (L.count[IT_MEANPART] > 0)
         hipLaunchKernelGGL(batch_meanpart, dim3(L.count[IT_MEANPART]), dim3(MEAN_THREADS), 0, s, a,
                            L.first[IT_MEANPART]);
-    hipLaunchKernelGGL(batch_meanfinal, dim3(L.count[IT_MEANFINAL]), dim3(MEAN_THREADS), 0, s, a,
-                       L.first[IT_MEANFINAL]);
+    if (L.count[IT_MEANFINAL] > 0)
+        hipLaunchKernelGGL(batch_meanfinal, dim3(L.count[IT_MEANFINAL]), dim3(MEAN_THREADS), 0, s, a,
+                           L.first[IT_MEANFINAL]);
     if (L.count[IT_SCORE] > 0) {
         for (const ScoreGroup &g : L.groups) {
             ProfScope prof("batch_score", s);  // one record per dispatch
@@ -783,8 +790,9 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
         if (!spectral(st)) continue;
         ProfScope prof("batch_spectral", s);
         const float *cal = reinterpret_cast<const float *>(base + L.st[i].cal);
-        const int rc = reduce_register_fft(cal + (int64_t)st.ref_index * st.W * st.H, cal, st.W, st.H, st.N,
-                                           st.radius, st.offsets, nullptr, nullptr, base + L.spec, L.spec_ws, s);
+        const int rc = spectral_search(cal + (int64_t)st.ref_index * st.W * st.H, cal, st.W, st.H, st.N - 1,
+                                       st.radius, st.ref_index, st.offsets, nullptr, nullptr, base + L.spec,
+                                       SPEC_ROUND_BYTES, s);
         if (rc != REDUCE_OK) return rc;
     }
     hipLaunchKernelGGL(batch_rect, dim3(L.count[IT_RECT]), dim3(64), 0, s, a, L.first[IT_RECT]);

@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "fftreg.h"
 #include "register_core.h"
 #include "register_plan.h"
 
@@ -34,7 +35,7 @@ namespace rd {
 void register_mean_final(const double *mean_parts, int32_t nparts, double count, double *mean, hipStream_t s);
 int32_t register_small_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
                               int32_t R, int32_t Rmax, const int32_t *centers, int32_t tx0, int32_t ty0, int32_t tw,
-                              int32_t th, const double *mean, double *partial, hipStream_t s);
+                              int32_t th, const double *mean, double *partial, int32_t skip, hipStream_t s);
 void register_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
                      int32_t R, int32_t Rmax, const int32_t *centers, const int32_t *map, int32_t tx0, int32_t ty0,
                      int32_t tw, int32_t th, const double *mean, double *partial, double *sc, reduce_offset_t *out,
@@ -45,7 +46,6 @@ constexpr int32_t FFT_P_MAX = 8192;    // longest rows: P/2 = 4096 complex value
 constexpr int COL_L = 256;             // rows per block of the contraction (transform length along y)
 constexpr int COL_KC = 16;             // spectrum columns per contraction workgroup
 constexpr int COL_LAGS = 144;          // most lags per pass: a block then adds at least 113 template rows
-constexpr size_t SPEC_ROUND_BYTES = size_t(2) << 30;  // spectra and partials of the frames of one round
 constexpr size_t FFT_FALLBACK_BYTES = size_t(256) << 20;
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
@@ -171,7 +171,7 @@ __device__ __forceinline__ void dft16(double2 (&v)[16])
 }
 
 // ---- row spectra -------------------------------------------------------------------------
-// Rows of batch b: row r (r < nrows) holds x(u) = base[b * batch + r * pitch + u] - sub for
+// Rows of batch b: row r (r < nrows) holds x(u) = base[(b + (b >= skip)) * batch + r * pitch + u] - sub for
 // u < ncols, 0 for ncols <= u < P; rows nrows <= r < rows_out are zero.  Output: the
 // half spectrum X(k), k = 0 .. P/2, at spec + b * spec_batch + r * PS, and the sum of
 // squares of each row at rowsq[b * rows_out + r].  A row of P real values is packed as
@@ -194,6 +194,7 @@ struct RowSrc {
     int64_t batch, pitch;
     int32_t ncols, nrows;
     const double *sub;  // device scalar subtracted from every value, or NULL
+    int32_t skip;       // batch b reads from b + 1 on from this one
 };
 
 constexpr int FFT_V = 16;                                   // values per thread
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(FFT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     const bool live = r < rows_out;
     const bool data = r < src.nrows;
     const double sub = src.sub ? *src.sub : 0.0;
-    const float *row = src.base + (int64_t)b * src.batch + (int64_t)(data ? r : 0) * src.pitch;
+    const float *row = src.base + (int64_t)(b + (b >= src.skip)) * src.batch + (int64_t)(data ? r : 0) * src.pitch;
 
     // packed load: value pair n = lt + i tpr, as one 8-byte load where the row allows it
     // (addresses clamped into the row, values past it replaced by zero)
@@ -608,7 +609,7 @@ __global__ __launch_bounds__(PICK_THREADS) void spec_pick(const double *__restri
 // sum_b ||A_b|| ||B_b|| <= c ||a|| ||b||, c = ceil(COL_L / M) the blocks a frame row is in.  A kept frame
 // gets second = the larger of its window's runner-up and that spectral score, the margin
 // and NEAR_TIE from it, and loses CLIPPED (its window is a step of the full search).
-// fb[k] = k for the frames that take the full search, else -1 (the slots of that search);
+// fb[k] = the frame of slot k if it takes the full search, else -1 (that search's slots);
 // info[k] says why (1: inner border, 2: not clear of the bound).
 // The exact scores of the window come as the tile partials of score_small<3>.
 __global__ __launch_bounds__(PICK_THREADS) void spec_settle(const double *__restrict__ partial, int32_t n_tiles,
@@ -616,7 +617,8 @@ __global__ __launch_bounds__(PICK_THREADS) void spec_settle(const double *__rest
                                                             const double *__restrict__ S, int32_t D, int32_t R,
                                                             const double *__restrict__ rowsq_a, int32_t rows_a,
                                                             const double *__restrict__ rowsq_b, int32_t rows_b,
-                                                            double factor, reduce_offset_t *__restrict__ offs,
+                                                            double factor, int32_t skip,
+                                                            reduce_offset_t *__restrict__ offs,
                                                             int32_t *__restrict__ fb, int32_t *__restrict__ info)
 {
     constexpr int NW = PICK_THREADS / 64;
@@ -696,8 +698,9 @@ __global__ __launch_bounds__(PICK_THREADS) void spec_settle(const double *__rest
     const bool border = ((o.flags & REDUCE_EDGE_X) && o.dx > -R && o.dx < R) ||
                         ((o.flags & REDUCE_EDGE_Y) && o.dy > -R && o.dy < R);
     const bool unsure = !(o.peak > out_best + bound);
-    fb[k] = border || unsure ? k : -1;
-    if (info) info[k] = (border ? 1 : 0) | (unsure ? 2 : 0);
+    const int32_t kf = k + (k >= skip ? 1 : 0);  // the slot's frame
+    fb[k] = border || unsure ? kf : -1;
+    info[kf] = (border ? 1 : 0) | (unsure ? 2 : 0);
     if (!border && !unsure) {
         o.second = fmax(o.second, out_best);
         if (o.second == -INFINITY) o.margin = INFINITY;
@@ -705,7 +708,7 @@ __global__ __launch_bounds__(PICK_THREADS) void spec_settle(const double *__rest
         else o.margin = (o.peak - o.second) / fabs(o.peak);
         o.flags &= ~(REDUCE_CLIPPED | REDUCE_NEAR_TIE);
         if (o.margin < REDUCE_NEAR_TIE_MARGIN) o.flags |= REDUCE_NEAR_TIE;
-        offs[k] = o;
+        offs[kf] = o;
     }
 }
 
@@ -720,7 +723,7 @@ struct FftLayout {
     size_t part_r, part_f, sc_f, total;
 };
 
-static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
+static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, size_t round_bytes, FftLayout *L)
 {
     const int32_t tw = W - 2 * R, th = H - 2 * R;
     if (tw < 1 || th < 1) return false;
@@ -747,7 +750,7 @@ static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
     L->n_band = (int32_t)ceil_div(L->n_blk, L->bpb);
     // frames per round of spectra, the rounds of equal size
     const size_t per_frame = sizeof(double2) * (size_t)L->PS * ((size_t)H + (size_t)L->n_band * L->D);
-    L->F = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)N, SPEC_ROUND_BYTES / per_frame));
+    L->F = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)N, round_bytes / per_frame));
     L->F = (int32_t)ceil_div(N, ceil_div(N, L->F));
     L->refine = reg_plan(W, H, 1, R);
     L->full = reg_plan(W, H, R, R);
@@ -770,7 +773,7 @@ static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, FftLayout *L)
     L->Zp = take(sizeof(double2) * (size_t)L->PS * L->n_band * L->D * L->F);
     L->S_fft = take(sizeof(double) * (size_t)N * L->D * L->D);
     L->cen = take(sizeof(int32_t) * 2 * (size_t)N);
-    L->info = take(sizeof(int32_t) * (size_t)N);
+    L->info = take(sizeof(int32_t) * ((size_t)N + 1));  // by frame, the skipped one among them
     L->fb = take(sizeof(int32_t) * (size_t)N);
     const RegPlan &pr = L->refine, &pf = L->full;
     L->part_r = take(sizeof(double) * (size_t)N * pr.n_tiles * pr.D * pr.D);
@@ -819,32 +822,44 @@ static void launch_fft_rows(const FftLayout &L, const RowSrc &src, int32_t rows_
     });
 }
 
-}  // namespace rd
-
-using namespace rd;
-
-extern "C" size_t reduce_register_fft_ws(int32_t W, int32_t H, int32_t N, int32_t radius)
+bool spectra_pay(int32_t W, int32_t H, int32_t N, int32_t R)
 {
-    if (W < 1 || H < 1 || N < 1 || N > 65535 || radius < 1 || W - 2 * radius < 1 || H - 2 * radius < 1 ||
-        W > FFT_P_MAX || 2 * radius + 1 > 1024)
-        return 0;
-    FftLayout L;
-    return fft_layout(W, H, N, radius, &L) ? L.total : 0;
+    if (R < 1 || N < 1 || N > 65535 || W > FFT_P_MAX || 2 * R + 1 > 1024 || W - 2 * R < 1 || H - 2 * R < 1) return false;
+    // a launch shape tuned for these sizes is what later calls of them use
+    RegShape tuned;
+    if (tuned_reg_shape(W, H, R, R, &tuned)) return false;
+    // Microseconds of both, from measured calls.  Direct sums: 23 - 40 TFLOP/s (512x512 x 16 at
+    // R = 17 347 us, 1024x1024 x 16 1182, 2048x2048 x 16 at R = 33 13264; windows of side 7 and
+    // less half of that), so the estimate is a low one.  Spectra: 100 us of dependent small
+    // launches and 6.5 us per million row values of the padded frames and the template (the
+    // same calls: 130, 206, 599), of which the contraction's part grows with its passes and
+    // with the rows its blocks read twice.  Near the line the two are within 30% of each
+    // other: 700x650 x 4 at R = 17 170 and 114, 512x512 x 4 at R = 17 123 and 105.
+    const double D = 2.0 * R + 1.0, T = (double)(W - 2 * R) * (H - 2 * R);
+    const double direct = 2.0 * N * T * D * D / 40e6;
+    int32_t P = 64;
+    while (P < W) P <<= 1;
+    const int32_t passes = (int32_t)ceil_div(2 * R + 1, COL_LAGS);
+    const double reread = (double)COL_L / (COL_L + 1 - (int32_t)ceil_div(2 * R + 1, passes));
+    const double spectral = 100.0 + (4.0 + 2.2 * passes * reread) * 1e-6 * (N + 1.0) * P * H;
+    return direct > 1.25 * spectral;
 }
 
-extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
-                                   int32_t radius, reduce_offset_t *out, double *scores, int32_t *info, void *ws,
-                                   size_t ws_bytes, void *stream)
+size_t spectral_ws(int32_t W, int32_t H, int32_t N, int32_t R, size_t round_bytes)
 {
-    if (!ref || !frames || !out) return fail(REDUCE_ERR_NULL, "reduce_register_fft: NULL buffer");
-    const int c = fft_check(W, H, N, radius, "reduce_register_fft");
-    if (c != REDUCE_OK) return c;
+    if (W < 1 || H < 1 || N < 1 || N > 65535 || R < 1 || W - 2 * R < 1 || H - 2 * R < 1 || W > FFT_P_MAX ||
+        2 * R + 1 > 1024)
+        return 0;
     FftLayout L;
-    if (!fft_layout(W, H, N, radius, &L))
-        return fail(REDUCE_ERR_UNSUPPORTED, "reduce_register_fft: no launch shape for these sizes");
-    if (!ws || ws_bytes < L.total)
-        return fail(REDUCE_ERR_WORKSPACE, "reduce_register_fft: workspace needs " + std::to_string(L.total) + " bytes");
-    hipStream_t s = as_stream(stream);
+    return fft_layout(W, H, N, R, round_bytes, &L) ? L.total : 0;
+}
+
+int spectral_search(const float *ref, const float *frames, int32_t W, int32_t H, int32_t N, int32_t R, int32_t skip,
+                    reduce_offset_t *out, double *scores, int32_t *info, void *ws, size_t round_bytes, hipStream_t s)
+{
+    FftLayout L;
+    if (!fft_layout(W, H, N, R, round_bytes, &L))
+        return fail(REDUCE_ERR_UNSUPPORTED, "search through row spectra: no launch shape for these sizes");
     unsigned char *b = static_cast<unsigned char *>(ws);
     auto at = [&](size_t off) { return static_cast<void *>(b + off); };
     double2 *tw = static_cast<double2 *>(at(L.tw));
@@ -857,7 +872,7 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
     int32_t *cen = static_cast<int32_t *>(at(L.cen));
     int32_t *inf = info ? info : static_cast<int32_t *>(at(L.info));
     int32_t *fb = static_cast<int32_t *>(at(L.fb));
-    const int32_t R = radius, D = L.D;
+    const int32_t D = L.D;
     const int32_t tx0 = R, ty0 = R, tw_ = W - 2 * R, th = H - 2 * R;
     const int64_t a_batch = (int64_t)L.PS * H;
     ProfScope prof("register_fft", s);
@@ -869,7 +884,7 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
     register_mean_final(mean_parts, n_parts, (double)tw_ * (double)th, mean, s);
     {
         ProfScope p2("fft_rows", s);
-        const RowSrc tsrc{ref + (int64_t)ty0 * W + tx0, 0, W, tw_, th, mean};
+        const RowSrc tsrc{ref + (int64_t)ty0 * W + tx0, 0, W, tw_, th, mean, 0x7fffffff};
         launch_fft_rows(L, tsrc, th, 1, tw, As, 0, rowsq_b, s);
     }
     ColArgs ca;
@@ -896,7 +911,8 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
         const int32_t nf = std::min(L.F, N - f0);
         {
             ProfScope p2("fft_rows", s);
-            const RowSrc fsrc{frames + (int64_t)f0 * W * H, (int64_t)W * H, W, W, H, nullptr};
+            const RowSrc fsrc{frames + (int64_t)(f0 + (f0 > skip)) * W * H, (int64_t)W * H, W, W, H, nullptr,
+                              f0 > skip ? 0x7fffffff : skip - f0};
             launch_fft_rows(L, fsrc, H, nf, tw, As, a_batch, rowsq_a + (int64_t)f0 * H, s);
         }
         {
@@ -919,12 +935,12 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
         ProfScope p2("fft_refine", s);
         double *part_r = static_cast<double *>(at(L.part_r));
         const int32_t n_tiles = register_small_scores(L.refine, ref, frames, W, H, N, 1, R, cen, tx0, ty0, tw_, th,
-                                                      mean, part_r, s);
+                                                      mean, part_r, skip, s);
         const double eps = 1.1102230246251565e-16;  // 2^-53
         const double factor = 4.0 * eps * (10.0 * L.log2n2 + (double)ceil_div(COL_L, L.M) * (124.0 + L.n_blk) +
                                            (double)L.P + 18.0 + 2.0 * EVAL_M);
         hipLaunchKernelGGL(spec_settle, dim3((unsigned)N), dim3(PICK_THREADS), 0, s, part_r, n_tiles, cen, Sf, D, R,
-                           rowsq_a, H, rowsq_b, th, factor, out, fb, inf);
+                           rowsq_a, H, rowsq_b, th, factor, skip, out, fb, inf);
     }
     // the full direct search for the frames not settled (nothing, for most calls)
     {
@@ -935,5 +951,29 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
                             static_cast<double *>(at(L.part_f)), static_cast<double *>(at(L.sc_f)), out, s);
         }
     }
-    return check_launch("reduce_register_fft");
+    return check_launch("search through row spectra");
+}
+
+}  // namespace rd
+
+using namespace rd;
+
+extern "C" size_t reduce_register_fft_ws(int32_t W, int32_t H, int32_t N, int32_t radius)
+{
+    return spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES);
+}
+
+extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
+                                   int32_t radius, reduce_offset_t *out, double *scores, int32_t *info, void *ws,
+                                   size_t ws_bytes, void *stream)
+{
+    if (!ref || !frames || !out) return fail(REDUCE_ERR_NULL, "reduce_register_fft: NULL buffer");
+    const int c = fft_check(W, H, N, radius, "reduce_register_fft");
+    if (c != REDUCE_OK) return c;
+    const size_t need = spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES);
+    if (need == 0) return fail(REDUCE_ERR_UNSUPPORTED, "reduce_register_fft: no launch shape for these sizes");
+    if (!ws || ws_bytes < need)
+        return fail(REDUCE_ERR_WORKSPACE, "reduce_register_fft: workspace needs " + std::to_string(need) + " bytes");
+    return spectral_search(ref, frames, W, H, N, radius, 0x7fffffff, out, scores, info, ws, SPEC_ROUND_BYTES,
+                           as_stream(stream));
 }

@@ -3,11 +3,13 @@
 // the kernels that wrap it and the host side of reduce_register.
 //
 // Roofline: VALU (FP64 FMA).  Algorithmic work per frame: |T| * (2R+1)^2 FMA.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <string>
 
 #include "common.h"
+#include "fftreg.h"
 #include "register_core.h"
 #include "register_plan.h"
 
@@ -155,13 +157,13 @@ void register_mean(const float *ref, int32_t W, int32_t tx0, int32_t ty0, int32_
 }
 
 // Tile partials of small windows (side <= 5) around the frames' centres, without the sums;
-// returns the tiles per frame.  partial holds [N][n_tiles][D*D] doubles.
+// returns the tiles per frame.  Slot k is frame k + (k >= skip), centers are by slot; partial holds [N][n_tiles][D*D] doubles.
 int32_t register_small_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
                               int32_t R, int32_t Rmax, const int32_t *centers, int32_t tx0, int32_t ty0, int32_t tw,
-                              int32_t th, const double *mean, double *partial, hipStream_t s)
+                              int32_t th, const double *mean, double *partial, int32_t skip, hipStream_t s)
 {
     const ScoreArgs a =
-        make_score_args(p, ref, frames, centers, mean, partial, W, H, N, R, Rmax, tx0, ty0, tw, th, 0x7fffffff);
+        make_score_args(p, ref, frames, centers, mean, partial, W, H, N, R, Rmax, tx0, ty0, tw, th, skip);
     launch_score_small(a, p, s);
     return a.n_tiles;
 }
@@ -222,7 +224,10 @@ extern "C" size_t reduce_register_ws(int32_t W, int32_t H, int32_t N, int32_t ra
     if (W - 2 * radius_max < 1 || H - 2 * radius_max < 1) return 0;
     const RegPlan p = reg_plan(W, H, radius, radius_max);
     if (p.D == 0) return 0;
-    return register_ws_bytes(p, N);
+    size_t need = register_ws_bytes(p, N);
+    if (radius == radius_max && spectra_pay(W, H, N, radius))
+        need = std::max(need, spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES_PLAIN));
+    return need;
 }
 
 // Argument checks shared by the search entry points; fills the template rectangle and the plan.
@@ -262,6 +267,16 @@ extern "C" int reduce_register(const float *ref, const float *frames, int32_t W,
     const size_t need = register_ws_bytes(p, N);
     if (!ws || ws_bytes < need)
         return fail(REDUCE_ERR_WORKSPACE, "reduce_register: workspace needs " + std::to_string(need) + " bytes");
+    // The full-window search of large problems goes through row spectra (the rule and its
+    // figures at spectra_pay): the same offsets, from exact sums.  Score planes, centres and
+    // other templates are summed directly, and so is a call whose workspace holds the
+    // direct search only.
+    if (!scores && !centers && !tmpl && radius == radius_max && spectra_pay(W, H, N, radius)) {
+        const size_t spec = spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES_PLAIN);
+        if (spec != 0 && ws_bytes >= spec && (reinterpret_cast<uintptr_t>(ws) & 15u) == 0)
+            return spectral_search(ref, frames, W, H, N, radius, 0x7fffffff, out, nullptr, nullptr, ws,
+                                   SPEC_ROUND_BYTES_PLAIN, as_stream(stream));
+    }
     return register_launch(ref, frames, W, H, N, radius, radius_max, centers, t[0], t[1], t[2], t[3], out, scores,
                            ws, p, as_stream(stream));
 }

@@ -224,15 +224,18 @@ extern "C" int reduce_tune_search(const float *ref, const float *frames, int32_t
         return fail(REDUCE_ERR_RANGE, "reduce_tune_search: no template for these sizes");
     if (reps < 1) reps = 1;
     hipStream_t s = as_stream(stream);
-    const size_t need_d = reduce_register_ws(W, H, N, radius, radius);
+    const RegPlan p = reg_plan(W, H, radius, radius);
+    const size_t need_d = p.D == 0 ? 0 : register_ws_bytes(p, N);
     const size_t need_s = reduce_register_fft_ws(W, H, N, radius);
     if (need_d == 0 || ws_bytes < need_d)
         return fail(REDUCE_ERR_WORKSPACE, "reduce_tune_search: workspace needs " + std::to_string(need_d) + " bytes");
+    if (N > 65535 || radius > 1024)
+        return fail(REDUCE_ERR_UNSUPPORTED, "reduce_tune_search: N above 65535 or radius above 1024");
     double td = 0.0, ts = 1e30;
     int rc = time_ms(s, reps,
                      [&]() {
-                         return reduce_register(ref, frames, W, H, N, radius, radius, nullptr, nullptr, out, nullptr,
-                                                ws, ws_bytes, s);
+                         return register_launch(ref, frames, W, H, N, radius, radius, nullptr, radius, radius,
+                                                W - 2 * radius, H - 2 * radius, out, nullptr, ws, p, s);
                      },
                      &td);
     if (rc != REDUCE_OK) return rc;
