@@ -237,9 +237,8 @@ int reduce_shift_spline(const float *in, float *out, int32_t W, int32_t H, int32
  *   aligned  device float [N][h][w];  out device float [h][w]
  *   keep     device uint8 [N][h][w] (1 = kept) or NULL
  *   n_rej    device int64 [1], set to the number of dropped values, or NULL
- * Stacks of up to 48 frames hold a pixel's values in registers (or, with the tuned
- * lanes per column, in an LDS tile); 49 - 128 frames (the paper's co-adding sets
- * reach 97, Section 3.1.2) in the thread's own slice of LDS.
+ * A pixel's values are held in registers (or, up to 48 frames and with the tuned lanes
+ * per column, in an LDS tile); the paper's co-adding sets reach 97 frames (Section 3.1.2).
  * missing != 0: NaN values (bad pixels, see reduce_mask_shifted) are missing: never
  * kept (keep 0), not counted in n_rej, and the clip runs over the pixel's other
  * values; a pixel without any gives NaN.  missing == 0: a NaN poisons its pixel.

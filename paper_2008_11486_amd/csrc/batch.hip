@@ -392,9 +392,9 @@ __global__ __launch_bounds__(COMB_TILE) void batch_fused(BatchArgs a, int32_t fi
     float x[MAXV];
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) x[i] = i < s.N ? tile[i * FUSE_PX + t] : 0.0f;
-    KeptBits<MAXV> kept;
+    ClipState st;
     unsigned dropped = 0;
-    const float res = clip_registers<MAXV>(x, s.N, (double)s.ksigma, s.max_iters, kept, dropped);
+    const float res = clip_registers<MAXV>(x, s.N, (double)s.ksigma, s.max_iters, st, dropped);
     const int64_t p = pb + t;
     if (p < plane) s.out[p] = res;
     else dropped = 0;
@@ -422,24 +422,21 @@ __global__ __launch_bounds__(256) void batch_mask(BatchArgs a, int32_t first, in
         if (reads_bad_pixel(s.mask, s.W, s.H, ss, s.integer_mode != 0, x0 + u, y0 + v)) row[u] = __builtin_nanf("");
 }
 
-// Stacks of 49 - 128 frames (MISS: stacks with a bad-pixel map, any depth): block it.a
-// of 64 pixel columns, values in LDS [N][64] (the launch sizes the tile for the deepest
-// stack of the phase).
-template <bool MISS>
-__global__ __launch_bounds__(COMB_DEEP_PX) __attribute__((amdgpu_waves_per_eu(3))) void batch_comb_deep(BatchArgs a, int32_t first)
+// Stacks of 49 - 128 frames (MISS: with a bad-pixel map): the block's columns with all their
+// values in registers (see combine_deep); MAXV covers the deepest stack of the phase.
+template <int MAXV, bool MISS>
+__global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(3, 3))) void batch_comb_deep(BatchArgs a, int32_t first)
 {
-    extern __shared__ float tile[];
     const Item it = a.items[first + blockIdx.x];
     const StackDev &s = a.stacks[it.stack];
     const int64_t plane = (int64_t)s.rect[2] * s.rect[3];
-    if (it.a >= ceil_div(plane, (int64_t)COMB_DEEP_PX)) return;  // uniform over the workgroup
-    unsigned dropped = combine_deep_block<MISS>(s.al, plane, al_plane(s.rect[2], s.rect[3]), s.N, (double)s.ksigma,
-                                                s.max_iters, s.out, nullptr, it.a, tile);
+    if (it.a >= ceil_div(plane, (int64_t)COMB_TILE)) return;  // uniform over the workgroup
+    const unsigned dropped = combine_cols_block<MAXV, 1, MISS>(s.al, plane, al_plane(s.rect[2], s.rect[3]), s.N,
+                                                               (double)s.ksigma, s.max_iters, s.out, nullptr, it.a);
     if (s.n_rej) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) dropped += __shfl_xor(dropped, off, 64);
-        if (threadIdx.x == 0 && dropped)
-            atomicAdd(reinterpret_cast<unsigned long long *>(s.n_rej), (unsigned long long)dropped);
+        const unsigned total = block_sum_u32(dropped);
+        if (threadIdx.x == 0 && total)
+            atomicAdd(reinterpret_cast<unsigned long long *>(s.n_rej), (unsigned long long)total);
     }
 }
 
@@ -590,7 +587,7 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
             sl.count[IT_FUSE32] = s.N > 16 && s.N <= 32 ? fb : 0;
             sl.count[IT_FUSE48] = s.N > 32 ? fb : 0;
         }
-        const int32_t deep_blocks = s.N > 48 ? (int32_t)ceil_div(fp, (int64_t)COMB_DEEP_PX) : 0;
+        const int32_t deep_blocks = s.N > 48 ? (int32_t)ceil_div(fp, (int64_t)COMB_TILE) : 0;
         sl.count[miss ? IT_COMB16M : IT_COMB16] = fuse ? 0 : c16;
         sl.count[miss ? IT_COMB32M : IT_COMB32] = fuse ? 0 : c32;
         sl.count[miss ? IT_COMB48M : IT_COMB48] = fuse ? 0 : c48;
@@ -825,11 +822,15 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
             hipLaunchKernelGGL((batch_comb<48, 1, true>), dim3(L.count[IT_COMB48M]), dim3(COMB_TILE), 0, s, a,
                                L.first[IT_COMB48M]);
         if (L.count[IT_COMBDEEP] > 0)
-            hipLaunchKernelGGL(batch_comb_deep<false>, dim3(L.count[IT_COMBDEEP]), dim3(COMB_DEEP_PX),
-                               sizeof(float) * (L.deep_n - COMB_DEEP_REG) * COMB_DEEP_PX, s, a, L.first[IT_COMBDEEP]);
+            deep_dispatch(L.deep_n, [&](auto Vc) {
+                hipLaunchKernelGGL((batch_comb_deep<decltype(Vc)::value, false>), dim3(L.count[IT_COMBDEEP]),
+                                   dim3(COMB_TILE), 0, s, a, L.first[IT_COMBDEEP]);
+            });
         if (L.count[IT_COMBMISS] > 0)
-            hipLaunchKernelGGL(batch_comb_deep<true>, dim3(L.count[IT_COMBMISS]), dim3(COMB_DEEP_PX),
-                               sizeof(float) * (L.miss_n - COMB_DEEP_REG) * COMB_DEEP_PX, s, a, L.first[IT_COMBMISS]);
+            deep_dispatch(L.miss_n, [&](auto Vc) {
+                hipLaunchKernelGGL((batch_comb_deep<decltype(Vc)::value, true>), dim3(L.count[IT_COMBMISS]),
+                                   dim3(COMB_TILE), 0, s, a, L.first[IT_COMBMISS]);
+            });
     }
     if (L.count[IT_FUSE16] + L.count[IT_FUSE32] + L.count[IT_FUSE48] > 0) {
         ProfScope prof("batch_fused", s);

@@ -49,20 +49,21 @@ __global__ __launch_bounds__(COMB_TILE) void combine_cols(
     }
 }
 
-// Stacks of 49 - 128 frames, and stacks with missing values: 64 pixel columns per
-// workgroup, values in LDS [N][64].
-template <bool MISS>
-__global__ __launch_bounds__(COMB_DEEP_PX) __attribute__((amdgpu_waves_per_eu(3))) void combine_deep(
+// Stacks of 49 - 128 frames: the same with up to 128 values of a column in registers, three
+// waves per SIMD.  Bound by HBM and FP64 issue alike: 97 frames of 2040x2040 are 1.63 GB.
+// With the values past 32 in LDS, flags in 64-bit words and every column clipped in place the
+// kernel took 0.91 ms, bound by the passes over all columns of a wave for the quarter of them
+// that drop a value; with the interval tests and the queue 0.56 (0.33 is the copy rate).
+template <int MAXV, bool MISS>
+__global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(3, 3))) void combine_deep(
     const float *__restrict__ aligned, int64_t plane, int32_t N, double ksigma, int32_t max_iters,
     float *__restrict__ out, uint8_t *__restrict__ keep, unsigned long long *__restrict__ n_rej)
 {
-    extern __shared__ float tile[];
-    unsigned dropped = combine_deep_block<MISS>(aligned, plane, plane, N, ksigma, max_iters, out, keep,
-                                                (int64_t)blockIdx.x, tile);
+    const unsigned dropped =
+        combine_cols_block<MAXV, 1, MISS>(aligned, plane, plane, N, ksigma, max_iters, out, keep, (int64_t)blockIdx.x);
     if (n_rej) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) dropped += __shfl_xor(dropped, off, 64);
-        if (threadIdx.x == 0 && dropped) atomicAdd(n_rej, (unsigned long long)dropped);
+        const unsigned total = block_sum_u32(dropped);
+        if (threadIdx.x == 0 && total) atomicAdd(n_rej, (unsigned long long)total);
     }
 }
 
@@ -79,21 +80,8 @@ static int combine_px()
     return 4;
 }
 
-static void launch_deep(bool missing, const float *aligned, int64_t plane, int32_t N, double ksigma,
-                        int32_t max_iters, float *out, uint8_t *keep, unsigned long long *n_rej, hipStream_t s)
-{
-    const dim3 grid((unsigned)ceil_div(plane, (int64_t)COMB_DEEP_PX));
-    const size_t lds = sizeof(float) * (N - COMB_DEEP_REG) * COMB_DEEP_PX;
-    if (missing)
-        hipLaunchKernelGGL(combine_deep<true>, grid, dim3(COMB_DEEP_PX), lds, s, aligned, plane, N, ksigma, max_iters,
-                           out, keep, n_rej);
-    else
-        hipLaunchKernelGGL(combine_deep<false>, grid, dim3(COMB_DEEP_PX), lds, s, aligned, plane, N, ksigma,
-                           max_iters, out, keep, n_rej);
-}
-
 // One lane per column (missing = 1 takes only this path): registers up to 48 frames,
-// the LDS-column kernel past that.
+// up to 128 of them past that.
 template <bool MISS>
 static void dispatch_cols(const float *aligned, int64_t plane, int32_t N, double ksigma, int32_t max_iters,
                           float *out, uint8_t *keep, unsigned long long *n_rej, hipStream_t s)
@@ -120,7 +108,10 @@ static void dispatch_cols(const float *aligned, int64_t plane, int32_t N, double
     } else if (N <= 48) {
         launch_cols(std::integral_constant<int, 48>{}, std::integral_constant<int, 1>{});
     } else {
-        launch_deep(MISS, aligned, plane, N, ksigma, max_iters, out, keep, n_rej, s);
+        deep_dispatch(N, [&](auto Vc) {
+            hipLaunchKernelGGL((combine_deep<decltype(Vc)::value, MISS>), dim3((unsigned)ceil_div(plane, COMB_TILE)),
+                               dim3(COMB_TILE), 0, s, aligned, plane, N, ksigma, max_iters, out, keep, n_rej);
+        });
     }
 }
 

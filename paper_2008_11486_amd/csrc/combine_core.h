@@ -160,164 +160,227 @@ __device__ __forceinline__ unsigned block_sum_u32(unsigned v)
     return t;
 }
 
-// Kept flags of up to MAXV values, one bit each (i is a compile-time index after
-// unrolling, so the word and the bit are fixed).
-template <int MAXV>
-struct KeptBits {
-    static constexpr int W = (MAXV + 63) / 64;
-    uint64_t w[W];
-    __device__ __forceinline__ bool get(int i) const { return ((w[i >> 6] >> (i & 63)) & 1ull) != 0; }
-    __device__ __forceinline__ void clear(int i) { w[i >> 6] &= ~(1ull << (i & 63)); }
-    __device__ __forceinline__ void first(int32_t N)  // values 0 .. N-1 kept
-    {
+// ---- one thread per pixel column ---------------------------------------------------------
+// f(i, exists) for i < N in order, i a constant after unrolling, eight at a time behind one
+// uniform test; in the group that N ends in, f also sees values past it (exists = false),
+// which hold the last frame's and are to be selected away, not branched around: branches per
+// value made the compiler keep the column in scratch.
+template <int MAXV, typename F>
+__device__ __forceinline__ void each_value(int32_t N, F f)
+{
+    static_assert(MAXV % 8 == 0, "whole groups of eight");
+    asm volatile("" : "+s"(N));  // each pass makes its own tests: kept across passes they spill
 #pragma unroll
-        for (int j = 0; j < W; ++j) {
-            const int32_t r = N - 64 * j;
-            w[j] = r >= 64 ? ~0ull : r <= 0 ? 0ull : ((1ull << r) - 1ull);
+    for (int c = 0; c < MAXV; c += 8) {
+        if (c + 8 <= N) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f(c + j, true);
+        } else if (c < N) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f(c + j, c + j < N);
         }
+    }
+}
+
+// The same for loops that fill a column's values: f(i) also past N up to the next eight.
+template <int MAXV, typename F>
+__device__ __forceinline__ void each_group(int32_t N, F f)
+{
+    asm volatile("" : "+s"(N));
+#pragma unroll
+    for (int c = 0; c < MAXV; c += 8)
+        if (c < N) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f(c + j);
+        }
+}
+
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+
+// The planes of the frames in turn: a uniform address, moved on by one plane per step and
+// opaque to the compiler, which would otherwise form all N plane addresses before the first
+// load and hold them for the later loops (hundreds of spilled scalar registers).
+template <typename T>
+struct PlaneWalk {
+    typedef __attribute__((address_space(1))) T G;  // global: not a flat access
+    G *at;
+    int64_t pstride;
+    int32_t left;  // steps until the last plane, where the walk stays
+    __device__ __forceinline__ PlaneWalk(T *first, int64_t stride, int32_t N) : pstride(stride), left(N - 1)
+    {
+        const uint64_t a = reinterpret_cast<uint64_t>(first);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+        at = (G *)(((uint64_t)hi << 32) | lo);
+    }
+    __device__ __forceinline__ G *next(int i)
+    {
+        G *r = at;
+        at += i < left ? pstride : 0;
+        asm volatile("" : "+s"(at));
+        return r;
     }
 };
 
+// The kept values of a column are those inside [lo, hi]: |x - m| > threshold is monotonic in
+// x on either side of m, also as rounded, so an iteration keeps an interval of floats, and
+// what several iterations keep (nothing dropped comes back) is the interval they share.  The
+// tests of a pass are then two float comparisons where a flag per value took a 64-bit mask
+// and selects.  A missing value (NaN) is in no interval.
+struct ClipState {
+    float lo, hi;  // kept: lo <= x <= hi
+    double s;      // sum of the kept values in frame order
+    int n;         // their number
+};
 
-// One thread per pixel column, the column's values read through x(i) (registers, or
-// the thread's own slice of LDS).  The arithmetic is that of clip_column with one
-// lane: sums in frame order in double, m = s / n, q = sum of (x - m)^2, threshold
-// ksigma * sqrt(q / n), drop |x - m| > threshold.  Two shortcuts leave every result
-// unchanged: the largest |x - m| of the q pass decides whether the drop pass is
-// needed at all, and when an iteration drops nothing its own mean is the final mean.
-// With FENCE a compiler barrier at each pass keeps values read from LDS from being
-// held in registers across passes.
-template <bool FENCE>
-__device__ __forceinline__ void clip_fence()
+// Sum and number of the kept values.  ALL: every value is kept (before the first drop,
+// without missing values).  Not-kept values add +0 to a sum that starts at +0: nothing.
+template <int MAXV, bool ALL, typename X>
+__device__ __forceinline__ void clip_sum(X x, int32_t N, ClipState &c)
 {
-    if (FENCE) asm volatile("" ::: "memory");
+    c.s = 0.0;
+    c.n = ALL ? N : 0;
+    each_value<MAXV>(N, [&](int i, bool exists) {
+        const float v = x(i);
+        const bool k = exists && (ALL || (v >= c.lo && v <= c.hi));
+        c.s = __dadd_rn(c.s, (double)(k ? v : 0.0f));
+        if (!ALL) c.n += k ? 1 : 0;
+    });
 }
 
-// With ALL (every value kept: the first iteration without missing values) the passes
-// carry no per-value selects: the values past N are zero (the loads fill them so), which
-// adds exactly nothing to a sum that starts at +0 (such a sum is never -0), and their
-// deviations are multiplied by the uniform weight 0 (1 for i < N, an exact product) so
-// they add exactly nothing to q and cannot raise the largest deviation.
-template <int MAXV, bool ALL, bool FENCE, typename X>
-__device__ __forceinline__ void clip_pass(X x, const KeptBits<MAXV> &kept, int32_t N, int n, double &s, double &m,
-                                          double &q, double &dmax)
+// Squared deviations of the kept values from m, in frame order, and the largest deviation.  A
+// not-kept value's deviation is replaced by 0, which adds exactly nothing.
+template <int MAXV, bool ALL, typename X>
+__device__ __forceinline__ void clip_squares(X x, int32_t N, const ClipState &c, double m, double &q, double &dmax)
 {
-    clip_fence<FENCE>();
-    s = 0.0;
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i)
-        if (ALL || kept.get(i)) s = __dadd_rn(s, (double)x(i));
-    m = s / (double)n;
     q = 0.0;
     dmax = 0.0;
-    clip_fence<FENCE>();
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i)
-        if (ALL || kept.get(i)) {
-            double d = __dsub_rn((double)x(i), m);
-            if (ALL) d = __dmul_rn(d, (double)min(max(N - i, 0), 1));
-            q = __dadd_rn(q, __dmul_rn(d, d));
-            dmax = fmax(dmax, fabs(d));
-        }
+    each_value<MAXV>(N, [&](int i, bool exists) {
+        const float v = x(i);
+        double d = __dsub_rn((double)v, m);
+        if (ALL)
+            d = exists ? d : 0.0;
+        else
+            d = exists && v >= c.lo && v <= c.hi ? d : 0.0;
+        q = __dadd_rn(q, __dmul_rn(d, d));
+        dmax = fmax(dmax, fabs(d));
+    });
 }
 
-// Clip one column; returns the mean and updates kept / dropped.
-// With MISS, NaN values are missing: never kept, not counted as dropped, and n counts
-// the others (a pixel with none gives NaN).
-template <int MAXV, bool FENCE, bool MISS, typename X>
-__device__ __forceinline__ float clip_values(X x, int32_t N, double ksigma, int32_t max_iters, KeptBits<MAXV> &kept,
+// Floats in order as integers, and back.
+__device__ __forceinline__ int32_t float_key(float v)
+{
+    const int32_t i = __float_as_int(v);
+    return i ^ ((i >> 31) & 0x7fffffff);
+}
+
+__device__ __forceinline__ float key_float(int32_t k) { return __int_as_float(k ^ ((k >> 31) & 0x7fffffff)); }
+
+// The largest float x with x - m <= thr as rounded (m and thr finite): the rounded sum m + thr
+// or its neighbour below, except where m + thr nearly cancels, when many floats round to one
+// difference and the end is found by bisection (33 steps at most).
+__device__ __forceinline__ float clip_end(double m, double thr)
+{
+    auto ok = [&](int32_t k) { return __dsub_rn((double)key_float(k), m) <= thr; };
+    const int32_t k = float_key((float)__dadd_rn(m, thr));
+    int32_t in, out;  // the end is in [in, out): ok(in), not ok(out)
+    if (ok(k)) {
+        if (!ok(k + 1)) return key_float(k);
+        in = k + 1;
+        out = float_key(INFINITY);
+    } else {
+        if (ok(k - 1)) return key_float(k - 1);
+        in = float_key(-INFINITY);
+        out = k - 1;
+    }
+    while ((int64_t)out - in > 1) {
+        const int32_t mid = (int32_t)(((int64_t)in + out) >> 1);
+        if (ok(mid)) in = mid;
+        else out = mid;
+    }
+    return key_float(in);
+}
+
+// The kept interval after an iteration with mean m and threshold thr: the floats with
+// |x - m| <= thr as rounded, within the interval so far.
+__device__ __forceinline__ void clip_narrow(ClipState &c, double m, double thr)
+{
+    c.hi = fminf(c.hi, clip_end(m, thr));
+    c.lo = fmaxf(c.lo, -clip_end(-m, thr));
+}
+
+// First iteration of a column: true, with the mean, when it settles there (nothing drops, or
+// no iterations are asked for).
+template <int MAXV, bool MISS, typename X>
+__device__ __forceinline__ bool clip_first(X x, int32_t N, double ksigma, int32_t max_iters, ClipState &c,
+                                           double &m, double &thr)
+{
+    c.lo = -INFINITY;
+    c.hi = INFINITY;
+    clip_sum<MAXV, !MISS>(x, N, c);
+    m = c.s / (double)c.n;
+    if (max_iters == 0) return true;
+    double q, dmax;
+    clip_squares<MAXV, !MISS>(x, N, c, m, q, dmax);
+    thr = __dmul_rn(ksigma, sqrt(q / (double)c.n));
+    return !(dmax > thr);
+}
+
+// The rest of the clip of a column whose first iteration (mean m, threshold thr, all values
+// present in c) drops values.
+template <int MAXV, typename X>
+__device__ __forceinline__ float clip_rest(X x, int32_t N, double ksigma, int32_t max_iters, ClipState &c, double m,
+                                           double thr, unsigned &dropped)
+{
+    for (int32_t it = 1;; ++it) {
+        const int n = c.n;
+        clip_narrow(c, m, thr);
+        clip_sum<MAXV, false>(x, N, c);
+        dropped += (unsigned)(n - c.n);
+        m = c.s / (double)c.n;
+        if (it >= max_iters) break;
+        double q, dmax;
+        clip_squares<MAXV, false>(x, N, c, m, q, dmax);
+        thr = __dmul_rn(ksigma, sqrt(q / (double)c.n));
+        if (!(dmax > thr)) break;
+    }
+    return (float)m;
+}
+
+// The whole clip of one column, its values read through x(i).  The arithmetic is that of
+// clip_column with one lane (sums in frame order in double, m = s / n, q = sum of
+// (x - m)^2, threshold ksigma * sqrt(q / n), drop |x - m| > threshold); when an iteration
+// drops nothing (the largest |x - m| tells) its own mean is the final mean.  c.lo, c.hi
+// bound the kept values.
+template <int MAXV, bool MISS, typename X>
+__device__ __forceinline__ float clip_values(X x, int32_t N, double ksigma, int32_t max_iters, ClipState &c,
                                              unsigned &dropped)
 {
-    kept.first(N);
-    int n = N;
-    if (MISS) {
-#pragma unroll
-        for (int i = 0; i < MAXV; ++i)
-            if (i < N && !(x(i) == x(i))) kept.clear(i);
-        n = 0;
-#pragma unroll
-        for (int j = 0; j < KeptBits<MAXV>::W; ++j) n += __popcll(kept.w[j]);
-    }
-    double s = 0.0, m = 0.0, q = 0.0, dmax = 0.0;
-    bool final_known = false;
-    for (int32_t it = 0; it < max_iters; ++it) {
-        if (it == 0 && !MISS)
-            clip_pass<MAXV, true, FENCE>(x, kept, N, n, s, m, q, dmax);
-        else
-            clip_pass<MAXV, false, FENCE>(x, kept, N, n, s, m, q, dmax);
-        const double thr = __dmul_rn(ksigma, sqrt(q / (double)n));
-        if (!(dmax > thr)) {
-            final_known = true;  // nothing drops: m is the mean of the final set
-            break;
-        }
-        int drop = 0;
-        clip_fence<FENCE>();
-#pragma unroll
-        for (int i = 0; i < MAXV; ++i)
-            if (kept.get(i) && fabs(__dsub_rn((double)x(i), m)) > thr) {
-                kept.clear(i);
-                ++drop;
-            }
-        n -= drop;
-        dropped += (unsigned)drop;
-    }
-    if (final_known) return (float)m;  // m = s / n of this final set
-    s = 0.0;
-    clip_fence<FENCE>();
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i)
-        if (kept.get(i)) s = __dadd_rn(s, (double)x(i));
-    return (float)(s / (double)n);
+    double m, thr;
+    if (clip_first<MAXV, MISS>(x, N, ksigma, max_iters, c, m, thr)) return (float)m;
+    return clip_rest<MAXV>(x, N, ksigma, max_iters, c, m, thr, dropped);
 }
 
-// The column in registers.  Each read goes through an empty asm statement that marks the
-// value as changed, so every pass converts it to double again instead of holding the
-// column's converted values across the passes (twice the registers; with them a compute
-// unit holds fewer waves and the kernel ran 10% slower).
-template <int MAXV, bool MISS = false>
-__device__ __forceinline__ float clip_registers(const float (&x)[MAXV], int32_t N, double ksigma, int32_t max_iters,
-                                                KeptBits<MAXV> &kept, unsigned &dropped)
-{
-    return clip_values<MAXV, false, MISS>(
-        [&](int i) {
-            float v = x[i];
-            asm volatile("" : "+v"(v));
-            return v;
-        },
-        N, ksigma, max_iters, kept, dropped);
-}
-
-// The first iteration of clip_registers alone: true, with the mean, when the column
-// settles there (nothing drops, or no iterations are asked for), the same operations in
-// the same order as clip_registers, so the mean has the same bits.
-template <int MAXV, bool MISS = false>
-__device__ __forceinline__ bool clip_first(const float (&x)[MAXV], int32_t N, double ksigma, int32_t max_iters,
-                                           float &mean)
-{
-    auto xv = [&](int i) {
+// Values in registers.  Each read goes through an empty asm statement that marks the value
+// as changed, so every pass converts it to double again instead of holding the column's
+// converted values across the passes (twice the registers; with them a compute unit holds
+// fewer waves and the kernel ran 10% slower).
+template <int MAXV>
+struct RegColumn {
+    const float (&x)[MAXV];
+    __device__ __forceinline__ float operator()(int i) const
+    {
         float v = x[i];
         asm volatile("" : "+v"(v));
         return v;
-    };
-    KeptBits<MAXV> kept;
-    kept.first(N);
-    int n = N;
-    if (MISS) {
-#pragma unroll
-        for (int i = 0; i < MAXV; ++i)
-            if (i < N && !(x[i] == x[i])) kept.clear(i);
-        n = 0;
-#pragma unroll
-        for (int j = 0; j < KeptBits<MAXV>::W; ++j) n += __popcll(kept.w[j]);
     }
-    double s, m, q, dmax;
-    if (MISS)
-        clip_pass<MAXV, false, false>(xv, kept, N, n, s, m, q, dmax);
-    else
-        clip_pass<MAXV, true, false>(xv, kept, N, n, s, m, q, dmax);
-    if (max_iters > 0 && dmax > __dmul_rn(ksigma, sqrt(q / (double)n))) return false;
-    mean = (float)m;
-    return true;
+};
+
+template <int MAXV, bool MISS = false>
+__device__ __forceinline__ float clip_registers(const float (&x)[MAXV], int32_t N, double ksigma, int32_t max_iters,
+                                                ClipState &c, unsigned &dropped)
+{
+    return clip_values<MAXV, MISS>(RegColumn<MAXV>{x}, N, ksigma, max_iters, c, dropped);
 }
 
 // PX adjacent pixel columns per thread: each frame's PX values come in as one vector
@@ -326,104 +389,100 @@ __device__ __forceinline__ bool clip_first(const float (&x)[MAXV], int32_t N, do
 // that starts 8-byte aligned taking two 8-byte loads).  Each thread runs the first
 // iteration of its columns; a column that drops values there (a few percent of them, but
 // in most waves at least one lane) goes to a queue in LDS, and once the workgroup's first
-// iterations are done its threads take the queued columns one each (their values kept in
-// LDS for columns of up to 32 values and the first 128 queued, else loaded again) and run
-// the whole clip, so the later iterations run on full waves instead of holding every wave
-// that has one such lane.
+// iterations are done its threads take the queued columns one each (their values, means and
+// thresholds kept in LDS for the first QCAP queued, else loaded and formed again) and run
+// the rest of the clip, so the later iterations run on full waves instead of holding every wave
+// that has one such lane.  No LDS copy for columns of 33 - 48 values (45 frames of 4096x2048:
+// 0.71 ms loading them again, 2.05 holding them until the queue is written); columns of
+// 49 - 128 values are built for three waves per SIMD and hold them (a quarter of 97-frame
+// columns drop a value).
 // Every result is that of clip_registers on the column.  Columns at or past `plane` are
 // neither written nor counted.  The whole workgroup must call this (it synchronises).
-template <int MAXV, int PX, bool MISS = false>
+template <int MAXV, int PX, bool MISS = false, int QCAP = (MAXV <= 32 ? 128 : MAXV <= 48 ? 0 : 96)>
 __device__ __forceinline__ unsigned combine_cols_block(const float *__restrict__ aligned, int64_t plane,
                                                        int64_t pstride, int32_t N, double ksigma, int32_t max_iters,
                                                        float *__restrict__ out, uint8_t *__restrict__ keep,
                                                        int64_t block)
 {
-    // queued columns whose values wait in LDS (later ones are loaded again); none for the
-    // 48-value columns, whose values held until the queue is written cost more registers
-    // than the loads (45 frames of 4096x2048: 0.71 ms loading, 2.05 ms holding them)
-    constexpr int QCAP = MAXV <= 32 ? 128 : 0;
     __shared__ int32_t queue[COMB_TILE * PX];         // columns (of this workgroup) that drop values
     __shared__ float qv[MAXV * (QCAP > 0 ? QCAP : 1)];  // value i of queue entry e at qv[i * QCAP + e]
+    // mean, threshold and number of values of the queued column's first iteration
+    __shared__ double qm[QCAP > 0 ? QCAP : 1], qt[QCAP > 0 ? QCAP : 1];
+    __shared__ int32_t qn[QCAP > 0 ? QCAP : 1];
     __shared__ int32_t queued;
     if (threadIdx.x == 0) queued = 0;
     const int64_t p0 = (block * COMB_TILE + threadIdx.x) * PX;
+    const int64_t pb = block * COMB_TILE * PX;  // first column of the workgroup
     float xs[PX][MAXV];
-    if (PX == 1 || p0 + PX <= plane) {
+    PlaneWalk<const float> in(aligned + pb, pstride, N);
+    if (PX > 1 && p0 + PX <= plane) {
+        const uint32_t o = threadIdx.x * PX;
+        each_group<MAXV>(N, [&](int i) {
+            // planes are aligned to two floats; the two pairs of PX = 4 become one load
+            const auto src = in.next(i) + o;
 #pragma unroll
-        for (int i = 0; i < MAXV; ++i) {
-            if (i < N) {
-                const float *src = aligned + (int64_t)i * pstride + p0;
-                if (PX == 4 && (((int64_t)i * pstride) & 3) == 0) {
-                    const float4 v = *reinterpret_cast<const float4 *>(src);
-                    xs[0][i] = v.x;
-                    xs[1][i] = v.y;
-                    xs[2][i] = v.z;
-                    xs[3][i] = v.w;
-                } else if (PX == 4) {  // a plane of even length: this frame starts 8-byte aligned
-                    const float2 u = *reinterpret_cast<const float2 *>(src);
-                    const float2 v = *reinterpret_cast<const float2 *>(src + 2);
-                    xs[0][i] = u.x;
-                    xs[1][i] = u.y;
-                    xs[2][i] = v.x;
-                    xs[3][i] = v.y;
-                } else if (PX == 2) {
-                    const float2 v = *reinterpret_cast<const float2 *>(src);
-                    xs[0][i] = v.x;
-                    xs[1][i] = v.y;
-                } else {
-                    xs[0][i] = p0 < plane ? src[0] : 0.0f;
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < PX; ++c) xs[c][i] = 0.0f;
+            for (int c = 0; c < PX; c += 2) {
+                const f32x2v v = *(const __attribute__((address_space(1))) f32x2v *)(src + c);
+                xs[c][i] = v[0];
+                if constexpr (PX > 1) xs[c + 1][i] = v[1];
             }
-        }
+        });
     } else {
+        // one column at a time; one past the plane reads the plane's last
+        uint32_t o[PX];
 #pragma unroll
-        for (int i = 0; i < MAXV; ++i)
+        for (int c = 0; c < PX; ++c) o[c] = (uint32_t)(min(p0 + c, plane - 1) - pb);
+        each_group<MAXV>(N, [&](int i) {
+            const auto src = in.next(i);
 #pragma unroll
-            for (int c = 0; c < PX; ++c)
-                xs[c][i] = (i < N && p0 + c < plane) ? aligned[(int64_t)i * pstride + p0 + c] : 0.0f;
+            for (int c = 0; c < PX; ++c) xs[c][i] = src[o[c]];
+        });
     }
     // first iterations; a column that drops values goes to the workgroup's queue
-    float res[PX];
+    double mean[PX], thr[PX];
+    int n1[PX];
     bool done[PX];
     bool all = p0 + PX <= plane;
 #pragma unroll
     for (int c = 0; c < PX; ++c) {
-        done[c] = clip_first<MAXV, MISS>(xs[c], N, ksigma, max_iters, res[c]);
+        ClipState st;
+        done[c] = clip_first<MAXV, MISS>(RegColumn<MAXV>{xs[c]}, N, ksigma, max_iters, st, mean[c], thr[c]);
+        n1[c] = st.n;
         all = all && done[c];
     }
     __syncthreads();  // the queue is empty
     if (PX > 1 && all) {
-        if (PX == 4)
-            *reinterpret_cast<float4 *>(out + p0) = make_float4(res[0], res[1], res[2], res[3]);
-        else
-            *reinterpret_cast<float2 *>(out + p0) = make_float2(res[0], res[1]);
+        if constexpr (PX == 4)
+            *reinterpret_cast<float4 *>(out + p0) = make_float4((float)mean[0], (float)mean[1], (float)mean[2],
+                                                                   (float)mean[3]);
+        else if constexpr (PX == 2)
+            *reinterpret_cast<float2 *>(out + p0) = make_float2((float)mean[0], (float)mean[1]);
     } else {
 #pragma unroll
         for (int c = 0; c < PX; ++c)
             if (p0 + c < plane) {
                 if (done[c]) {
-                    out[p0 + c] = res[c];
+                    out[p0 + c] = (float)mean[c];
                 } else {
                     const int32_t e = atomicAdd(&queued, 1);
                     queue[e] = (int32_t)threadIdx.x * PX + c;
                     if (e < QCAP) {
-#pragma unroll
-                        for (int i = 0; i < MAXV; ++i) qv[i * QCAP + e] = xs[c][i];
+                        each_group<MAXV>(N, [&](int i) { qv[i * QCAP + e] = xs[c][i]; });
+                        qm[e] = mean[c];
+                        qt[e] = thr[c];
+                        qn[e] = n1[c];
                     }
                 }
             }
     }
     if (keep) {  // a settled column keeps every value (every value present)
+        PlaneWalk<uint8_t> to(keep + pb, plane, N);
+        each_value<MAXV>(N, [&](int i, bool exists) {
+            const auto dst = to.next(i) + threadIdx.x * PX;
 #pragma unroll
-        for (int i = 0; i < MAXV; ++i)
-            if (i < N)
-#pragma unroll
-                for (int c = 0; c < PX; ++c)
-                    if (p0 + c < plane && done[c])
-                        keep[(int64_t)i * plane + p0 + c] = (uint8_t)(!MISS || xs[c][i] == xs[c][i]);
+            for (int c = 0; c < PX; ++c)
+                if (exists && p0 + c < plane && done[c]) dst[c] = (uint8_t)(!MISS || xs[c][i] == xs[c][i]);
+        });
     }
     __syncthreads();
     // the queued columns, one per thread: the whole clip (values from LDS, past QCAP
@@ -431,169 +490,45 @@ __device__ __forceinline__ unsigned combine_cols_block(const float *__restrict__
     unsigned dropped = 0;
     const int32_t nq = queued;
     for (int32_t e = threadIdx.x; e < nq; e += COMB_TILE) {
-        const int64_t p = block * COMB_TILE * PX + queue[e];
+        const uint32_t o = (uint32_t)queue[e];
+        const int64_t p = pb + o;
         float x[MAXV];
+        if (e < QCAP)
+            each_group<MAXV>(N, [&](int i) { x[i] = qv[i * QCAP + e]; });
+        else {
+            PlaneWalk<const float> again(aligned + pb, pstride, N);
+            each_group<MAXV>(N, [&](int i) { x[i] = again.next(i)[o]; });
+        }
+        ClipState st;
+        double m, t;
         if (e < QCAP) {
-#pragma unroll
-            for (int i = 0; i < MAXV; ++i) x[i] = qv[i * QCAP + e];
+            st.lo = -INFINITY;
+            st.hi = INFINITY;
+            st.n = qn[e];
+            m = qm[e];
+            t = qt[e];
         } else {
-#pragma unroll
-            for (int i = 0; i < MAXV; ++i) x[i] = i < N ? aligned[(int64_t)i * pstride + p] : 0.0f;
+            clip_first<MAXV, MISS>(RegColumn<MAXV>{x}, N, ksigma, max_iters, st, m, t);
         }
-        KeptBits<MAXV> kept;
-        out[p] = clip_registers<MAXV, MISS>(x, N, ksigma, max_iters, kept, dropped);
+        out[p] = clip_rest<MAXV>(RegColumn<MAXV>{x}, N, ksigma, max_iters, st, m, t, dropped);
         if (keep) {
-#pragma unroll
-            for (int i = 0; i < MAXV; ++i)
-                if (i < N) keep[(int64_t)i * plane + p] = (uint8_t)kept.get(i);
+            PlaneWalk<uint8_t> to(keep + pb, plane, N);
+            each_value<MAXV>(N, [&](int i, bool exists) {
+                const auto dst = to.next(i) + o;
+                if (exists) *dst = (uint8_t)(x[i] >= st.lo && x[i] <= st.hi);
+            });
         }
     }
     return dropped;
 }
 
-// Stacks deeper than a register column: a 64-thread workgroup, one thread per pixel
-// column; the first 32 values of a column stay in registers, the others wait in the
-// thread's own slice of an LDS tile [N - 32][64] (each thread writes and reads only its
-// own column, so no barrier is needed).  The frames
-// come in batches of 32 loads in flight; the passes loop over the frames at run time
-// with the kept flags in two 64-bit words.  Same arithmetic, in the same order, as
-// clip_values (sums over the kept values in frame order, m = s / n, the squared
-// deviations and the largest one, the threshold, the drops).  With MISS, NaN values are
-// missing: never kept, not counted as dropped, and n counts the others (a pixel with
-// none gives NaN).
-constexpr int COMB_DEEP_PX = 64;
-constexpr int COMB_DEEP_BATCH = 64;  // the most loads a wave keeps in flight
-constexpr int COMB_DEEP_REG = 32;    // the first values of a column stay in registers
-static_assert(COMB_DEEP_REG < COMB_MAX_N + 1, "the LDS-column kernels serve stacks deeper than COMB_MAX_N");
-
-// f(i, x_i, kept_i) for the values of a column in frame order (f selects rather than
-// branches on kept_i): values 0 .. COMB_DEEP_REG-1 from xr, the others from the LDS
-// slice col (value i at col[(i - COMB_DEEP_REG) * COMB_DEEP_PX]); the kept flags are
-// bit i of k0 (i < 64) and bit i - 64 of k1.  N > COMB_DEEP_REG.
+// Register class of a stack of 49 - 128 frames.
 template <typename F>
-__device__ __forceinline__ void deep_each(const float (&xr)[COMB_DEEP_REG], const float *col, uint64_t k0,
-                                          uint64_t k1, int32_t N, F f)
+inline void deep_dispatch(int32_t N, F &&f)
 {
-#pragma unroll
-    for (int i = 0; i < COMB_DEEP_REG; ++i) f(i, (double)xr[i], ((k0 >> i) & 1ull) != 0);
-    uint64_t w = k0 >> COMB_DEEP_REG;
-    const int32_t n0 = min(N, 64);
-#pragma unroll 4
-    for (int i = COMB_DEEP_REG; i < n0; ++i, w >>= 1)
-        f(i, (double)col[(i - COMB_DEEP_REG) * COMB_DEEP_PX], (w & 1ull) != 0);
-    w = k1;
-#pragma unroll 4
-    for (int i = 64; i < N; ++i, w >>= 1) f(i, (double)col[(i - COMB_DEEP_REG) * COMB_DEEP_PX], (w & 1ull) != 0);
-}
-
-// f(x_i) for every value of a column in frame order (all of them kept: the first
-// iteration without missing values).  The empty asm statements mark the register
-// values as changed, so each pass converts them to double again instead of holding 32
-// converted values (64 more registers) across the passes.
-template <typename F>
-__device__ __forceinline__ void deep_each_all(float (&xr)[COMB_DEEP_REG], const float *col, int32_t N, F f)
-{
-#pragma unroll
-    for (int i = 0; i < COMB_DEEP_REG; ++i) asm volatile("" : "+v"(xr[i]));
-#pragma unroll
-    for (int i = 0; i < COMB_DEEP_REG; ++i) f((double)xr[i]);
-#pragma unroll 4
-    for (int i = COMB_DEEP_REG; i < N; ++i) f((double)col[(i - COMB_DEEP_REG) * COMB_DEEP_PX]);
-}
-
-template <bool MISS>
-__device__ __forceinline__ unsigned combine_deep_block(const float *__restrict__ aligned, int64_t plane,
-                                                       int64_t pstride, int32_t N, double ksigma, int32_t max_iters,
-                                                       float *__restrict__ out, uint8_t *__restrict__ keep,
-                                                       int64_t block, float *tile)
-{
-    const int t = threadIdx.x;
-    const int64_t p = block * COMB_DEEP_PX + t;
-    const float *src = aligned + (p < plane ? p : plane - 1);
-    float *col = tile + t;  // values COMB_DEEP_REG .. N-1 (the tile is [N - COMB_DEEP_REG][64])
-    float xr[COMB_DEEP_REG];
-    for (int32_t i0 = 0; i0 < N; i0 += COMB_DEEP_BATCH) {
-        float v[COMB_DEEP_BATCH];
-#pragma unroll
-        for (int j = 0; j < COMB_DEEP_BATCH; ++j) v[j] = src[(int64_t)min(i0 + j, N - 1) * pstride];
-        if (i0 == 0) {
-#pragma unroll
-            for (int j = 0; j < COMB_DEEP_REG; ++j) xr[j] = v[j];
-        }
-#pragma unroll
-        for (int j = 0; j < COMB_DEEP_BATCH; ++j)
-            if (i0 + j >= COMB_DEEP_REG && i0 + j < N) col[(i0 + j - COMB_DEEP_REG) * COMB_DEEP_PX] = v[j];
-    }
-    uint64_t k0 = N >= 64 ? ~0ull : ((1ull << N) - 1ull);
-    uint64_t k1 = N >= 128 ? ~0ull : N <= 64 ? 0ull : ((1ull << (N - 64)) - 1ull);
-    int n = N;
-    if (MISS) {
-        uint64_t m0 = 0, m1 = 0;
-        deep_each(xr, col, k0, k1, N, [&](int i, double x, bool k) {
-            const uint64_t bit = (k && x == x) ? 1ull : 0ull;
-            if (i < 64) m0 |= bit << i;
-            else m1 |= bit << (i - 64);
-        });
-        k0 = m0;
-        k1 = m1;
-        n = __popcll(k0) + __popcll(k1);
-    }
-    unsigned dropped = 0;
-    // the drop pass of one iteration also forms the next sum (the same values in the
-    // same order as a separate pass over the kept set)
-    // before the first drop (and without missing values) every value is kept: the same
-    // sums without the flag selects
-    double s = 0.0;
-    if (MISS)
-        deep_each(xr, col, k0, k1, N, [&](int, double x, bool k) { s = k ? __dadd_rn(s, x) : s; });
-    else
-        deep_each_all(xr, col, N, [&](double x) { s = __dadd_rn(s, x); });
-    double mean = -1.0;
-    bool final_known = false;
-    for (int32_t it = 0; it < max_iters; ++it) {
-        const double m = s / (double)n;
-        double q = 0.0, dmax = 0.0;
-        if (!MISS && it == 0)
-            deep_each_all(xr, col, N, [&](double x) {
-                const double d = __dsub_rn(x, m);
-                q = __dadd_rn(q, __dmul_rn(d, d));
-                dmax = fmax(dmax, fabs(d));
-            });
-        else
-            deep_each(xr, col, k0, k1, N, [&](int, double x, bool k) {
-                const double d = __dsub_rn(x, m);
-                q = k ? __dadd_rn(q, __dmul_rn(d, d)) : q;
-                dmax = k ? fmax(dmax, fabs(d)) : dmax;
-            });
-        const double thr = __dmul_rn(ksigma, sqrt(q / (double)n));
-        if (!(dmax > thr)) {  // nothing drops: m is the mean of the final set
-            mean = m;
-            final_known = true;
-            break;
-        }
-        int drop = 0;
-        s = 0.0;
-        uint64_t n0 = 0, n1 = 0;  // the flags after this iteration
-        deep_each(xr, col, k0, k1, N, [&](int i, double x, bool k) {
-            const bool out = k && fabs(__dsub_rn(x, m)) > thr;
-            const bool stay = k && !out;
-            drop += out ? 1 : 0;
-            s = stay ? __dadd_rn(s, x) : s;
-            const uint64_t bit = stay ? 1ull : 0ull;
-            if (i < 64) n0 |= bit << i;
-            else n1 |= bit << (i - 64);
-        });
-        k0 = n0;
-        k1 = n1;
-        n -= drop;
-        dropped += (unsigned)drop;
-    }
-    if (p >= plane) return 0u;
-    out[p] = (float)(final_known ? mean : s / (double)n);
-    if (keep)
-        for (int i = 0; i < N; ++i)
-            keep[(int64_t)i * plane + p] = (uint8_t)((((i < 64 ? k0 : k1) >> (i & 63)) & 1ull) != 0);
-    return dropped;
+    if (N <= 64) f(std::integral_constant<int, 64>{});
+    else if (N <= 104) f(std::integral_constant<int, 104>{});
+    else f(std::integral_constant<int, 128>{});
 }
 
 }  // namespace rd
