@@ -126,6 +126,8 @@ KERNEL_SYMBOLS = {"batch_score": "batch_score", "batch_shift": "batch_shift", "b
                   "combine": ["combine_cols<", "false>"], "combine_deep": "combine_deep<false>",
                   "combine_missing": ["combine_cols<", "true>"], "mask_shifted": "mask_shifted",
                   "shift_spline": ("spline_rows", "spline_cols")}  # one call = both passes
+# counter runs of builds that do the same in one kernel
+ONE_KERNEL = {"shift_spline": "spline_shift"}
 
 
 def source_hash(kernel):
@@ -174,6 +176,8 @@ def traffic_from(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, workload,
         if k not in kernels:
             continue
         syms = syms if isinstance(syms, tuple) else (syms,)  # a call of several kernels: their sum
+        if any(ONE_KERNEL.get(k, "\0") in n for n, _ in fr):
+            syms = (ONE_KERNEL[k],)
         fetch = write = 0.0
         dispatches = None
         for sym in syms:

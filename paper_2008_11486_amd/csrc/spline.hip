@@ -17,12 +17,14 @@
 // Positions are clamped into [0, L-1] (inside the overlap they never need it); a clamped
 // position takes f[0] or f[L-1].
 //
-// Two streaming passes, FP32 arithmetic: rows (every frame row at the shifted x of every
-// output column, into a workspace [N][H][w]), then columns of that result at the shifted
-// y.  The shift is the same for the whole frame, so output u sits on knot x0 + fx + u
-// (before clamping) with the same fraction: a thread that owns a run of knots holds in
-// registers everything its run's outputs need.
+// One pass, FP32 arithmetic: a workgroup walks down a strip of columns, forms the row
+// splines of 64 frame rows at a time at the shifted x of its columns, keeps them in LDS and
+// takes the column splines of those at the shifted y.  The shift is the same for the whole
+// frame, so output u sits on knot x0 + fx + u (before clamping) with the same fraction: a
+// thread that owns a run of knots holds in registers everything its run's outputs need.
+#include <algorithm>
 #include <string>
+#include <type_traits>
 
 #include "common.h"
 #include "shift_core.h"  // clampi
@@ -31,7 +33,7 @@ namespace rd {
 
 constexpr int SP_T = 16;                          // recursion warm-up, knots
 constexpr double SP_Z = -0.26794919243112270;     // sqrt 3 - 2
-constexpr double SP_C = 0.28867513459481287;      // 1 / (2 sqrt 3)
+constexpr double SP_H0 = 0.28867513459481287;     // 1 / (2 sqrt 3)
 
 struct SpTaps {
     float v[SP_T + 1];
@@ -41,7 +43,7 @@ __host__ __device__ constexpr SpTaps sp_taps()
     SpTaps t{};
     double p = 1.0;
     for (int j = 0; j <= SP_T; ++j) {
-        t.v[j] = (float)(SP_C * p);
+        t.v[j] = (float)(SP_H0 * p);
         p *= SP_Z;
     }
     return t;
@@ -128,13 +130,10 @@ __device__ __forceinline__ void sp_ends_raw(float P0, float PL, int32_t L, float
                                             float &A, float &B)
 {
     sp_ends(P0, PL, L, A, B);
-    const float c6 = (float)(6.0 * SP_C);
+    const float c6 = (float)(6.0 * SP_H0);
     A -= c6 * fmaf(-2.0f, f0, f1 + f0);    // the recursion's own g at knot 0
     B -= c6 * fmaf(-2.0f, fl1, fl1 + fl2);  // and at knot L-1
 }
-
-// End corrections are needed only within a few dozen knots of a line end (z^40 < 1e-22).
-constexpr int SP_NEAR = 40;
 
 // The outputs of a run of K knots s .. s+K-1 (M of knot s+K is p[K]): fw and p as in
 // sp_recur.  Knots at or beyond an end first get their M (zero at both ends, plus the
@@ -144,12 +143,24 @@ template <int K>
 __device__ __forceinline__ void sp_outputs(const float (&fw)[K + 2 * SP_T + 3], float (&p)[K + 1], int32_t s,
                                            int32_t L, bool near, float A, float B, const SpW &wt, float (&o)[K])
 {
+    // (the powers of z by products along the run: a power per knot and end, an exp2 each, made
+    // the correction cost more than the recursions in rows of one run)
     if (near) {
+        const float z = (float)SP_Z;
+        float e = A * sp_zpow(max(s, 0));  // A z^i, from knot max(s, 0) on
 #pragma unroll
         for (int r = 0; r <= K; ++r) {
-            const int32_t i = s + r;
-            p[r] = (i <= 0 || i >= L - 1) ? 0.0f : p[r] + A * sp_zpow(i) + B * sp_zpow(L - 1 - i);
+            p[r] += e;
+            e = s + r >= 0 ? e * z : e;
         }
+        e = B * sp_zpow(max(L - 1 - (s + K), 0));  // B z^(L-1-i), from knot min(s + K, L - 1) back
+#pragma unroll
+        for (int r = K; r >= 0; --r) {
+            p[r] += e;
+            e = s + r <= L - 1 ? e * z : e;
+        }
+#pragma unroll
+        for (int r = 0; r <= K; ++r) p[r] = s + r <= 0 || s + r >= L - 1 ? 0.0f : p[r];
     }
 #pragma unroll
     for (int r = 0; r < K; ++r) {
@@ -161,172 +172,156 @@ __device__ __forceinline__ void sp_outputs(const float (&fw)[K + 2 * SP_T + 3], 
     }
 }
 
-// LDS index of staged value (or output) e: a pad word every 16 puts the stride-16
-// windows of the lanes on distinct banks.
-__device__ __forceinline__ int sp_pad(int e) { return e + (e >> 4); }
+// ---- both passes in one --------------------------------------------------------------------
+constexpr int SP_C = 64;                     // output columns of a strip
+constexpr int SP_V = 32;                     // frame rows per batch, output rows per tile
+constexpr int SP_Q = 16;                     // knots per thread, along x and along y
+constexpr int SP_THREADS = SP_V * SP_C / SP_Q;
+constexpr int SP_X = SP_C + 1 + 2 * SP_T + 2;  // staged values of a row; odd modulo 16, so that the 16 rows x 4
+                                               // runs of a wave's windows start on distinct banks
+constexpr int SP_RING = 96;                  // ring of row-spline lines: three batches (a tile reads 67 lines)
+constexpr int SP_RP = SP_C + 1;              // its pitch: a wave stores 16 rows x 4 runs at once
+constexpr int SP_NR = SP_V * 64 / SP_THREADS;  // rows a wave stages
+static_assert(SP_X % 2 == 1 && SP_X > 64 && SP_X <= 128, "two loads per staged row");
+constexpr int SP_AHEAD = SP_RING / SP_V - 1;   // batches formed before a tile
+static_assert(SP_RING % SP_V == 0 && SP_V + 2 * SP_T + 3 <= SP_RING, "a tile's lines");
 
-// ---- pass 1: rows -------------------------------------------------------------------------
-constexpr int SP_N = 64;                           // lanes: one wave per workgroup
-constexpr int SP_Q = 16;                           // knots (outputs) per lane
-constexpr int SP_U = SP_N * SP_Q;                  // outputs per workgroup
-constexpr int SP_F = SP_U + 1 + 2 * SP_T + 2;      // staged values
-constexpr int SP_NL = (SP_F + SP_N - 1) / SP_N;    // staged values per lane
-constexpr int SP_FP = SP_F + (SP_F >> 4) + 1;
-
-// A workgroup takes 1024 output columns of one row: it stages their knots' values plus a
-// 17-value halo, every lane runs the two recursions over its 16 knots and forms their
-// outputs, which go back through LDS so that consecutive lanes store consecutive columns.
-__global__ __launch_bounds__(SP_N) void spline_rows(const float *__restrict__ in, float *__restrict__ R, int32_t W,
-                                                    int32_t H, const float *__restrict__ offs, int32_t x0, int32_t w,
-                                                    int32_t wp)
+// The line ends matter to knots within SP_T + 1 of them only (|z|^18 < 6e-11 of the end's
+// second derivative); a run of knots from ka on with an end that near, or with
+// knots outside the line, is an end run.
+__device__ __forceinline__ bool sp_end_run(int32_t ka, int32_t run, int32_t L)
 {
-    __shared__ float fs[SP_FP];
-    const int32_t k = blockIdx.z, j = blockIdx.y, u0 = blockIdx.x * SP_U;
-    const int t = threadIdx.x;
-    const float sx = offs[2 * k];
-    const float fl = floorf(sx);
-    const int32_t fx = (int32_t)fl;
-    const float *row = in + ((int64_t)k * H + j) * W;
-    float *dst = R + ((int64_t)k * H + j) * wp;
-    const int32_t L = W;
-    const int32_t un = min(u0 + SP_U, w) - u0;
-    if (L < 2) {
-        for (int32_t d = t; d < un; d += SP_N) dst[u0 + d] = row[0];
-        return;
-    }
-    const int32_t ka = x0 + u0 + fx;     // knot of output u0 (before clamping)
-    const int32_t base = ka - SP_T - 1;  // line index of staged value 0
-    const bool near0 = ka < SP_NEAR, nearL = ka + SP_U + 1 > L - 1 - SP_NEAR;  // uniform
-    {
-        float v[SP_NL];
-#pragma unroll
-        for (int r = 0; r < SP_NL; ++r) v[r] = row[clampi(base + t + SP_N * r, 0, L - 1)];
-#pragma unroll
-        for (int r = 0; r < SP_NL; ++r)
-            if (t + SP_N * r < SP_F) fs[sp_pad(t + SP_N * r)] = v[r];
-    }
-    float A = 0.0f, B = 0.0f;
-    if (near0 || nearL) {
-        auto get = [&](int32_t i) { return row[i]; };
-        sp_ends_raw(near0 ? sp_end_p(get, L, 0) : 0.0f, nearL ? sp_end_p(get, L, 1) : 0.0f, L, row[0],
-                    row[min(1, L - 1)], row[max(L - 2, 0)], row[L - 1], A, B);
-    }
-    __syncthreads();
-    float o[SP_Q];
-    {
-        const int q0 = SP_Q * t;
-        float fw[SP_Q + 2 * SP_T + 3], p[SP_Q + 1];
-#pragma unroll
-        for (int r = 0; r < SP_Q + 2 * SP_T + 3; ++r) fw[r] = fs[sp_pad(q0 + r)];
-        sp_recur<SP_Q>(fw, p);
-        sp_outputs<SP_Q>(fw, p, ka + q0, L, near0 || nearL, A, B, sp_weights(sx - fl), o);
-    }
-    __syncthreads();  // every lane has read its window
-#pragma unroll
-    for (int r = 0; r < SP_Q; ++r) fs[sp_pad(SP_Q * t + r)] = o[r];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < SP_Q; ++q) {
-        const int d = t + SP_N * q;  // consecutive lanes store consecutive columns
-        if (d < un) dst[u0 + d] = fs[sp_pad(d)];
-    }
+    return L < 2 || ka <= SP_T + 1 || ka + run >= L - 2 - SP_T;
 }
 
-// ---- pass 2: columns ----------------------------------------------------------------------
-constexpr int SPC_C = 64;                          // columns per workgroup
-constexpr int SPC_G = 4;                           // row groups (threads = SPC_C * SPC_G)
-constexpr int SPC_Q = 16;                          // knots (output rows) per thread and tile
-constexpr int SPC_V = SPC_G * SPC_Q;               // output rows per tile
-constexpr int SPC_F = SPC_V + 1 + 2 * SP_T + 2;    // line values a tile reads
-constexpr int SPC_RING = 128;                      // LDS ring of line values (>= SPC_F)
-constexpr int SPC_NT = 2;                          // tiles per workgroup (short walks keep the
-                                                   // workgroups that run together on the same
-                                                   // rows: 8-tile walks were 10% slower)
-constexpr int SPC_NL0 = (SPC_F + SPC_G - 1) / SPC_G;
-constexpr int SPC_NL = SPC_V / SPC_G;              // new lines per thread and tile
-constexpr int SP_E = SP_T + 2;                     // values at each line end that P[0], P[L-1] read
-static_assert(SPC_RING >= SPC_F && (SPC_RING & (SPC_RING - 1)) == 0, "ring");
-static_assert(2 * SP_E <= SPC_RING, "the end values pass through the ring");
-
-// A workgroup walks down SPC_NT tiles of 64 columns x 64 output rows.  Line value m of a
-// column sits in ring row m mod 128; a tile whose first output row sits on knot kb reads
-// lines kb - 17 .. kb + 81, so the next tile adds 64 new lines, loaded into registers
-// while the current tile is computed and stored once its reads are done.  A thread's 16
-// output rows are its own knots.  The end corrections are the same for every tile of a
-// column: each thread forms them for its column at the start.
-__global__ __launch_bounds__(SPC_C *SPC_G) void spline_cols(const float *__restrict__ R, float *__restrict__ out,
-                                                            int32_t H, const float *__restrict__ offs, int32_t y0,
-                                                            int32_t w, int32_t wp, int32_t h)
+// (A, B) of a line from the values of an end run's window, get(i) = f[i].
+template <typename Get>
+__device__ __forceinline__ void sp_run_ends(Get get, int32_t ka, int32_t run, int32_t L, float &A, float &B)
 {
-    __shared__ float ring[SPC_RING][SPC_C];
-    const int32_t k = blockIdx.z, vs = blockIdx.y * SPC_V * SPC_NT, c0 = blockIdx.x * SPC_C;
-    const int32_t ve = min(vs + SPC_V * SPC_NT, h);
-    const int c = threadIdx.x % SPC_C, rg = threadIdx.x / SPC_C;
-    const float sy = offs[2 * k + 1];
-    const float fl = floorf(sy);
-    const int32_t fy = (int32_t)fl;
-    const int32_t L = H;
-    const int32_t col = min(c0 + c, w - 1);
-    const bool live = c0 + c < w;
-    const float *src = R + (int64_t)k * H * wp + col;
-    auto at = [&](int32_t i) { return src[(int64_t)clampi(i, 0, L - 1) * wp]; };
-    if (L < 2) {
-        for (int32_t v = vs + rg; v < ve; v += SPC_G)
-            if (live) out[((int64_t)k * h + v) * w + c0 + c] = at(0);
-        return;
-    }
-    int32_t kb = y0 + vs + fy;  // knot of the tile's first output row (before clamping)
-    const bool near0 = kb < SP_NEAR, nearL = y0 + ve - 1 + fy + 1 > L - 1 - SP_NEAR;  // uniform
-    float A = 0.0f, B = 0.0f;
-    if (near0 || nearL) {
-        // ring row e holds f[e] and ring row SP_E + e holds f[L - SP_E + e] (indices clamped
-        // into the line) until the first tile is staged; sp_end_p reads only 0 .. L-1
-        for (int e = rg; e < 2 * SP_E; e += SPC_G) ring[e][c] = at(e < SP_E ? e : L - 2 * SP_E + e);
-        __syncthreads();
-        auto lo = [&](int32_t i) { return ring[min(i, SP_E - 1)][c]; };
-        auto hi = [&](int32_t i) { return ring[SP_E + max(i - (L - SP_E), 0)][c]; };
-        sp_ends_raw(near0 ? sp_end_p(lo, L, 0) : 0.0f, nearL ? sp_end_p(hi, L, 1) : 0.0f, L, lo(0), lo(1),
-                    hi(L - 2), hi(L - 1), A, B);
-        __syncthreads();
-    }
-    {
-        float v[SPC_NL0];
+    // with no knot of the line in the run every output is a clamped value
+    const bool any = ka + run >= 0 && ka <= L - 1 && L >= 2;
+    const bool near0 = any && ka <= SP_T + 1, nearL = any && ka + run >= L - 2 - SP_T;
+    A = B = 0.0f;
+    if (near0 || nearL)
+        sp_ends_raw(near0 ? sp_end_p(get, L, 0) : 0.0f, nearL ? sp_end_p(get, L, 1) : 0.0f, L,
+                    near0 ? get(0) : 0.0f, near0 ? get(1) : 0.0f, nearL ? get(L - 2) : 0.0f,
+                    nearL ? get(L - 1) : 0.0f, A, B);
+}
+
+// A workgroup takes a strip of 64 output columns and n_tile tiles of 32 output rows of frame k.
+// Batch b is the frame rows kb0 - 17 + 32 b ... of the walk whose first output row sits on
+// knot kb0 (rows and columns clamped into the frame): 32 rows x 99 values are staged in LDS,
+// four threads per row run the two recursions over 16 knots each and put the row splines
+// into the ring, line m of the walk at ring row m mod 96.  Tile i reads lines 32 i ... 32 i
+// + 66, batches i to i + 2; a thread has one column and 16 knots.  The next batch's loads
+// are in flight while a batch and a tile are computed.
+//
+// Bound by HBM and by the recursions' issue alike.  Row and column passes over a workspace
+// moved the frames twice (0.79 ms for 180 frames of 1020x1020, 0.68 with the end corrections
+// by products); in one pass 0.49 ms, reading and writing once being 0.31 at the copy rate; batches of 64 rows 0.50.
+// Strips of 64 columns read 99 for them, mostly from L2: neighbouring strips run on one XCD.
+__global__ __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void spline_shift(
+    const float *__restrict__ in, float *__restrict__ out, int32_t W, int32_t H, const float *__restrict__ offs,
+    int32_t x0, int32_t y0, int32_t w, int32_t h, int32_t n_strip, int32_t n_seg, int32_t n_tile)
+{
+    __shared__ float st[SP_V * SP_X];
+    __shared__ float ring[SP_RING * SP_RP];
+    const int32_t id = xcd_logical_id((int32_t)blockIdx.x, (int32_t)gridDim.x);
+    const int32_t strip = id % n_strip, sk = id / n_strip, seg = sk % n_seg, k = sk / n_seg;
+    const int32_t c0 = strip * SP_C, v_lo = seg * n_tile * SP_V, v_hi = min(v_lo + n_tile * SP_V, h);
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const float sx = offs[2 * k], sy = offs[2 * k + 1];
+    const float flx = floorf(sx), fly = floorf(sy);
+    const int32_t ka = x0 + c0 + (int32_t)flx;   // knot of the strip's first column (before clamping)
+    const int32_t kb0 = y0 + v_lo + (int32_t)fly;  // knot of the walk's first row
+    const int32_t xb = ka - SP_T - 1, yb = kb0 - SP_T - 1;
+    const float *f = in + (int64_t)k * W * H;
+    const SpW wx = sp_weights(sx - flx), wy = sp_weights(sy - fly);
+    const bool end_x = sp_end_run(ka, SP_C, W);
+    // the second load of a row repeats its last value in the lanes past it
+    const int32_t cx0 = clampi(xb + lane, 0, W - 1), cx1 = clampi(xb + min(64 + lane, SP_X - 1), 0, W - 1);
+    float r0[SP_NR], r1[SP_NR];
+    auto load = [&](int32_t b) {  // wave wv: rows wv, wv + 4, ... of batch b
 #pragma unroll
-        for (int r = 0; r < SPC_NL0; ++r) v[r] = at(kb - SP_T - 1 + rg + SPC_G * r);
-#pragma unroll
-        for (int r = 0; r < SPC_NL0; ++r)
-            if (rg + SPC_G * r < SPC_F) ring[(kb - SP_T - 1 + rg + SPC_G * r) & (SPC_RING - 1)][c] = v[r];
-    }
-    const SpW wt = sp_weights(sy - fl);
-    const int q0 = SPC_Q * rg;
-    for (int32_t v0 = vs; v0 < ve; v0 += SPC_V, kb += SPC_V) {
-        __syncthreads();  // the ring holds this tile's lines
-        // the next tile's new lines: hi .. hi + 63
-        const int32_t hi = kb + SPC_F - SP_T - 1;
-        const bool more = v0 + SPC_V < ve;
-        float nv[SPC_NL];
-        if (more) {
-#pragma unroll
-            for (int r = 0; r < SPC_NL; ++r) nv[r] = at(hi + rg + SPC_G * r);
+        for (int i = 0; i < SP_NR; ++i) {
+            const float *row = f + (int64_t)clampi(yb + SP_V * b + wv + (SP_THREADS / 64) * i, 0, H - 1) * W;
+            r0[i] = row[cx0];
+            r1[i] = row[cx1];
         }
-        float o[SPC_Q];
+    };
+    const int32_t tiles = (v_hi - v_lo + SP_V - 1) / SP_V;
+    load(0);
+    for (int32_t b = 0, slot = 0; b < tiles + SP_AHEAD; ++b, slot = slot + SP_V < SP_RING ? slot + SP_V : 0) {
+        // the previous batch's windows have been read (barrier after them)
+#pragma unroll
+        for (int i = 0; i < SP_NR; ++i) st[(wv + (SP_THREADS / 64) * i) * SP_X + lane] = r0[i];
+        if (lane < SP_X - 64) {
+#pragma unroll
+            for (int i = 0; i < SP_NR; ++i) st[(wv + (SP_THREADS / 64) * i) * SP_X + 64 + lane] = r1[i];
+        }
+        if (b + 1 < tiles + SP_AHEAD) load(b + 1);
+        __syncthreads();  // the batch is staged, and the ring's older half has been read
         {
-            float fw[SPC_Q + 2 * SP_T + 3], p[SPC_Q + 1];
-            const int32_t m0 = kb + q0 - SP_T - 1;
+            const int rr = t >> 2, q0 = SP_Q * (t & 3);
+            float fw[SP_Q + 2 * SP_T + 3], p[SP_Q + 1], o[SP_Q];
+            const float *win = st + rr * SP_X;
 #pragma unroll
-            for (int r = 0; r < SPC_Q + 2 * SP_T + 3; ++r) fw[r] = ring[(m0 + r) & (SPC_RING - 1)][c];
-            sp_recur<SPC_Q>(fw, p);
-            sp_outputs<SPC_Q>(fw, p, kb + q0, L, near0 || nearL, A, B, wt, o);
+            for (int r = 0; r < SP_Q + 2 * SP_T + 3; ++r) fw[r] = win[q0 + r];
+            float A = 0.0f, B = 0.0f;
+            int32_t kx = ka;
+            asm volatile("" : "+s"(kx));  // the tests of the run's knots are not kept across batches (they spill)
+            if (end_x) sp_run_ends([&](int32_t i) { return win[i - xb]; }, kx, SP_C, W, A, B);
+            sp_recur<SP_Q>(fw, p);
+            sp_outputs<SP_Q>(fw, p, kx + q0, W, end_x, A, B, wx, o);
+            float *line = ring + (slot + rr) * SP_RP + q0;
+#pragma unroll
+            for (int r = 0; r < SP_Q; ++r) line[r] = o[r];
         }
-        if (live) {
+        __syncthreads();
+        if (b < SP_AHEAD) continue;
+        // the tile's first row in the walk; its lines are i0 ..., in the ring from the slot after
+        // this batch's on (the oldest)
+        const int32_t i0 = SP_V * (b - SP_AHEAD);
+        const int32_t s0 = slot + SP_V < SP_RING ? slot + SP_V : 0;
+        const int c = lane, q0 = SP_Q * wv;
+        const int32_t kb = kb0 + i0;
+        auto line = [&](int32_t m) {  // line m of the walk
+            const int32_t r = s0 + m - i0;
+            return ring[(r < SP_RING ? r : r - SP_RING) * SP_RP + c];
+        };
+        float fw[SP_Q + 2 * SP_T + 3], p[SP_Q + 1], o[SP_Q];
+        // the window's first line sits at a multiple of 16 in the ring: each place where it wraps
+        // has its own reads at fixed offsets (an address per read was a fifth of the pass)
+        const int32_t w0 = s0 + q0;  // < SP_RING
+        const float *first = ring + w0 * SP_RP + c;
+        auto window = [&](auto Wc) {
+            constexpr int wrap = decltype(Wc)::value;  // reads from `wrap` on start over
 #pragma unroll
-            for (int r = 0; r < SPC_Q; ++r)
-                if (v0 + q0 + r < ve) out[((int64_t)k * h + v0 + q0 + r) * w + c0 + c] = o[r];
+            for (int r = 0; r < SP_Q + 2 * SP_T + 3; ++r) fw[r] = first[(r < wrap ? r : r - SP_RING) * SP_RP];
+        };
+        static_assert(SP_RING == 96 && SP_Q == 16, "places of the wrap");
+        switch (w0) {
+        case 48: window(std::integral_constant<int, 48>{}); break;
+        case 64: window(std::integral_constant<int, 32>{}); break;
+        case 80: window(std::integral_constant<int, 16>{}); break;
+        default: window(std::integral_constant<int, SP_RING>{}); break;
         }
-        if (more) {
-            __syncthreads();  // this tile's reads of the ring are done
+        const bool end_y = sp_end_run(kb, SP_V, H);
+        float A = 0.0f, B = 0.0f;
+        if (end_y) sp_run_ends([&](int32_t i) { return line(i - yb); }, kb, SP_V, H, A, B);
+        sp_recur<SP_Q>(fw, p);
+        sp_outputs<SP_Q>(fw, p, kb + q0, H, end_y, A, B, wy, o);
+        if (c0 + c < w) {
+            const int32_t v = v_lo + i0 + q0;
+            float *dst = out + ((int64_t)k * h + v) * w + c0;  // uniform over the wave
+            if (v + SP_Q <= v_hi) {
 #pragma unroll
-            for (int r = 0; r < SPC_NL; ++r) ring[(hi + rg + SPC_G * r) & (SPC_RING - 1)][c] = nv[r];
+                for (int r = 0; r < SP_Q; ++r, dst += w) dst[c] = o[r];
+            } else {
+#pragma unroll
+                for (int r = 0; r < SP_Q; ++r, dst += w)
+                    if (v + r < v_hi) dst[c] = o[r];
+            }
         }
     }
 }
@@ -357,12 +352,15 @@ extern "C" int reduce_shift_spline(const float *in, float *out, int32_t W, int32
     if (ws_bytes < need)
         return fail(REDUCE_ERR_WORKSPACE, "reduce_shift_spline: workspace needs " + std::to_string(need) + " bytes");
     hipStream_t s = as_stream(stream);
-    float *R = static_cast<float *>(ws);
     ProfScope prof("shift_spline", s);
-    hipLaunchKernelGGL(spline_rows, dim3((unsigned)ceil_div(w, SP_U), (unsigned)H, (unsigned)N), dim3(SP_N), 0, s, in,
-                       R, W, H, offs, x0, w, wp);
-    hipLaunchKernelGGL(spline_cols,
-                       dim3((unsigned)ceil_div(w, SPC_C), (unsigned)ceil_div(h, SPC_V * SPC_NT), (unsigned)N),
-                       dim3(SPC_C * SPC_G), 0, s, R, out, H, offs, y0, w, wp, h);
+    // one walk down the whole strip where the strips fill the chip (four workgroups per compute
+    // unit); with fewer, walks are cut, each cut forming one more batch of row splines
+    const int32_t n_strip = (int32_t)ceil_div(w, SP_C), tiles = (int32_t)ceil_div(h, SP_V);
+    const int64_t cuts = std::min<int64_t>(tiles, ceil_div(1024, (int64_t)n_strip * N));
+    const int32_t n_tile = (int32_t)ceil_div(tiles, cuts), n_seg = (int32_t)ceil_div(tiles, n_tile);
+    const int64_t grid = (int64_t)n_strip * n_seg * N;
+    if (grid > INT32_MAX) return fail(REDUCE_ERR_UNSUPPORTED, "reduce_shift_spline: too many strips");
+    hipLaunchKernelGGL(spline_shift, dim3((unsigned)grid), dim3(SP_THREADS), 0, s, in, out, W, H, offs, x0, y0, w, h,
+                       n_strip, n_seg, n_tile);
     return check_launch("reduce_shift_spline");
 }
