@@ -82,7 +82,7 @@ struct StackDev {
     reduce_offset_t *offsets;
     int64_t *n_rej;
     // sizes and parameters
-    int32_t W, H, N, ref, R, max_iters, integer_mode, cal_vec, K;
+    int32_t W, H, N, ref, R, max_iters, integer_mode, K;
     float ksigma;
     // workspace
     float *cal;           // [N][H][W]
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(CAL_BLOCK) void batch_cal(BatchArgs a, int32_t firs
     const Item it = a.items[first + blockIdx.x];
     const StackDev &s = a.stacks[it.stack];
     const int64_t i = (int64_t)it.a * CAL_BLOCK + threadIdx.x;
-    if (s.cal_vec)
+    if (s.W >= CAL_VEC)
         calibrate_group8(s.raw, s.rrp, s.rfp, s.bias, s.dark, s.flat, s.crp, s.cal, s.W, s.H, s.N, i);
     else
         calibrate_pixel(s.raw, s.rrp, s.rfp, s.bias, s.dark, s.flat, s.crp, s.cal, s.W, s.H, s.N, i);
@@ -515,14 +515,6 @@ static bool spectral(const reduce_stack_t &s)
                                                               spectral_ws(s.W, s.H, s.N - 1, s.radius, SPEC_ROUND_BYTES) != 0));
 }
 
-// Dark subtraction takes 8-pixel groups when rows, pitches and pointers allow it.
-static bool cal_vec_ok(const reduce_stack_t &s)
-{
-    const auto a16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-    return s.W % CAL_VEC == 0 && s.raw_row_pitch % CAL_VEC == 0 && s.raw_frame_pitch % CAL_VEC == 0 &&
-           s.cal_row_pitch % 4 == 0 && a16(s.raw) && a16(s.dark) && a16(s.flat) && (!s.bias || a16(s.bias));
-}
-
 static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
 {
     BatchLayout L;
@@ -559,7 +551,7 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
         off += al(sizeof(float) * 2 * s.N);
         sl.rect = off;
         off += 256;
-        sl.count[IT_CAL] = (int32_t)ceil_div(cal_vec_ok(s) ? fp / CAL_VEC : fp, CAL_BLOCK);
+        sl.count[IT_CAL] = (int32_t)ceil_div(s.W >= CAL_VEC ? cal_groups(s.W) * s.H : fp, CAL_BLOCK);
         sl.count[IT_MEANPART] = ndir > 0 ? n_mean_parts : 0;
         sl.count[IT_MEANFINAL] = ndir > 0 ? 1 : 0;
         sl.count[IT_SCORE] = p.K != 0 ? ndir * p.wg_per_frame : 0;
@@ -687,7 +679,6 @@ static int build_descriptors(const reduce_stack_t *stacks, int32_t n, void *ws, 
         d.R = st.radius;
         d.max_iters = st.max_iters;
         d.integer_mode = st.integer_mode ? 1 : 0;
-        d.cal_vec = cal_vec_ok(st) ? 1 : 0;
         d.K = sl.plan.K;
         d.ksigma = st.ksigma;
         d.cal = reinterpret_cast<float *>(base + sl.cal);

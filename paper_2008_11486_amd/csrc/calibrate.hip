@@ -1,10 +1,13 @@
 // Bias and dark subtraction and flat division of a stack of uint16 frames (Section
 // 2.1/2.2).
 //
-// Streaming kernel: each thread owns 8 consecutive pixels of one row, loads the
+// Streaming kernel, bound by HBM: each thread owns 8 consecutive pixels of one row, loads the
 // dark and flat values for them once (2 x 32 B), then walks the N frames with one
 // 16 B uint16 load and two 16 B float stores per frame.  Bytes per input pixel:
-// 2 (raw) + 4 (out) + 8/N (dark, flat).
+// 2 (raw) + 4 (out) + 8/N (dark, flat).  Rows of any pitch and start take these loads (a
+// region of interest cut from frames 50 pixels wider ran pixel by pixel before: 16 of
+// 6144x6160 with bias 1.07 ms, now 0.81; 0.83 at the copy rate); rows of fewer than 8 pixels go pixel by
+// pixel.
 #include "calibrate_core.h"
 #include "common.h"
 
@@ -28,8 +31,6 @@ __global__ __launch_bounds__(CAL_BLOCK) void calibrate_scalar(
                     (int64_t)blockIdx.x * CAL_BLOCK + threadIdx.x);
 }
 
-static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 }  // namespace rd
 
 using namespace rd;
@@ -43,12 +44,9 @@ extern "C" int reduce_calibrate(const uint16_t *raw, int64_t raw_row_pitch, int6
     if (raw_row_pitch < W || raw_frame_pitch < raw_row_pitch * (int64_t)(H - 1) + W || cal_row_pitch < W)
         return fail(REDUCE_ERR_SHAPE, "reduce_calibrate: pitch smaller than the frame");
     hipStream_t s = as_stream(stream);
-    const bool vec = (W % CAL_VEC == 0) && (raw_row_pitch % CAL_VEC == 0) && (raw_frame_pitch % CAL_VEC == 0) &&
-                     (cal_row_pitch % 4 == 0) && aligned16(raw) && aligned16(dark) && aligned16(flat) &&
-                     aligned16(out) && (!bias || aligned16(bias));
     ProfScope prof("calibrate", s);
-    if (vec) {
-        const int64_t groups = (int64_t)(W / CAL_VEC) * H;
+    if (W >= CAL_VEC) {
+        const int64_t groups = cal_groups(W) * H;
         hipLaunchKernelGGL(calibrate_vec8, dim3((unsigned)ceil_div(groups, CAL_BLOCK)), dim3(CAL_BLOCK), 0, s,
                            raw, raw_row_pitch, raw_frame_pitch, bias, dark, flat, cal_row_pitch, out, W, H, N);
     } else {
