@@ -144,12 +144,12 @@ __global__ __launch_bounds__(BATCH_THREADS) void batch_score(BatchArgs a, int32_
     score_tile<K>(s.sa, it.a, smem);
 }
 
-__global__ __launch_bounds__(SMALL_COLS) void batch_score_small(BatchArgs a, int32_t first)
+__global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void batch_score_small(BatchArgs a, int32_t first)
 {
-    __shared__ __align__(16) float fl[SMALL_LDS_FLOATS];
+    __shared__ double red[SMALL_LDS_DOUBLES];
     const Item it = a.items[first + blockIdx.x];
     const StackDev &s = a.stacks[it.stack];
-    small_dispatch(s.sa.D, [&](auto Dc) { score_small_tile<decltype(Dc)::value>(s.sa, it.a, fl); });
+    small_dispatch(s.sa.D, [&](auto Dc) { score_small_tile<decltype(Dc)::value>(s.sa, it.a, red); });
 }
 
 __global__ __launch_bounds__(64 * SUM_WAVES) void batch_sum(BatchArgs a, int32_t first)
@@ -766,7 +766,7 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
         }
     }
     if (L.count[IT_SSCORE] > 0)
-        hipLaunchKernelGGL(batch_score_small, dim3(L.count[IT_SSCORE]), dim3(SMALL_COLS), 0, s, a,
+        hipLaunchKernelGGL(batch_score_small, dim3(L.count[IT_SSCORE]), dim3(SMALL_THREADS), 0, s, a,
                            L.first[IT_SSCORE]);
     if (L.count[IT_SUM] > 0)
         hipLaunchKernelGGL(batch_sum, dim3(L.count[IT_SUM]), dim3(64 * SUM_WAVES), 0, s, a, L.first[IT_SUM]);

@@ -114,7 +114,7 @@ bool reg_plan_from_shape(int32_t W, int32_t H, int32_t R, int32_t Rmax, const Re
 
 bool reg_plan_small(int32_t W, int32_t H, int32_t R, int32_t Rmax, RegPlan *out)
 {
-    constexpr int32_t COLS = 256, CH = 15, ROWS = 240;  // the device constants SMALL_COLS, SMALL_CH, SMALL_ROWS
+    constexpr int32_t COLS = 256, CH = 15, ROWS = 240;  // columns and most rows of a tile (SMALL_COLS, SMALL_ROWS); rows in steps of CH
     RegPlan p{};
     p.D = 2 * R + 1;
     if (p.D > 5) return false;

@@ -115,10 +115,10 @@ ScoreArgs make_score_args(const RegPlan &p, const float *ref, const float *frame
 }
 
 template <int D>
-__global__ __launch_bounds__(SMALL_COLS) void score_small(ScoreArgs a)
+__global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void score_small(ScoreArgs a)
 {
-    __shared__ __align__(16) float fl[SMALL_LDS_FLOATS];
-    score_small_tile<D>(a, (int32_t)blockIdx.x, fl);
+    __shared__ double red[SMALL_LDS_DOUBLES];
+    score_small_tile<D>(a, (int32_t)blockIdx.x, red);
 }
 
 template <int K>
@@ -135,9 +135,9 @@ static void launch_score_small(const ScoreArgs &a, const RegPlan &p, hipStream_t
     // workgroups for this call's template (at most the plan's, which is sized for the largest)
     const dim3 grid((unsigned)((int64_t)a.n_tiles * a.N));
     switch (p.D) {
-    case 1: hipLaunchKernelGGL(score_small<1>, grid, dim3(SMALL_COLS), 0, s, a); break;
-    case 3: hipLaunchKernelGGL(score_small<3>, grid, dim3(SMALL_COLS), 0, s, a); break;
-    default: hipLaunchKernelGGL(score_small<5>, grid, dim3(SMALL_COLS), 0, s, a); break;
+    case 1: hipLaunchKernelGGL(score_small<1>, grid, dim3(SMALL_THREADS), 0, s, a); break;
+    case 3: hipLaunchKernelGGL(score_small<3>, grid, dim3(SMALL_THREADS), 0, s, a); break;
+    default: hipLaunchKernelGGL(score_small<5>, grid, dim3(SMALL_THREADS), 0, s, a); break;
     }
 }
 

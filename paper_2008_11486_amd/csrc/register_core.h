@@ -273,134 +273,183 @@ __device__ __forceinline__ void score_tile(const ScoreArgs &a, int32_t lid, unsi
 }
 
 // ---- small windows (side D <= 5) ------------------------------------------------------------
-// A tile is BR template rows (the plan's, a multiple of SMALL_CH of at most SMALL_ROWS)
-// x SMALL_COLS template columns for one workgroup of
-// SMALL_COLS threads; thread t owns template column SMALL_COLS * colblock + t and walks down
-// the tile with all D x D candidate sums in registers.  The frame rows a template row needs
-// (D of them, one per window row) slide down with it in a register ring of D rows, converted
-// to FP64 once; the newest row of the ring comes from LDS, where the workgroup stages the
-// frame in chunks of SMALL_CH rows x SMALL_FC columns, double-buffered: the loads of the next
-// chunk (and its template values) are issued before the current chunk is computed, so one
-// barrier per chunk is the only wait.  At the end each sum is reduced over the wave with a
-// fixed butterfly and over the waves in wave order, and written as the tile's partial in the
-// layout of the general kernel.
-constexpr int SMALL_COLS = 256;                       // template columns per tile, one per thread
-constexpr int SMALL_CH = 15;                          // template rows per chunk (a multiple of every D)
-constexpr int SMALL_ROWS = 16 * SMALL_CH;             // most template rows per tile
-constexpr int SMALL_FC = SMALL_COLS + 4;              // frame columns per staged row (>= SMALL_COLS + D - 1)
-constexpr int SMALL_LDS_FLOATS = 2 * SMALL_CH * SMALL_FC + SMALL_COLS;  // both chunk buffers, one spare slot per thread
+// A tile is BR template rows (the plan's, at most SMALL_ROWS) x SMALL_COLS template columns for
+// one workgroup of SMALL_THREADS threads; each of its waves takes a quarter of the rows and
+// all the columns, four adjacent ones per lane, and walks down its rows with the D x D sums in
+// registers.  The D + 3 frame values of the D frame rows a template row needs slide down
+// with it in a register ring, converted to FP64 once; a row's new values come straight from
+// global memory, as 16-byte loads at element alignment (neighbouring lanes share all but
+// four of them, from L1), SMALL_AHEAD rows before they are used.  At the end each sum is
+// reduced over the wave with a fixed butterfly and over the waves in wave order, and written
+// as the tile's partial in the layout of the general kernel.
+//
+// Bound by HBM (4 bytes per frame pixel) and, for D = 5, FP64 issue (25 FMA and 3
+// conversions per pixel).  With one column per lane and the frame staged in LDS chunks (5
+// conversions and 5 LDS reads per pixel, a barrier per 15 rows) D = 5 took 450 us for 16
+// frames of 4096x4096 and D = 3 739 for 15 of 6144x6160; now 360 and 493.
+// The order of the tiles: with the slots of a tile one after the other D = 3 takes 493 us
+// for 15 of 6144x6160 and 736 frame by frame (the reference is read once, not with every frame);
+// D = 5 gains nothing (399 and 404 us, 16 of 4608x4096) and loses where frames lie a power
+// of two apart (449 and 380, 16 of 4096x4096), so it goes frame by frame.
+constexpr int SMALL_VEC = 4;                          // template columns per lane
+constexpr int SMALL_COLS = 64 * SMALL_VEC;            // template columns per tile
+constexpr int SMALL_THREADS = 256;
+constexpr int SMALL_ROWS = 240;                       // most template rows per tile
 constexpr int SMALL_D_MAX = 5;
-static_assert(SMALL_CH % 15 == 0, "chunk rows must be a multiple of 1, 3 and 5");
-static_assert(4 * SMALL_CH <= SMALL_COLS && SMALL_FC - SMALL_COLS == 4, "extra staged columns");
-static_assert(SMALL_LDS_FLOATS * 4 >= 8 * (SMALL_COLS / 64) * SMALL_D_MAX * SMALL_D_MAX, "reduction scratch");
+constexpr int SMALL_LDS_DOUBLES = (SMALL_THREADS / 64) * SMALL_D_MAX * SMALL_D_MAX;
+
+typedef float reg_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float reg_f2 __attribute__((ext_vector_type(2), aligned(4)));
+
+// n consecutive floats from row[x] on, as vectors
+template <int n>
+__device__ __forceinline__ void load_floats(const float *__restrict__ row, int32_t x, float (&v)[n])
+{
+#pragma unroll
+    for (int i = 0; i + 4 <= n; i += 4) {
+        const reg_f4 u = *reinterpret_cast<const reg_f4 *>(row + x + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i + e] = u[e];
+    }
+    if constexpr (n % 4 != 0) {
+        static_assert(n % 4 == 2, "4, 6 or 8 values");
+        const reg_f2 u = *reinterpret_cast<const reg_f2 *>(row + x + n - 2);
+        v[n - 2] = u[0];
+        v[n - 1] = u[1];
+    }
+}
+
+// Workgroups go round the XCDs: each XCD takes every eighth tile, all slots of it one after
+// the other, so a tile's reference comes from its L2 after the first slot while the XCDs
+// read neighbouring columns.
+__device__ __forceinline__ void small_shared_order(int32_t lid, int32_t n_tiles, int32_t N, int32_t *tile, int32_t *k)
+{
+    const int32_t whole = n_tiles & ~7;
+    const bool in = lid < whole * N;
+    const int32_t i = in ? lid >> 3 : lid - whole * N;
+    const int32_t q = i / N;
+    *k = i - q * N;
+    *tile = in ? q * 8 + (lid & 7) : whole + q;
+}
 
 template <int D>
-__device__ __forceinline__ void score_small_tile(const ScoreArgs &a, int32_t lid, float *__restrict__ fl)
+__device__ __forceinline__ void score_small_tile(const ScoreArgs &a, int32_t lid, double *__restrict__ red)
 {
+    constexpr int V = SMALL_VEC, NF = V + D - 1;      // frame values of a lane's row
+    constexpr int G = D == 1 ? 4 : D == 3 ? 6 : 5;    // rows per turn of the ring (a multiple of D) and rows ahead
     const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
-    const int32_t tile = lid % a.n_tiles, k = lid / a.n_tiles;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    int32_t tile, k;
+    if constexpr (D < SMALL_D_MAX) {
+        small_shared_order(lid, a.n_tiles, a.N, &tile, &k);
+    } else {
+        k = lid / a.n_tiles;
+        tile = lid - k * a.n_tiles;
+    }
     const int32_t kf = a.map ? a.map[k] : k + (k >= a.skip ? 1 : 0);
     if (kf < 0) return;  // an idle slot: the whole workgroup leaves before any barrier
     const int32_t ci = a.map ? kf : k;
     const int32_t strip = tile / a.n_xchunks, colb = tile - strip * a.n_xchunks;
-    const int32_t x = colb * SMALL_COLS + t;
-    const bool col_ok = x < a.tw;
-    const int32_t y0 = strip * a.BR, rows = min(y0 + a.BR, a.th) - y0;
-    const int nch = (rows + SMALL_CH - 1) / SMALL_CH;
-    const int32_t cx = a.centers ? a.centers[2 * ci] : 0, cy = a.centers ? a.centers[2 * ci + 1] : 0;
+    const int32_t cx = a.centers ? __builtin_amdgcn_readfirstlane(a.centers[2 * ci]) : 0;
+    const int32_t cy = a.centers ? __builtin_amdgcn_readfirstlane(a.centers[2 * ci + 1]) : 0;
     const float *f = a.frames + (int64_t)kf * a.W * a.H;
     const double mean = *a.mean;
-    // staged column c is frame column fx0 + c, clamped into the frame (an offset beyond
-    // +-Rmax is discarded when the tiles are summed, so any in-frame value will do); frame
-    // row of window row 0 at template row y0 is fy0; chunk ch holds frame rows
-    // fy0 + D - 1 + ch * SMALL_CH + [0, SMALL_CH), clamped likewise
-    const int32_t fx0 = a.tx0 + colb * SMALL_COLS + cx - a.R;
-    const int32_t fy0 = a.ty0 + y0 + cy - a.R;
-    // 32-bit element offsets (a frame holds fewer than 2^31 pixels)
-    const uint32_t W = (uint32_t)a.W;
-    const float *tcol = a.ref + a.tx0 + (col_ok ? x : 0);
-    const int32_t ty_last = a.ty0 + y0 + rows - 1;
-
-    // staging: thread t loads column t of every chunk row, and threads t < 4 * SMALL_CH also
-    // one of the SMALL_FC - SMALL_COLS extra columns (row t / 4, column SMALL_COLS + t % 4);
-    // row offsets are uniform over the workgroup
-    const int32_t gxm = min(max(fx0 + t, 0), a.W - 1);
-    const bool has_x = t < 4 * SMALL_CH;
-    const int xr = has_x ? t >> 2 : 0, xc = SMALL_COLS + (t & 3);
-    const int32_t gxx = min(max(fx0 + xc, 0), a.W - 1);
-    float pf[SMALL_CH], pfx;
-    auto load_chunk = [&](int ch) {
-        const int32_t gy0 = fy0 + D - 1 + ch * SMALL_CH;
-#pragma unroll
-        for (int r = 0; r < SMALL_CH; ++r) pf[r] = f[(uint32_t)min(max(gy0 + r, 0), a.H - 1) * W + (uint32_t)gxm];
-        pfx = f[(uint32_t)min(max(gy0 + xr, 0), a.H - 1) * W + (uint32_t)gxx];
-    };
-    // branch-free: a thread without an extra value writes it to its spare slot
-    const int xslot = has_x ? xr * SMALL_FC + xc : 2 * SMALL_CH * SMALL_FC + t;
-    auto store_chunk = [&](int buf) {
-        float *dst = fl + buf * (SMALL_CH * SMALL_FC);
-#pragma unroll
-        for (int r = 0; r < SMALL_CH; ++r) dst[r * SMALL_FC + t] = pf[r];
-        fl[has_x ? buf * (SMALL_CH * SMALL_FC) + xslot : xslot] = pfx;
-    };
-    // template value of row y0 + yl of this thread's column (rows past the tile repeat its last)
-    auto tmpl_at = [&](int32_t yl) { return tcol[(uint32_t)min(a.ty0 + y0 + yl, ty_last) * W]; };
-
-    load_chunk(0);  // in flight together with the ring's first rows and the first template values
-    // the ring starts with frame rows fy0 .. fy0 + D - 2 (window rows 0 .. D-2 of template row 0)
-    double ring[D][D];
-#pragma unroll
-    for (int i = 0; i + 1 < D; ++i) {
-        const float *row = f + (uint32_t)min(max(fy0 + i, 0), a.H - 1) * W;
-#pragma unroll
-        for (int j = 0; j < D; ++j) ring[i][j] = (double)row[min(max(fx0 + t + j, 0), a.W - 1)];
-    }
+    // the wave's rows of the tile, of template rows y0 .. y0 + rows - 1
+    const int32_t yt = strip * a.BR, tile_rows = min(yt + a.BR, a.th) - yt;
+    const int32_t rpw = (tile_rows + SMALL_THREADS / 64 - 1) / (SMALL_THREADS / 64);
+    const int32_t y0 = yt + wave * rpw, rows = min(rpw, tile_rows - wave * rpw);
+    // the frame values of template columns x .. x + V - 1 are those of frame columns x + fx .. x + fx + NF - 1
+    // of frame rows fy + (template row - y0) + 0 .. D - 1, clamped into the frame (an offset
+    // beyond +-Rmax is discarded when the tiles are summed, so any in-frame value will do)
+    const int32_t fx = a.tx0 + cx - a.R, fy = a.ty0 + y0 + cy - a.R;
     double acc[D * D];
 #pragma unroll
     for (int q = 0; q < D * D; ++q) acc[q] = 0.0;
-    const double colw = col_ok ? 1.0 : 0.0;
-
-    // template values one chunk ahead: tv[p] holds row ch * SMALL_CH + p while chunk ch is
-    // computed and is refilled with row (ch + 1) * SMALL_CH + p right after its use
-    float tv[SMALL_CH];
+    auto walk = [&](auto inside) {
+        constexpr bool IN = decltype(inside)::value;
+        // A lane that would reach past the template takes its last V columns and leaves out
+        // those that are another lane's, so nothing outside the template's reach is weighed, not
+        // even by zero; a template narrower than V columns has one column to a lane.
+        const bool narrow = !IN && a.tw < V;
+        const int32_t x0 = narrow ? lane : colb * SMALL_COLS + V * lane;
+        const int32_t x = min(x0, a.tw - (narrow ? 1 : V));
+        auto frame_row = [&](int32_t i, float (&v)[NF]) {
+            const float *row = f + (int64_t)min(max(fy + i, 0), a.H - 1) * a.W;
+            if constexpr (IN) {
+                load_floats<NF>(row, x + fx, v);
+            } else {
 #pragma unroll
-    for (int p = 0; p < SMALL_CH; ++p) tv[p] = tmpl_at(p);
-    store_chunk(0);
-    __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) {
-        // the loads and stores of the next chunk are unconditional (rows are clamped into
-        // the frame; after the last chunk they fill the idle buffer, which is not read), so
-        // the loop body stays one block and the compiler keeps the computation in place
-        load_chunk(ch + 1);
-        const float *src = fl + (ch & 1) * (SMALL_CH * SMALL_FC) + t;
-        // the staged row of template row p + 1 is read while row p is computed
-        float nxt[D];
-#pragma unroll
-        for (int j = 0; j < D; ++j) nxt[j] = src[j];
-#pragma unroll
-        for (int p = 0; p < SMALL_CH; ++p) {
-            // frame row of window row D-1 for template row ch * SMALL_CH + p enters the ring
-#pragma unroll
-            for (int j = 0; j < D; ++j) ring[(p + D - 1) % D][j] = (double)nxt[j];
-            if (p + 1 < SMALL_CH) {
-#pragma unroll
-                for (int j = 0; j < D; ++j) nxt[j] = src[(p + 1) * SMALL_FC + j];
+                for (int e = 0; e < NF; ++e) v[e] = row[min(max(x + fx + e, 0), a.W - 1)];
             }
-            // zero weight for columns past the template and rows past the tile
-            const double rv = ((double)tv[p] - mean) * (ch * SMALL_CH + p < rows ? colw : 0.0);
-            tv[p] = tmpl_at((ch + 1) * SMALL_CH + p);
+        };
+        auto tmpl_row = [&](int32_t i, float (&v)[V]) {  // rows past the wave's repeat its last
+            const float *row = a.ref + (int64_t)(a.ty0 + y0 + min(i, rows - 1)) * a.W;
+            if constexpr (IN) {
+                load_floats<V>(row, a.tx0 + x, v);
+            } else {
 #pragma unroll
-            for (int i = 0; i < D; ++i)
+                for (int e = 0; e < V; ++e) v[e] = row[min(a.tx0 + x + e, a.W - 1)];
+            }
+        };
+        bool ok[V];  // the lane's own columns
 #pragma unroll
-                for (int j = 0; j < D; ++j) acc[i * D + j] = fma(rv, ring[(p + i) % D][j], acc[i * D + j]);
-            __builtin_amdgcn_sched_barrier(0);  // one row at a time: bounds the registers in flight
+        for (int e = 0; e < V; ++e) ok[e] = x + e >= x0;
+        double ring[D][NF];
+#pragma unroll
+        for (int i = 0; i + 1 < D; ++i) {
+            float v[NF];
+            frame_row(i, v);
+#pragma unroll
+            for (int e = 0; e < NF; ++e) ring[i][e] = (double)v[e];
         }
-        store_chunk((ch + 1) & 1);
-        __syncthreads();
+        // row i's newest frame row and its template values, loaded A rows ahead
+        constexpr int A = IN ? G : 1;
+        float pf[A][NF], pt[A][V];
+#pragma unroll
+        for (int p = 0; p < A; ++p) {
+            frame_row(D - 1 + p, pf[p]);
+            tmpl_row(p, pt[p]);
+            __builtin_amdgcn_sched_barrier(0);  // in the loop's order, or its first wait is for all of them
+        }
+        // template row i0 + p; then the row A further on is loaded in its place
+        auto step = [&](int32_t i0, int p, bool ahead) {
+#pragma unroll
+            for (int e = 0; e < NF; ++e) ring[(p + D - 1) % D][e] = (double)pf[p % A][e];
+            double r[V];
+#pragma unroll
+            for (int e = 0; e < V; ++e) r[e] = ok[e] ? (double)pt[p % A][e] - mean : 0.0;
+            if (ahead) {
+                frame_row(i0 + A + p + D - 1, pf[p % A]);
+                tmpl_row(i0 + A + p, pt[p % A]);
+            }
+#pragma unroll
+            for (int e = 0; e < V; ++e) {  // D * D independent sums between two uses of one
+                if (e > 0 && narrow) break;
+#pragma unroll
+                for (int i = 0; i < D; ++i)
+#pragma unroll
+                    for (int j = 0; j < D; ++j)
+                        acc[i * D + j] = fma(r[e], ring[(p + i) % D][j + e], acc[i * D + j]);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // one row at a time: bounds the registers in flight
+        };
+        int32_t i0 = 0;
+        for (; i0 + G <= rows; i0 += G) {
+#pragma unroll
+            for (int p = 0; p < G; ++p) step(i0, p, true);
+        }
+#pragma unroll
+        for (int p = 0; p + 1 < G; ++p)  // the remainder: what is loaded ahead is all it needs
+            if (i0 + p < rows) step(i0, p, A < G);
+    };
+    if (rows > 0) {
+        // whether all candidates lie inside the frame's columns (uniform): no load needs a clamp
+        if (a.tw >= V && fx >= 0 && fx + a.tw + D - 1 <= a.W)
+            walk(std::true_type{});
+        else
+            walk(std::false_type{});
     }
     // wave butterflies, then the waves in order
-    double *red = reinterpret_cast<double *>(fl);
 #pragma unroll
     for (int q = 0; q < D * D; ++q) {
         double v = acc[q];
@@ -412,10 +461,9 @@ __device__ __forceinline__ void score_small_tile(const ScoreArgs &a, int32_t lid
     if (t < D * D) {
         double v = red[t];
 #pragma unroll
-        for (int w = 1; w < SMALL_COLS / 64; ++w) v += red[w * (D * D) + t];
+        for (int w = 1; w < SMALL_THREADS / 64; ++w) v += red[w * (D * D) + t];
         a.partial[((int64_t)k * a.n_tiles + tile) * (int64_t)(D * D) + t] = v;
     }
-    __syncthreads();  // LDS is reused by the caller's next item
 }
 
 template <typename F>
