@@ -236,101 +236,192 @@ __global__ void pack_weights(const float *__restrict__ params, uint16_t *__restr
 }
 
 // ---- convolution forward ---------------------------------------------------------------------
-// One wave: 16 consecutive output pixels of a row x 32 channels per MFMA pair; results go
-// through LDS for 16-byte stores.  Layer 1 (CIN = 2): the workgroup's four waves cover 64
-// pixels, and the three input rows of both channels they need are staged in LDS with
-// coalesced loads first.  Layers 2-4 (CIN = 32): a wave keeps the weights of all nine taps
-// in registers and covers NG groups of 64 pixels (one group per pass of the workgroup), so
-// the weights are read once per NG * 64 pixels.  The accumulation order (taps in order,
-// one MFMA per tap and 16 channels) is the same in every case.
-constexpr int CONV_NG = 4;  // 64-pixel groups per workgroup of the 32-channel layers
+// The weights are the matrix instruction's first operand and 16 consecutive output pixels of a
+// row the second, so a lane ends up with one pixel; the weight rows are dealt so that its
+// 2 x 4 values are eight consecutive channels, one 16-byte store, and a wave writes 1 KB in
+// one piece without a trip through LDS.  Accumulation order: taps in order, one instruction
+// per tap and 16 channels.
+//
+// Channel of row r of the first (and, + 4, of the second) weight tile, so that the lane with
+// rows 4 g .. 4 g + 3 of both holds channels 8 g .. 8 g + 7.
+__device__ __forceinline__ int tile_channel(int r) { return 8 * (r >> 2) + (r & 3); }
 
-template <int CIN>
-__global__ __launch_bounds__(256) void conv_fwd(const uint16_t *__restrict__ x, const uint16_t *__restrict__ ref,
-                                                int64_t ref_stride, const uint16_t *__restrict__ img, int32_t H,
-                                                int32_t W, const uint16_t *__restrict__ wf,
-                                                const float *__restrict__ bias, uint16_t *__restrict__ y)
+__device__ __forceinline__ uint4 pack8(const float (&v)[8])
 {
-    constexpr int NG = CIN == 2 ? 1 : CONV_NG;
-    constexpr int XC = 2 * 64 + 4;  // staged input columns (129 used)
-    __shared__ __align__(16) uint16_t tile[4][16 * CNN_CH];
-    __shared__ uint16_t in2[CIN == 2 ? 3 * 2 * XC : 1];
+    uint32_t w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)f2bf(v[2 * j]) | ((uint32_t)f2bf(v[2 * j + 1]) << 16);
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// bias, ReLU, bfloat16
+__device__ __forceinline__ uint4 relu8(const f32x4 &acc0, const f32x4 &acc1, const float (&b)[8])
+{
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[j] = fmaxf(acc0[j] + b[j], 0.0f);
+        v[4 + j] = fmaxf(acc1[j] + b[4 + j], 0.0f);
+    }
+    return pack8(v);
+}
+
+// One row of a [H][W][32] plane as a buffer: reads past either end give zero and writes there
+// are dropped, so the loops over rows have no branches, whose joins would wait for
+// every load in flight.  A row that does not exist is an empty buffer.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_row(const uint16_t *plane, int32_t row, int32_t H, int32_t W)
+{
+    const bool in = row >= 0 && row < H;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(plane) + (int64_t)min(max(row, 0), H - 1) * W * CNN_CH,
+                                             0, in ? W * (CNN_CH * 2) : 0, 0x00027000);
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ bf16x8 row_load8(__amdgpu_buffer_rsrc_t row, uint32_t off)
+{
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(row, off, 0, 0));
+}
+
+__device__ __forceinline__ void row_store8(__amdgpu_buffer_rsrc_t row, uint32_t off, uint4 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), row, off, 0, 0);
+}
+
+constexpr uint32_t ROW_NONE = 0x80000000u;  // an offset past the end of every row
+
+constexpr int CONV_ROWS = 8;  // output rows per workgroup; its four waves take 16 columns each
+
+// Layer 1 (two input channels): the input rows of the tile are staged in LDS with both
+// channels in one word, so a tap is one word and the pixel operand (18 of 32 products, the
+// rest zeros) four LDS reads.  Bound by the stores; 16 pairs of 1024x1024 took 140 us with one
+// row per workgroup and the transposed result sent through LDS, now 67 (268 MB written).
+__global__ __launch_bounds__(256) void conv_first(const uint16_t *__restrict__ ref, int64_t ref_stride,
+                                                  const uint16_t *__restrict__ img, int32_t H, int32_t W,
+                                                  const uint16_t *__restrict__ wf, const float *__restrict__ bias,
+                                                  uint16_t *__restrict__ y)
+{
+    constexpr int XC = 2 * 64 + 1;        // staged input columns
+    constexpr int XR = 2 * CONV_ROWS + 1;  // and rows
+    __shared__ uint32_t in2[XR * XC + 3];
     const int32_t Ho = (H + 1) / 2, Wo = (W + 1) / 2;
-    const int32_t b = blockIdx.z, oy = blockIdx.y;
+    const int32_t b = blockIdx.z, oy0 = blockIdx.y * CONV_ROWS, gx0 = blockIdx.x * 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 15, kg = lane >> 4;
-
-    bf16x8 wb0[CIN == 2 ? 1 : 9], wb1[CIN == 2 ? 1 : 9];
+    const bf16x8 w0 = load8(wf + tile_channel(m) * 32 + kg * 8);
+    const bf16x8 w1 = load8(wf + (tile_channel(m) + 4) * 32 + kg * 8);
+    float bv[8];
 #pragma unroll
-    for (int t = 0; t < (CIN == 2 ? 1 : 9); ++t) {
-        wb0[t] = load8(wf + (t * 32 + m) * 32 + kg * 8);
-        wb1[t] = load8(wf + (t * 32 + 16 + m) * 32 + kg * 8);
+    for (int j = 0; j < 8; ++j) bv[j] = bias[8 * kg + j];
+    const uint16_t *rb = ref + (int64_t)b * ref_stride, *ib = img + (int64_t)b * H * W;
+
+    // input rows 2 oy0 - 1 + r, columns 2 gx0 - 1 + col
+    constexpr int PER = (XR * XC + 255) / 256;
+    uint16_t va[PER], vb[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int e = i * 256 + threadIdx.x, r = e / XC, col = e - r * XC;
+        const int32_t iy = 2 * oy0 + r - 1, ix = 2 * gx0 - 1 + col;
+        const bool in = e < XR * XC && iy >= 0 && iy < H && ix >= 0 && ix < W;
+        const int64_t p = in ? (int64_t)iy * W + ix : 0;
+        va[i] = rb[p];
+        vb[i] = ib[p];
+        if (!in) va[i] = vb[i] = 0;
     }
-    const float bias0 = bias[m], bias1 = bias[16 + m];
-
-    for (int g = 0; g < NG; ++g) {
-        const int32_t gx0 = (blockIdx.x * NG + g) * 64;  // first output pixel of the group
-        if (gx0 >= Wo) break;                            // uniform over the workgroup
-        const int32_t ox0 = gx0 + wave * 16;
-        const int32_t ox = ox0 + m;
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (CIN == 2) {
-            // input rows 2 oy - 1 .. 2 oy + 1, columns 2 gx0 - 1 + c, both channels
-            for (int e = threadIdx.x; e < 3 * 2 * (XC - 3); e += 256) {
-                const int r = e / (2 * (XC - 3)), rem = e - r * 2 * (XC - 3);
-                const int c = rem / (XC - 3), col = rem - c * (XC - 3);
-                const int32_t iy = 2 * oy + r - 1, ix = 2 * gx0 - 1 + col;
-                uint16_t v = 0;
-                if (iy >= 0 && iy < H && ix >= 0 && ix < W) {
-                    const int64_t p = (int64_t)iy * W + ix;
-                    v = c == 0 ? ref[(int64_t)b * ref_stride + p] : img[(int64_t)b * H * W + p];
-                }
-                in2[(r * 2 + c) * XC + col] = v;
-            }
-            __syncthreads();
-            // K = 18 (tap, channel) pairs + zeros
-            uint16_t e8[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int k = kg * 8 + j;
-                uint16_t v = 0;
-                if (k < 18 && ox < Wo) {
-                    const int t = k >> 1, c = k & 1;
-                    v = in2[((t / 3) * 2 + c) * XC + 2 * (ox - gx0) + t % 3];
-                }
-                e8[j] = v;
-            }
-            const uint4 pk = make_uint4(e8[0] | ((uint32_t)e8[1] << 16), e8[2] | ((uint32_t)e8[3] << 16),
-                                        e8[4] | ((uint32_t)e8[5] << 16), e8[6] | ((uint32_t)e8[7] << 16));
-            const bf16x8 a = __builtin_bit_cast(bf16x8, pk);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wb0[0], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wb1[0], acc1, 0, 0, 0);
-        } else {
+    for (int i = 0; i < PER; ++i) {
+        const int e = i * 256 + threadIdx.x;
+        if (e < XR * XC) in2[e] = (uint32_t)va[i] | ((uint32_t)vb[i] << 16);
+    }
+    __syncthreads();
+    const int32_t ox = gx0 + 16 * wave + m;
+    int at[4];  // the lane's taps 4 kg .. 4 kg + 3
 #pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const int32_t iy = 2 * oy + t / 3 - 1, ix = 2 * ox + t % 3 - 1;
-                bf16x8 a = zero8();
-                if (ox < Wo && iy >= 0 && iy < H && ix >= 0 && ix < W)
-                    a = load8(x + (((int64_t)b * H + iy) * W + ix) * CNN_CH + kg * 8);
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wb0[t], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wb1[t], acc1, 0, 0, 0);
-            }
-        }
-        // lane holds pixels 4 kg + j, channel m (tile 0) and 16 + m (tile 1)
+    for (int j = 0; j < 4; ++j) {
+        const int t = min(4 * kg + j, 8);
+        at[j] = (t / 3) * XC + 2 * (16 * wave + m) + t % 3;
+    }
+#pragma unroll
+    for (int r = 0; r < CONV_ROWS; ++r) {
+        const int32_t oy = oy0 + r;
+        uint32_t e[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int px = 4 * kg + j;
-            tile[wave][px * CNN_CH + m] = f2bf(fmaxf(acc0[j] + bias0, 0.0f));
-            tile[wave][px * CNN_CH + 16 + m] = f2bf(fmaxf(acc1[j] + bias1, 0.0f));
+            e[j] = in2[2 * r * XC + at[j]];
+            if (4 * kg + j > 8) e[j] = 0;
         }
-        __syncthreads();
-        const int px = lane >> 2, c8 = (lane & 3) * 8;
-        const int32_t oxs = ox0 + px;
-        if (oxs < Wo) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(&tile[wave][px * CNN_CH + c8]);
-            *reinterpret_cast<uint4 *>(y + (((int64_t)b * Ho + oy) * Wo + oxs) * CNN_CH + c8) = v;
+        const bf16x8 a = __builtin_bit_cast(bf16x8, make_uint4(e[0], e[1], e[2], e[3]));
+        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, a, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, a, acc1, 0, 0, 0);
+        row_store8(plane_row(y + (int64_t)b * Ho * Wo * CNN_CH, oy, Ho, Wo), (uint32_t)ox * 64 + kg * 16,
+                   relu8(acc0, acc1, bv));
+    }
+}
+
+// Layers 2 - 4 (32 input channels): a wave keeps the weights of all nine taps in registers and
+// walks down CONV_ROWS output rows; of the three input rows of an output row it keeps the
+// last for the next and has that one's other two loaded before this one's products.  Bound by
+// memory: the three layers of 16 pairs of 1024x1024 took 170 us a row and four pixel
+// groups per workgroup (nine loads per row, the result through LDS), now 115 (440 MB).
+__global__ __launch_bounds__(256) void conv_next(const uint16_t *__restrict__ x, int32_t H, int32_t W,
+                                                 const uint16_t *__restrict__ wf, const float *__restrict__ bias,
+                                                 uint16_t *__restrict__ y)
+{
+    const int32_t Ho = (H + 1) / 2, Wo = (W + 1) / 2;
+    const int32_t b = blockIdx.z, oy0 = blockIdx.y * CONV_ROWS;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = lane & 15, kg = lane >> 4;
+    const int32_t ox = blockIdx.x * 64 + 16 * wave + m;
+    bf16x8 w0[9], w1[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        w0[t] = load8(wf + (t * 32 + tile_channel(m)) * 32 + kg * 8);
+        w1[t] = load8(wf + (t * 32 + tile_channel(m) + 4) * 32 + kg * 8);
+    }
+    float bv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) bv[j] = bias[8 * kg + j];
+    const uint16_t *xb = x + (int64_t)b * H * W * CNN_CH;
+    uint16_t *yb = y + (int64_t)b * Ho * Wo * CNN_CH;
+    const uint32_t o1 = (uint32_t)ox * 128 + kg * 16;  // column 2 ox; 64 bytes to a pixel
+    const uint32_t o0 = ox > 0 ? o1 - 64 : ROW_NONE;
+    auto load_row = [&](int32_t iy, bf16x8 (&v)[3]) {  // columns 2 ox - 1 .. 2 ox + 1
+        const __amdgpu_buffer_rsrc_t row = plane_row(xb, iy, H, W);
+        v[0] = row_load8(row, o0);
+        v[1] = row_load8(row, o1);
+        v[2] = row_load8(row, o1 + 64);
+    };
+    bf16x8 top[3], mid[3], bot[3];
+    load_row(2 * oy0 - 1, top);
+    load_row(2 * oy0, mid);
+    load_row(2 * oy0 + 1, bot);
+#pragma unroll
+    for (int r = 0; r < CONV_ROWS; ++r) {
+        const int32_t oy = oy0 + r;
+        bf16x8 mid_n[3], bot_n[3];
+        if (r + 1 < CONV_ROWS) {
+            load_row(2 * oy + 2, mid_n);
+            load_row(2 * oy + 3, bot_n);
         }
-        __syncthreads();  // the tiles (and staged rows) are reused by the next group
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const bf16x8 a = t < 3 ? top[t % 3] : t < 6 ? mid[t % 3] : bot[t % 3];
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0[t], a, acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[t], a, acc1, 0, 0, 0);
+        }
+        row_store8(plane_row(yb, oy, Ho, Wo), (uint32_t)ox * 64 + kg * 16, relu8(acc0, acc1, bv));
+        if (r + 1 < CONV_ROWS) {
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                top[kx] = bot[kx];
+                mid[kx] = mid_n[kx];
+                bot[kx] = bot_n[kx];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -692,61 +783,98 @@ __global__ __launch_bounds__(256) void wgrad_reduce(const float *__restrict__ wp
 
 // ---- data gradient -------------------------------------------------------------------------------
 // dX[iy][ix][ci] = sum over the taps whose output pixel exists of dZ[oy][ox][co] W[t][ci][co];
-// the result times the ReLU mask of X is the previous layer's dZ.  A wave takes 16 input
-// pixels of one row with the same x parity (ix = 2 j + px), so all 16 share the valid
-// taps: one ky for even iy, two for odd; likewise kx.
+// the result times the ReLU mask of X is the previous layer's dZ.  A lane takes the 2 x 2 input
+// pixels (2 q, 2 q + 1) x (2 j, 2 j + 1), which need dZ at rows q, q + 1 and columns j, j + 1:
+// four loads for the nine taps, whose weights stay in registers, as operands dealt like the
+// forward's, so the mask is read and the result written in 16-byte pieces, both pixels of a
+// pair by neighbouring instructions.  The wave walks down DG_ROWS row pairs and keeps the lower
+// row of dZ for the next.  Bound by memory: the three layers of 16 pairs of 1024x1024 took 304 us with
+// one parity per wave and a pass through LDS, now 157 (790 MB).
+constexpr int DG_ROWS = 4;
+
 __global__ __launch_bounds__(256) void dgrad(const uint16_t *__restrict__ dz, const uint16_t *__restrict__ wd,
                                              const uint16_t *__restrict__ xin, int32_t H, int32_t W,
                                              uint16_t *__restrict__ dzin)
 {
-    __shared__ __align__(16) uint16_t tile[4][16 * CNN_CH];
     const int32_t Ho = (H + 1) / 2, Wo = (W + 1) / 2;
-    const int32_t b = blockIdx.z;
-    const int32_t iy = blockIdx.y >> 1, px = blockIdx.y & 1;
+    const int32_t b = blockIdx.z, q0 = blockIdx.y * DG_ROWS;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int32_t j0 = (blockIdx.x * 4 + wave) * 16;
     const int m = lane & 15, kg = lane >> 4;
-    const int32_t jm = j0 + m, ixm = 2 * jm + px;
-
-    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-    for (int ky = 0; ky < 3; ++ky) {
-        const int32_t ny = iy + 1 - ky;
-        if (ny < 0 || (ny & 1)) continue;
-        const int32_t oy = ny >> 1;
-        if (oy >= Ho) continue;
-        for (int kx = 0; kx < 3; ++kx) {
-            if ((px + 1 - kx) & 1) continue;
-            const int t = 3 * ky + kx;
-            const int32_t nx = ixm + 1 - kx;  // even by the parity of the tile
-            bf16x8 a = zero8();
-            if (ixm < W && nx >= 0 && (nx >> 1) < Wo)
-                a = load8(dz + (((int64_t)b * Ho + oy) * Wo + (nx >> 1)) * CNN_CH + kg * 8);
-            const bf16x8 b0 = load8(wd + ((int64_t)t * CNN_CH + m) * CNN_CH + kg * 8);
-            const bf16x8 b1 = load8(wd + ((int64_t)t * CNN_CH + 16 + m) * CNN_CH + kg * 8);
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, acc1, 0, 0, 0);
-        }
-    }
-    // lane holds pixels 4 kg + j, input channel m (and 16 + m)
+    const int32_t j = blockIdx.x * 64 + 16 * wave + m;
+    bf16x8 w0[9], w1[9];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int pp = 4 * kg + j;
-        const int32_t ix = 2 * (j0 + pp) + px;
-        float g0 = 0.0f, g1 = 0.0f;
-        if (ix < W) {
-            const uint16_t *xp = xin + (((int64_t)b * H + iy) * W + ix) * CNN_CH;
-            g0 = bf2f(xp[m]) > 0.0f ? acc0[j] : 0.0f;
-            g1 = bf2f(xp[16 + m]) > 0.0f ? acc1[j] : 0.0f;
-        }
-        tile[wave][pp * CNN_CH + m] = f2bf(g0);
-        tile[wave][pp * CNN_CH + 16 + m] = f2bf(g1);
+    for (int t = 0; t < 9; ++t) {
+        w0[t] = load8(wd + ((int64_t)t * CNN_CH + tile_channel(m)) * CNN_CH + kg * 8);
+        w1[t] = load8(wd + ((int64_t)t * CNN_CH + tile_channel(m) + 4) * CNN_CH + kg * 8);
     }
-    __syncthreads();
-    const int pp = lane >> 2, c8 = (lane & 3) * 8;
-    const int32_t ix = 2 * (j0 + pp) + px;
-    if (ix < W) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(&tile[wave][pp * CNN_CH + c8]);
-        *reinterpret_cast<uint4 *>(dzin + (((int64_t)b * H + iy) * W + ix) * CNN_CH + c8) = v;
+    const uint16_t *zb = dz + (int64_t)b * Ho * Wo * CNN_CH;
+    const uint16_t *xb = xin + (int64_t)b * H * W * CNN_CH;
+    uint16_t *gb = dzin + (int64_t)b * H * W * CNN_CH;
+    const uint32_t zo = (uint32_t)j * 64 + kg * 16, xo = (uint32_t)j * 128 + kg * 16;
+    bf16x8 z[2][2], zn[2];  // rows q and q + 1, columns j and j + 1; row q + 2
+    bf16x8 xm[2][2], xn[2][2];
+    auto load_z = [&](int32_t oy, bf16x8 (&v)[2]) {
+        const __amdgpu_buffer_rsrc_t row = plane_row(zb, oy, Ho, Wo);
+        v[0] = row_load8(row, zo);
+        v[1] = row_load8(row, zo + 64);
+    };
+    auto load_x = [&](int32_t q, bf16x8 (&v)[2][2]) {
+#pragma unroll
+        for (int py = 0; py < 2; ++py) {
+            const __amdgpu_buffer_rsrc_t row = plane_row(xb, 2 * q + py, H, W);
+            v[py][0] = row_load8(row, xo);
+            v[py][1] = row_load8(row, xo + 64);
+        }
+    };
+    load_z(q0, z[0]);
+    load_z(q0 + 1, z[1]);
+    load_x(q0, xm);
+#pragma unroll
+    for (int i = 0; i < DG_ROWS; ++i) {
+        const int32_t q = q0 + i;
+        if (i + 1 < DG_ROWS) {
+            load_z(q + 2, zn);
+            load_x(q + 1, xn);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int py = 0; py < 2; ++py) {
+            const __amdgpu_buffer_rsrc_t out = plane_row(gb, 2 * q + py, H, W);
+#pragma unroll
+            for (int px = 0; px < 2; ++px) {
+                f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ky = 0; ky < 3; ++ky) {
+                    if ((py + 1 - ky) & 1) continue;
+                    const int dq = (py + 1 - ky) / 2;  // row q + dq of dZ
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx) {
+                        if ((px + 1 - kx) & 1) continue;
+                        const int dj = (px + 1 - kx) / 2;
+                        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0[3 * ky + kx], z[dq][dj], acc0, 0, 0, 0);
+                        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[3 * ky + kx], z[dq][dj], acc1, 0, 0, 0);
+                    }
+                }
+                const uint4 xw = __builtin_bit_cast(uint4, xm[py][px]);
+                const uint32_t xv[4] = {xw.x, xw.y, xw.z, xw.w};
+                float g[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    g[c] = bf2f((uint16_t)(xv[c / 2] >> (16 * (c & 1)))) > 0.0f ? (c < 4 ? acc0[c & 3] : acc1[c & 3])
+                                                                              : 0.0f;
+                row_store8(out, xo + 64 * px, pack8(g));
+            }
+        }
+        if (i + 1 < DG_ROWS) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                z[0][e] = z[1][e];
+                z[1][e] = zn[e];
+                xm[0][e] = xn[0][e];
+                xm[1][e] = xn[1][e];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -822,13 +950,12 @@ int cnn_forward_launch(const uint16_t *ref, int64_t ref_stride, const uint16_t *
     for (int l = 0; l < 4; ++l) {
         uint16_t *out = reinterpret_cast<uint16_t *>(base + L.act[l]);
         const float *bias = params + cnn_weight_offset(l) + 9 * (l == 0 ? 2 : CNN_CH) * CNN_CH;
-        dim3 grid((unsigned)ceil_div(L.ws[l], 64 * (l == 0 ? 1 : CONV_NG)), (unsigned)L.hs[l], (unsigned)B);
+        const dim3 grid((unsigned)ceil_div(L.ws[l], 64), (unsigned)ceil_div(L.hs[l], CONV_ROWS), (unsigned)B);
         if (l == 0)
-            hipLaunchKernelGGL(conv_fwd<2>, grid, dim3(256), 0, s, nullptr, ref, ref_stride, img, hh, ww, wf, bias,
-                               out);
+            hipLaunchKernelGGL(conv_first, grid, dim3(256), 0, s, ref, ref_stride, img, hh, ww, wf, bias, out);
         else
-            hipLaunchKernelGGL(conv_fwd<32>, grid, dim3(256), 0, s, in, nullptr, 0, nullptr, hh, ww,
-                               wf + 1024 + (size_t)(l - 1) * 9 * 1024, bias, out);
+            hipLaunchKernelGGL(conv_next, grid, dim3(256), 0, s, in, hh, ww, wf + 1024 + (size_t)(l - 1) * 9 * 1024,
+                               bias, out);
         in = out;
         hh = L.hs[l];
         ww = L.ws[l];
@@ -879,8 +1006,8 @@ int cnn_backward_launch(const uint16_t *ref, int64_t ref_stride, const uint16_t 
         hipLaunchKernelGGL(wgrad_reduce, dim3((unsigned)((n_w + CNN_CH) / 32)), dim3(256), 0, s, wpart, bpart,
                            chunks, n_w, gw, gw + n_w);
         if (l > 0) {
-            const int32_t jn = (win + 1) / 2;
-            dim3 grid((unsigned)ceil_div(jn, 64), (unsigned)(2 * hin), (unsigned)B);
+            const dim3 grid((unsigned)ceil_div((win + 1) / 2, 64), (unsigned)ceil_div((hin + 1) / 2, DG_ROWS),
+                            (unsigned)B);
             hipLaunchKernelGGL(dgrad, grid, dim3(256), 0, s, dz[cur], wd + (size_t)(l - 1) * 9 * 1024, xin, hin, win,
                                dz[cur ^ 1]);
             cur ^= 1;
