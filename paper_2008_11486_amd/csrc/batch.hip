@@ -11,13 +11,13 @@
 //   PICK       argmax, runner-up, parabola of one frame
 //   RECT       common overlap of the stack from its offsets
 //   SHIFT      a 16-row strip of one frame's bilinear shift onto the overlap
-//   COMB*      sigma-clipped mean of a block of pixel columns (one launch per frame-count
-//              class: up to 16, 32, 48, 64 or 128 frames)
-//   FUSE*      for a block of output pixels of a stack of up to 48 frames without a
-//              bad-pixel map: every frame's aligned values (bilinear taps of the
-//              calibrated frames, in registers) and the clipped mean, in one pass (one
-//              launch per frame-count class; such stacks take no SHIFT or COMB item and
-//              keep no aligned frames)
+//   MASK       aligned values that read a bad pixel become NaN, one row of one frame
+//   COMB*      sigma-clipped mean of a block of pixel columns of a stack of 49 to 128
+//              frames (with a bad-pixel map: the mean of the values that are not missing)
+//   FUSE*      for a tile of output pixels of a stack of up to 48 frames: every frame's
+//              aligned (and masked) values and the clipped mean, in one pass (one launch
+//              per class of up to 16, 32 or 48 frames, without and with a bad-pixel map;
+//              such stacks take no SHIFT, MASK or COMB item and keep no aligned frames)
 //
 // Each phase is one kernel launch with one workgroup per item over all stacks; the
 // stream orders the phases, so every dependency is met at a kernel boundary and no
@@ -33,6 +33,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -51,8 +52,6 @@ ScoreArgs make_score_args(const RegPlan &p, const float *ref, const float *frame
                           int32_t Rmax, int32_t tx0, int32_t ty0, int32_t tw, int32_t th, int32_t skip);
 
 constexpr int BATCH_THREADS = 512;
-constexpr int COMB_PX16 = 4;    // pixel columns per thread of the up-to-16-frame combine
-constexpr int COMB_PX32 = 2;    // ... of the up-to-32-frame combine
 
 // Plane stride (floats) of the aligned-frame workspace for an overlap of w x h: padded
 // to 4 floats so that every frame's plane starts 16-byte aligned.
@@ -60,10 +59,9 @@ __host__ __device__ inline int64_t al_plane(int64_t w, int64_t h) { return (w * 
 
 enum ItemType : int32_t {
     IT_CAL = 0, IT_MEANPART, IT_MEANFINAL, IT_SCORE, IT_SSCORE, IT_SUM, IT_PICK, IT_RECT, IT_SHIFT, IT_MASK,
-    IT_COMB16, IT_COMB32, IT_COMB48, IT_COMBDEEP, IT_COMB16M, IT_COMB32M, IT_COMB48M, IT_COMBMISS,
-    IT_FUSE16, IT_FUSE32, IT_FUSE48
+    IT_COMBDEEP, IT_COMBMISS, IT_FUSE16, IT_FUSE32, IT_FUSE48, IT_FUSE16M, IT_FUSE32M, IT_FUSE48M
 };
-constexpr int N_PHASES = IT_FUSE48 + 1;
+constexpr int N_PHASES = IT_FUSE48M + 1;
 
 struct Item {
     int32_t type, stack, a, pad;
@@ -93,6 +91,7 @@ struct StackDev {
     double *scores;       // [N-1][D*D]
     float *soffs;         // [N][2] offsets applied by the shift
     int32_t *rect;        // [4]
+    unsigned long long *slots;  // counters of dropped values (see add_dropped) or NULL
     int32_t n_mean_parts;
     ScoreArgs sa;
 };
@@ -240,168 +239,247 @@ __global__ __launch_bounds__(SH_BLOCK) void batch_shift(BatchArgs a, int32_t fir
                                    y0, w, h, pstride, vs, aligned);
 }
 
-// Sigma-clipped mean of block it.a of the stack's overlap; PX pixel columns per thread
-// when the overlap plane allows vector loads, else one.
-template <int MAXV, int PX, bool MISS>
-__global__ __launch_bounds__(COMB_TILE) void batch_comb(BatchArgs a, int32_t first)
-{
-    const Item it = a.items[first + blockIdx.x];
-    const StackDev &s = a.stacks[it.stack];
-    const int64_t plane = (int64_t)s.rect[2] * s.rect[3];
-    const int64_t pstride = al_plane(s.rect[2], s.rect[3]);
-    // the aligned planes are padded to 4 floats; the output image needs PX-float alignment
-    const bool vec = PX > 1 && (reinterpret_cast<uintptr_t>(s.out) & (uintptr_t)(4 * PX - 1)) == 0;
-    const int64_t blocks = vec ? ceil_div(plane, (int64_t)COMB_TILE * PX) : ceil_div(plane, (int64_t)COMB_TILE);
-    if (it.a >= blocks) return;  // uniform over the workgroup
-    unsigned dropped;
-    if (vec)
-        dropped = combine_cols_block<MAXV, PX, MISS>(s.al, plane, pstride, s.N, (double)s.ksigma, s.max_iters,
-                                                     s.out, nullptr, it.a);
-    else
-        dropped = combine_cols_block<MAXV, 1, MISS>(s.al, plane, pstride, s.N, (double)s.ksigma, s.max_iters, s.out,
-                                                    nullptr, it.a);
-    if (s.n_rej) {
-        const unsigned total = block_sum_u32(dropped);
-        if (threadIdx.x == 0 && total) atomicAdd(reinterpret_cast<unsigned long long *>(s.n_rej),
-                                                 (unsigned long long)total);
-    }
-}
-
 // ---- shift + clipped mean in one pass ---------------------------------------------------
-// Q + 1 taps of one frame row at columns c0 .. c0 + Q (clamped into the row), as shift_strip
-// reads them: two 16-byte loads from the aligned column c0 - (c0 & 3) when they lie inside
-// the row (rows 16-byte aligned), else one float at a time.
-template <int Q>
-__device__ __forceinline__ void row_taps(const float *__restrict__ row, int32_t c0, int32_t W, bool aligned,
-                                         float (&t)[Q + 1])
-{
-    static_assert(Q <= 4, "two 16-byte loads cover the taps");
-    const int32_t al = c0 & 3, b = c0 - al;
-    if (aligned && b >= 0 && b + 8 <= W) {
-        const float4 u = *reinterpret_cast<const float4 *>(row + b);
-        const float4 v = *reinterpret_cast<const float4 *>(row + b + 4);
-        const float raw[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-        switch (al) {
-        case 0:
-#pragma unroll
-            for (int e = 0; e <= Q; ++e) t[e] = raw[e];
-            break;
-        case 1:
-#pragma unroll
-            for (int e = 0; e <= Q; ++e) t[e] = raw[1 + e];
-            break;
-        case 2:
-#pragma unroll
-            for (int e = 0; e <= Q; ++e) t[e] = raw[2 + e];
-            break;
-        default:
-#pragma unroll
-            for (int e = 0; e <= Q; ++e) t[e] = raw[3 + e];
-            break;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e <= Q; ++e) t[e] = row[clampi(c0 + e, 0, W - 1)];
-    }
-}
-
-// Aligned values of frame k at the Q output pixels (u0 + e, v) of one row of the overlap,
-// exactly as shift_strip makes them: taps in rows clamp(y0 + v + iy) and the one below
-// (when the vertical fraction is not zero), columns clamp(x0 + u + ix) and the one to the
-// right (when the horizontal fraction is not zero), from the calibrated frame.
-template <int Q>
-__device__ __forceinline__ void aligned_row(const StackDev &s, int32_t k, int32_t u0, int32_t v, int32_t x0,
-                                            int32_t y0, bool aligned, float (&r)[Q])
-{
-    const ShiftSetup ss = shift_setup(s.soffs[2 * k], s.soffs[2 * k + 1]);
-    const bool integer = s.integer_mode != 0;
-    const bool step = ss.a > 0.0;
-    const bool down = !integer && ss.b > 0.0;
-    const int32_t j = clampi(y0 + v + ss.iy, 0, s.H - 1);
-    const int32_t j1 = clampi(down ? j + 1 : j, 0, s.H - 1);
-    const int32_t c0 = x0 + u0 + ss.ix;
-    const float *f = s.cal + (int64_t)k * s.W * s.H;
-    float t0[Q + 1], t1[Q + 1];
-    row_taps<Q>(f + (int64_t)j * s.W, c0, s.W, aligned, t0);
-    if (j1 != j)
-        row_taps<Q>(f + (int64_t)j1 * s.W, c0, s.W, aligned, t1);
-    else
-#pragma unroll
-        for (int e = 0; e <= Q; ++e) t1[e] = t0[e];
-#pragma unroll
-    for (int e = 0; e < Q; ++e) {
-        if (integer) {
-            r[e] = t0[e];
-        } else {
-            const float f10 = step ? t0[e + 1] : t0[e];
-            const float f11 = step ? t1[e + 1] : t1[e];
-            r[e] = bilerp(ss.a, ss.b, t0[e], f10, t1[e], f11);
-        }
-    }
-}
-
-// A block of FUSE_PX consecutive output pixels (linear index over the overlap) of every
-// frame: first the aligned values, FUSE_Q pixels of one frame per work unit, all units of
-// the block spread over the workgroup (many loads in flight) into an LDS tile
-// [N][FUSE_PX]; then one thread per pixel clips its column of the tile in registers (the
-// queue of combine_cols_block made this phase slower: 22.2 -> 24.0 ms per step on the
-// 64-stack workload, so every column is clipped in place).
-constexpr int FUSE_PX = 256;
+// A tile of FUSE_COLS x FUSE_ROWS output pixels of every frame: first the aligned values, a
+// work unit being FUSE_Q columns of all the tile's rows of one frame, whose FUSE_ROWS + 1 tap
+// rows are loaded at once (16 and 4 bytes at element alignment) and each used for the two
+// output rows it lies between, into an LDS tile [N][FUSE_ROWS][FUSE_COLS]; then one thread per
+// pixel runs the first iteration of the clip on its column of the tile, and the few columns
+// that drop a value go through the rest of it together (see combine_cols_block), again from
+// the tile.  With a bad-pixel map (MASK) the taps' map bytes come in the same way, values
+// that read a bad pixel are NaN, and the clip leaves them out.
+//
+// Bound by the loads of the calibrated frames and, about equally, double arithmetic (a tap's
+// conversion, four products and three sums per value, eight operations in the clip).  With
+// 256 consecutive pixels per workgroup, two tap rows loaded for each output row, 11 frames of
+// 4096x4096 with 3 of 2048x2048 took 490 us, now 376; 23 of 2048x2048 with 30 of 1024x1024 437, now 305;
+// 16 masked frames of 6144x6160 as a shift, a mask and a clip (which write and read the
+// aligned frames) 2100, now 1020.  Registers are held to what the LDS tile allows in waves:
+// 16 frames took 400 us at seven waves per SIMD, 376 at eight.
+constexpr int FUSE_COLS = 64;
+constexpr int FUSE_ROWS = 4;
+constexpr int FUSE_PX = FUSE_COLS * FUSE_ROWS;
 constexpr int FUSE_Q = 4;
+constexpr int FUSE_QCAP = 64;  // queued columns whose first iteration is kept
 static_assert(FUSE_PX == COMB_TILE, "one pixel per thread in the clip");
 
-template <int MAXV>
-__global__ __launch_bounds__(COMB_TILE) void batch_fused(BatchArgs a, int32_t first)
+typedef float fuse_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t fuse_u32 __attribute__((aligned(1)));
+
+// Aligned values of frame k at FUSE_Q output pixels (u0 + e) of rows v0 .. v0 + FUSE_ROWS - 1
+// into dst [row][FUSE_COLS], exactly as shift_strip makes them: taps in rows
+// clamp(y0 + v + iy) and the one below (when the vertical fraction is not zero), columns
+// clamp(x0 + u + ix) and the one to the right (when the horizontal fraction is not zero),
+// from the calibrated frame; and NaN where mask_shifted_kernel would write it.
+template <bool MASK, bool INTEGER>
+__device__ __forceinline__ void aligned_unit(const StackDev &s, int32_t k, int32_t u0, int32_t v0, int32_t x0,
+                                             int32_t y0, float *__restrict__ dst)
 {
-    extern __shared__ float tile[];  // [N][FUSE_PX]
-    const Item it = a.items[first + blockIdx.x];
-    const StackDev &s = a.stacks[it.stack];
-    const int32_t x0 = s.rect[0], y0 = s.rect[1], w = s.rect[2], h = s.rect[3];
-    const int64_t plane = (int64_t)w * h;
-    const int64_t pb = (int64_t)it.a * FUSE_PX;
-    if (pb >= plane) return;  // uniform over the workgroup
-    const bool aligned = s.W % 4 == 0;  // calibrated rows start 16-byte aligned
-    const int t = threadIdx.x;
-    constexpr int UNITS = FUSE_PX / FUSE_Q;         // work units per frame
-    constexpr int KSTEP = COMB_TILE / UNITS;        // frames taken together
-    // thread t: pixels q * FUSE_Q .. + FUSE_Q - 1 of the block, frames k0, k0 + KSTEP, ...
-    const int q = t % UNITS, k0 = t / UNITS;
-    const int64_t p0 = pb + q * FUSE_Q;
-    const int32_t v0 = (int32_t)(p0 / w), u0 = (int32_t)(p0 - (int64_t)v0 * w);
-    const bool one_row = p0 + FUSE_Q <= plane && u0 + FUSE_Q <= w;
-#pragma unroll 4
-    for (int32_t k = k0; k < s.N; k += KSTEP) {
-        float r[FUSE_Q] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (one_row) {
-            aligned_row<FUSE_Q>(s, k, u0, v0, x0, y0, aligned, r);
+    constexpr int Q = FUSE_Q, R = FUSE_ROWS;
+    const ShiftSetup ss = shift_setup(s.soffs[2 * k], s.soffs[2 * k + 1]);
+    const bool step = !INTEGER && ss.a > 0.0;
+    const bool down = !INTEGER && ss.b > 0.0;
+    const int32_t c0 = x0 + u0 + ss.ix, j0 = y0 + v0 + ss.iy;
+    const float *f = s.cal + (int64_t)k * s.W * s.H;
+    auto store = [&](float (&o)[Q], uint64_t bad, int r) {
+        if constexpr (MASK) {  // byte e of bad: column c0 + e of either tap row
+            const uint64_t b = step ? bad | (bad >> 8) : bad;
+            if ((uint32_t)b) {
+#pragma unroll
+                for (int e = 0; e < Q; ++e)
+                    if ((b >> (8 * e)) & 0xff) o[e] = __builtin_nanf("");
+            }
+        }
+        *reinterpret_cast<float4 *>(dst + r * FUSE_COLS) = make_float4(o[0], o[1], o[2], o[3]);
+    };
+    auto values = [&](const float (&t0)[Q + 1], const float (&t1)[Q + 1], uint64_t bad, int r) {
+        float o[Q];
+#pragma unroll
+        for (int e = 0; e < Q; ++e) {
+            // the right-hand tap is the next column only when it carries weight
+            const float f10 = step ? t0[e + 1] : t0[e], f11 = step ? t1[e + 1] : t1[e];
+            o[e] = INTEGER ? t0[e] : bilerp(ss.a, ss.b, t0[e], f10, t1[e], f11);
+        }
+        store(o, bad, r);
+    };
+    if (c0 >= 0 && c0 + Q + 1 <= s.W && j0 >= 0) {
+        // rows j0 .. j0 + R: the lower tap row of an output row is the upper one of the next
+        // (past the last frame row both are that row)
+        float t[R + 1][Q + 1];
+        uint64_t m[R + 1];
+        int64_t at = (int64_t)j0 * s.W + c0;
+        if (j0 >= s.H) at = (int64_t)(s.H - 1) * s.W + c0;
+#pragma unroll
+        for (int i = 0; i <= R; ++i) {
+            const fuse_f4 v = *reinterpret_cast<const fuse_f4 *>(f + at);
+#pragma unroll
+            for (int e = 0; e < Q; ++e) t[i][e] = v[e];
+            t[i][Q] = f[at + Q];
+            m[i] = 0;
+            if constexpr (MASK)
+                m[i] = *reinterpret_cast<const fuse_u32 *>(s.mask + at) | ((uint64_t)s.mask[at + Q] << 32);
+            at += j0 + i + 1 < s.H ? s.W : 0;
+        }
+        if (step && down) {
+            // bilerp with each tap converted once
+            const double ra = 1.0 - ss.a, rb = 1.0 - ss.b;
+            const double w00 = __dmul_rn(ra, rb), w10 = __dmul_rn(ss.a, rb), w01 = __dmul_rn(ra, ss.b),
+                         w11 = __dmul_rn(ss.a, ss.b);
+            double d0[Q + 1], d1[Q + 1];
+#pragma unroll
+            for (int e = 0; e <= Q; ++e) d0[e] = (double)t[0][e];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float o[Q];
+#pragma unroll
+                for (int e = 0; e <= Q; ++e) {
+                    float f1 = t[r + 1][e];
+                    asm volatile("" : "+v"(f1));  // converted here, not all rows beforehand
+                    d1[e] = (double)f1;
+                }
+#pragma unroll
+                for (int e = 0; e < Q; ++e)
+                    o[e] = (float)__dadd_rn(__dadd_rn(__dadd_rn(__dmul_rn(w00, d0[e]), __dmul_rn(w10, d0[e + 1])),
+                                                      __dmul_rn(w01, d1[e])),
+                                            __dmul_rn(w11, d1[e + 1]));
+                store(o, m[r] | m[r + 1], r);
+                __builtin_amdgcn_sched_barrier(0);  // one row at a time: bounds the registers in flight
+#pragma unroll
+                for (int e = 0; e <= Q; ++e) d0[e] = d1[e];
+            }
         } else {
 #pragma unroll
-            for (int c = 0; c < FUSE_Q; ++c) {
-                const int64_t p = p0 + c;
-                if (p < plane) {
-                    const int32_t v = (int32_t)(p / w);
-                    float r1[1];
-                    aligned_row<1>(s, k, (int32_t)(p - (int64_t)v * w), v, x0, y0, aligned, r1);
-                    r[c] = r1[0];
+            for (int r = 0; r < R; ++r) {
+                float t1[Q + 1];
+#pragma unroll
+                for (int e = 0; e <= Q; ++e) t1[e] = down ? t[r + 1][e] : t[r][e];
+                values(t[r], t1, down ? m[r] | m[r + 1] : m[r], r);
+            }
+        }
+    } else {
+#pragma unroll 1
+        for (int r = 0; r < R; ++r) {
+            const int32_t j = clampi(j0 + r, 0, s.H - 1), j1 = clampi(down ? j + 1 : j, 0, s.H - 1);
+            float t0[Q + 1], t1[Q + 1];
+            uint64_t bad = 0;
+#pragma unroll
+            for (int e = 0; e <= Q; ++e) {
+                const int32_t c = clampi(c0 + e, 0, s.W - 1);
+                t0[e] = f[(int64_t)j * s.W + c];
+                t1[e] = f[(int64_t)j1 * s.W + c];
+                if constexpr (MASK)
+                    bad |= (uint64_t)(s.mask[(int64_t)j * s.W + c] | s.mask[(int64_t)j1 * s.W + c]) << (8 * e);
+            }
+            values(t0, t1, bad, r);
+        }
+    }
+}
+
+// The number of dropped values: one addition per tile to one address takes 12 ns, longer than
+// the rest of the tile (16 masked frames of 6144x6160, 147000 tiles: 1820 us, of which
+// 1100 without it), so stacks of many tiles add into REJ_SLOTS counters, which batch_rejected
+// adds up after the launch.
+constexpr int REJ_SLOTS = 64;
+constexpr int REJ_STRIDE = 8;    // 64 bytes apart
+constexpr int REJ_TILES = 4096;  // tiles from which on a stack has them
+
+__device__ __forceinline__ void add_dropped(const StackDev &s, int32_t item, unsigned total)
+{
+    unsigned long long *n = s.slots ? s.slots + item % REJ_SLOTS * REJ_STRIDE
+                                    : reinterpret_cast<unsigned long long *>(s.n_rej);
+    if (total) atomicAdd(n, (unsigned long long)total);
+}
+
+__global__ __launch_bounds__(REJ_SLOTS) void batch_rejected(BatchArgs a)
+{
+    const StackDev &s = a.stacks[blockIdx.x];
+    if (!s.slots || !s.n_rej) return;
+    unsigned long long v = s.slots[threadIdx.x * REJ_STRIDE];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (threadIdx.x == 0) *s.n_rej = (int64_t)v;
+}
+
+template <int MAXV, bool MASK>
+__global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(MAXV == 16 ? (MASK ? 7 : 8) : 5))) void batch_fused(BatchArgs a, int32_t first, int32_t count)
+{
+    extern __shared__ float tile[];  // [MAXV][FUSE_ROWS][FUSE_COLS]
+    __shared__ int32_t queue[FUSE_PX];  // pixels that drop values
+    __shared__ double qm[FUSE_QCAP], qt[FUSE_QCAP];  // mean, threshold and number of values of their first iteration
+    __shared__ int32_t qn[FUSE_QCAP];
+    __shared__ int32_t queued;
+    // XCD-aware order: the tap row that two rows of tiles share is in one L2
+    const Item it = a.items[first + xcd_logical_id((int32_t)blockIdx.x, count)];
+    const StackDev &s = a.stacks[it.stack];
+    const int32_t x0 = s.rect[0], y0 = s.rect[1], w = s.rect[2], h = s.rect[3];
+    const int32_t tiles_x = (w + FUSE_COLS - 1) / FUSE_COLS, tiles = tiles_x * ((h + FUSE_ROWS - 1) / FUSE_ROWS);
+    if (w < 1 || h < 1 || it.a >= tiles) return;  // uniform over the workgroup
+    const int32_t ty = it.a / tiles_x, u0 = (it.a - ty * tiles_x) * FUSE_COLS, v0 = ty * FUSE_ROWS;
+    const int32_t N = __builtin_amdgcn_readfirstlane(s.N);
+    const double ksigma = (double)s.ksigma;
+    const int t = threadIdx.x;
+    constexpr int UNITS = FUSE_COLS / FUSE_Q;  // work units per frame
+    const int q = t % UNITS;
+    unsigned dropped = 0;
+    {
+        if (t == 0) queued = 0;
+#pragma unroll
+        for (int i = 0; i < MAXV * UNITS / COMB_TILE; ++i) {
+            const int32_t k = t / UNITS + i * (COMB_TILE / UNITS);
+            if (k < N && u0 + q * FUSE_Q < w) {
+                float *dst = tile + k * FUSE_PX + q * FUSE_Q;
+                if (s.integer_mode)
+                    aligned_unit<MASK, true>(s, k, u0 + q * FUSE_Q, v0, x0, y0, dst);
+                else
+                    aligned_unit<MASK, false>(s, k, u0 + q * FUSE_Q, v0, x0, y0, dst);
+            }
+        }
+        __syncthreads();
+        // first iterations; the pixels that drop values go to the queue (see combine_cols_block)
+        {
+            float x[MAXV];
+            each_group<MAXV>(N, [&](int i) { x[i] = tile[i * FUSE_PX + t]; });
+            const int32_t u = u0 + t % FUSE_COLS, v = v0 + t / FUSE_COLS;
+            ClipState st;
+            double m, thr;
+            const bool done = clip_first<MAXV, MASK>(RegColumn<MAXV>{x}, N, ksigma, s.max_iters, st, m, thr);
+            if (u < w && v < h) {
+                if (done) {
+                    s.out[(int64_t)v * w + u] = (float)m;
+                } else {
+                    const int32_t e = atomicAdd(&queued, 1);
+                    queue[e] = t;
+                    if (e < FUSE_QCAP) {
+                        qm[e] = m;
+                        qt[e] = thr;
+                        qn[e] = st.n;
+                    }
                 }
             }
         }
-        *reinterpret_cast<float4 *>(tile + (int64_t)k * FUSE_PX + q * FUSE_Q) = make_float4(r[0], r[1], r[2], r[3]);
+        __syncthreads();
+        if (t < queued) {
+            const int32_t c = queue[t], u = u0 + c % FUSE_COLS, v = v0 + c / FUSE_COLS;
+            float x[MAXV];
+            each_group<MAXV>(N, [&](int i) { x[i] = tile[i * FUSE_PX + c]; });
+            ClipState st;
+            double m, thr;
+            if (t < FUSE_QCAP) {
+                st.lo = -INFINITY;
+                st.hi = INFINITY;
+                st.n = qn[t];
+                m = qm[t];
+                thr = qt[t];
+            } else {
+                clip_first<MAXV, MASK>(RegColumn<MAXV>{x}, N, ksigma, s.max_iters, st, m, thr);
+            }
+            s.out[(int64_t)v * w + u] =
+                clip_rest<MAXV>(RegColumn<MAXV>{x}, N, ksigma, s.max_iters, st, m, thr, dropped);
+        }
     }
-    __syncthreads();
-    float x[MAXV];
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i) x[i] = i < s.N ? tile[i * FUSE_PX + t] : 0.0f;
-    ClipState st;
-    unsigned dropped = 0;
-    const float res = clip_registers<MAXV>(x, s.N, (double)s.ksigma, s.max_iters, st, dropped);
-    const int64_t p = pb + t;
-    if (p < plane) s.out[p] = res;
-    else dropped = 0;
     if (s.n_rej) {
         const unsigned total = block_sum_u32(dropped);
-        if (threadIdx.x == 0 && total)
-            atomicAdd(reinterpret_cast<unsigned long long *>(s.n_rej), (unsigned long long)total);
+        if (t == 0) add_dropped(s, it.a, total);
     }
 }
 
@@ -440,18 +518,22 @@ __global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(3, 3)
     }
 }
 
-__global__ void batch_reset(int64_t *const *n_rej, int32_t n_stacks)
+__global__ __launch_bounds__(REJ_SLOTS) void batch_reset(BatchArgs a)
 {
-    for (int32_t i = threadIdx.x; i < n_stacks; i += blockDim.x)
-        if (n_rej[i]) *n_rej[i] = 0;
+    const StackDev &s = a.stacks[blockIdx.x];
+    if (s.n_rej && threadIdx.x == 0) *s.n_rej = 0;
+    if (s.slots) s.slots[threadIdx.x * REJ_STRIDE] = 0;
 }
 
 // ---- host side ---------------------------------------------------------------------------
 static size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 
+// Tiles of the fused phase, for the whole frame.
+static int64_t fuse_tiles(int32_t W, int32_t H) { return ceil_div(W, FUSE_COLS) * ceil_div(H, FUSE_ROWS); }
+
 struct StackLayout {
     RegPlan plan;
-    size_t cal, al, mean_parts, mean, partial, scores, soffs, rect;
+    size_t cal, al, mean_parts, mean, partial, scores, soffs, rect, slots;  // slots: 0 for none
     int32_t count[N_PHASES];
 };
 
@@ -464,7 +546,7 @@ struct ScoreGroup {
 
 struct BatchLayout {
     std::vector<StackLayout> st;
-    size_t items, stacks, nrej_ptrs, total;
+    size_t items, stacks, total;
     int32_t n_items;
     int32_t first[N_PHASES], count[N_PHASES];
     size_t score_lds;
@@ -530,7 +612,7 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
         const int32_t nreg = s.N - 1;
         // a stack of up to 48 frames without a bad-pixel map takes the fused phase (no
         // aligned frames in the workspace)
-        const bool fuse = s.mask == nullptr && s.N <= 48;
+        const bool fuse = s.N <= 48;
         sl.cal = off;
         off += al(sizeof(float) * fp * s.N);
         sl.al = off;
@@ -551,6 +633,8 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
         off += al(sizeof(float) * 2 * s.N);
         sl.rect = off;
         off += 256;
+        sl.slots = fuse && fuse_tiles(s.W, s.H) >= REJ_TILES ? off : 0;
+        if (sl.slots) off += al(sizeof(uint64_t) * REJ_SLOTS * REJ_STRIDE);
         sl.count[IT_CAL] = (int32_t)ceil_div(s.W >= CAL_VEC ? cal_groups(s.W) * s.H : fp, CAL_BLOCK);
         sl.count[IT_MEANPART] = ndir > 0 ? n_mean_parts : 0;
         sl.count[IT_MEANFINAL] = ndir > 0 ? 1 : 0;
@@ -561,28 +645,16 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
         sl.count[IT_RECT] = 1;
         sl.count[IT_SHIFT] =
             fuse ? 0 : s.N * (int32_t)ceil_div(s.H, SH_ROWS) * (int32_t)ceil_div(s.W, (int64_t)SH_BLOCK * SH_VEC);
-        // enough clip items for the whole frame (the overlap is only known on the device),
-        // PX columns per thread when the output image allows PX-float stores
-        const int px = s.N <= 16 ? COMB_PX16 : s.N <= 32 ? COMB_PX32 : 1;
-        const bool vec = px > 1 && (reinterpret_cast<uintptr_t>(s.out) & (uintptr_t)(4 * px - 1)) == 0;
-        const int32_t comb_blocks = (int32_t)ceil_div(fp, (int64_t)COMB_TILE * (vec ? px : 1));
-        // a stack with a bad-pixel map has its aligned values masked and takes the combine
-        // that leaves missing values out
+        // enough items for the whole frame (the overlap is only known on the device); a stack
+        // with a bad-pixel map takes the clip that leaves missing values out
         const bool miss = s.mask != nullptr;
-        sl.count[IT_MASK] = miss ? s.N * s.H : 0;
-        const int32_t c16 = s.N <= 16 ? comb_blocks : 0;
-        const int32_t c32 = s.N > 16 && s.N <= 32 ? comb_blocks : 0;
-        const int32_t c48 = s.N > 32 && s.N <= 48 ? comb_blocks : 0;
+        sl.count[IT_MASK] = miss && !fuse ? s.N * s.H : 0;
         if (fuse) {
-            const int32_t fb = (int32_t)ceil_div(fp, (int64_t)FUSE_PX);
-            sl.count[IT_FUSE16] = s.N <= 16 ? fb : 0;
-            sl.count[IT_FUSE32] = s.N > 16 && s.N <= 32 ? fb : 0;
-            sl.count[IT_FUSE48] = s.N > 32 ? fb : 0;
+            const int32_t fb = (int32_t)fuse_tiles(s.W, s.H);
+            sl.count[s.N <= 16 ? (miss ? IT_FUSE16M : IT_FUSE16)
+                               : s.N <= 32 ? (miss ? IT_FUSE32M : IT_FUSE32) : (miss ? IT_FUSE48M : IT_FUSE48)] = fb;
         }
         const int32_t deep_blocks = s.N > 48 ? (int32_t)ceil_div(fp, (int64_t)COMB_TILE) : 0;
-        sl.count[miss ? IT_COMB16M : IT_COMB16] = fuse ? 0 : c16;
-        sl.count[miss ? IT_COMB32M : IT_COMB32] = fuse ? 0 : c32;
-        sl.count[miss ? IT_COMB48M : IT_COMB48] = fuse ? 0 : c48;
         sl.count[miss ? IT_COMBMISS : IT_COMBDEEP] = deep_blocks;
         if (s.N > 48) (miss ? L.miss_n : L.deep_n) = std::max(miss ? L.miss_n : L.deep_n, s.N);
         for (int q = 0; q < N_PHASES; ++q) L.count[q] += sl.count[q];
@@ -623,8 +695,6 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
     off += al(sizeof(Item) * (size_t)std::max<int64_t>(total, 0));
     L.stacks = off;
     off += al(sizeof(StackDev) * (size_t)n);
-    L.nrej_ptrs = off;
-    off += al(sizeof(int64_t *) * (size_t)n);
     L.total = off;
     return L;
 }
@@ -654,7 +724,6 @@ static int build_descriptors(const reduce_stack_t *stacks, int32_t n, void *ws, 
 {
     unsigned char *base = static_cast<unsigned char *>(ws);
     std::vector<StackDev> sd(n);
-    std::vector<int64_t *> nrej(n);
     for (int32_t i = 0; i < n; ++i) {
         const reduce_stack_t &st = stacks[i];
         const StackLayout &sl = L.st[i];
@@ -671,7 +740,7 @@ static int build_descriptors(const reduce_stack_t *stacks, int32_t n, void *ws, 
         d.out_rect = st.out_rect;
         d.offsets = st.offsets;
         d.n_rej = st.n_rej;
-        nrej[i] = st.n_rej;
+        d.slots = sl.slots ? reinterpret_cast<unsigned long long *>(base + sl.slots) : nullptr;
         d.W = st.W;
         d.H = st.H;
         d.N = st.N;
@@ -702,8 +771,7 @@ static int build_descriptors(const reduce_stack_t *stacks, int32_t n, void *ws, 
         const auto cost = [&](int32_t z) {
             const RegPlan &p = L.st[z].plan;
             return (double)(L.st[z].count[IT_SCORE] + L.st[z].count[IT_SSCORE]) * p.BR * p.TX * p.C +
-                   (double)L.st[z].count[IT_SHIFT] + (double)L.st[z].count[IT_FUSE16] +
-                   (double)L.st[z].count[IT_FUSE32] + (double)L.st[z].count[IT_FUSE48];
+                   (double)std::accumulate(L.st[z].count + IT_SHIFT, L.st[z].count + N_PHASES, 0);
         };
         return cost(x) > cost(y);
     });
@@ -723,7 +791,6 @@ static int build_descriptors(const reduce_stack_t *stacks, int32_t n, void *ws, 
     e->host.assign(L.total - L.items, 0);
     std::memcpy(e->host.data(), items.data(), sizeof(Item) * items.size());
     std::memcpy(e->host.data() + (L.stacks - L.items), sd.data(), sizeof(StackDev) * sd.size());
-    std::memcpy(e->host.data() + (L.nrej_ptrs - L.items), nrej.data(), sizeof(int64_t *) * nrej.size());
     return REDUCE_OK;
 }
 
@@ -746,8 +813,7 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
     BatchArgs a;
     a.items = reinterpret_cast<const Item *>(base + L.items);
     a.stacks = reinterpret_cast<const StackDev *>(base + L.stacks);
-    int64_t *const *nrej_dev = reinterpret_cast<int64_t *const *>(base + L.nrej_ptrs);
-    hipLaunchKernelGGL(batch_reset, dim3(1), dim3(256), 0, s, nrej_dev, n);
+    hipLaunchKernelGGL(batch_reset, dim3(n), dim3(REJ_SLOTS), 0, s, a);
     if (L.count[IT_CAL] > 0)
         hipLaunchKernelGGL(batch_cal, dim3(L.count[IT_CAL]), dim3(CAL_BLOCK), 0, s, a, L.first[IT_CAL]);
     if (L.count[IT_MEANPART] > 0)
@@ -794,24 +860,6 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
                            L.count[IT_MASK]);
     {
         ProfScope prof("batch_comb", s);
-        if (L.count[IT_COMB16] > 0)
-            hipLaunchKernelGGL((batch_comb<16, COMB_PX16, false>), dim3(L.count[IT_COMB16]), dim3(COMB_TILE), 0, s,
-                               a, L.first[IT_COMB16]);
-        if (L.count[IT_COMB32] > 0)
-            hipLaunchKernelGGL((batch_comb<32, COMB_PX32, false>), dim3(L.count[IT_COMB32]), dim3(COMB_TILE), 0, s,
-                               a, L.first[IT_COMB32]);
-        if (L.count[IT_COMB48] > 0)
-            hipLaunchKernelGGL((batch_comb<48, 1, false>), dim3(L.count[IT_COMB48]), dim3(COMB_TILE), 0, s, a,
-                               L.first[IT_COMB48]);
-        if (L.count[IT_COMB16M] > 0)
-            hipLaunchKernelGGL((batch_comb<16, COMB_PX16, true>), dim3(L.count[IT_COMB16M]), dim3(COMB_TILE), 0, s,
-                               a, L.first[IT_COMB16M]);
-        if (L.count[IT_COMB32M] > 0)
-            hipLaunchKernelGGL((batch_comb<32, COMB_PX32, true>), dim3(L.count[IT_COMB32M]), dim3(COMB_TILE), 0, s,
-                               a, L.first[IT_COMB32M]);
-        if (L.count[IT_COMB48M] > 0)
-            hipLaunchKernelGGL((batch_comb<48, 1, true>), dim3(L.count[IT_COMB48M]), dim3(COMB_TILE), 0, s, a,
-                               L.first[IT_COMB48M]);
         if (L.count[IT_COMBDEEP] > 0)
             deep_dispatch(L.deep_n, [&](auto Vc) {
                 hipLaunchKernelGGL((batch_comb_deep<decltype(Vc)::value, false>), dim3(L.count[IT_COMBDEEP]),
@@ -823,19 +871,21 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
                                    dim3(COMB_TILE), 0, s, a, L.first[IT_COMBMISS]);
             });
     }
-    if (L.count[IT_FUSE16] + L.count[IT_FUSE32] + L.count[IT_FUSE48] > 0) {
-        ProfScope prof("batch_fused", s);
-        // the tile holds the frames of the class's deepest stack
-        if (L.count[IT_FUSE16] > 0)
-            hipLaunchKernelGGL(batch_fused<16>, dim3(L.count[IT_FUSE16]), dim3(COMB_TILE),
-                               sizeof(float) * FUSE_PX * 16, s, a, L.first[IT_FUSE16]);
-        if (L.count[IT_FUSE32] > 0)
-            hipLaunchKernelGGL(batch_fused<32>, dim3(L.count[IT_FUSE32]), dim3(COMB_TILE),
-                               sizeof(float) * FUSE_PX * 32, s, a, L.first[IT_FUSE32]);
-        if (L.count[IT_FUSE48] > 0)
-            hipLaunchKernelGGL(batch_fused<48>, dim3(L.count[IT_FUSE48]), dim3(COMB_TILE),
-                               sizeof(float) * FUSE_PX * 48, s, a, L.first[IT_FUSE48]);
-    }
+    ProfScope prof("batch_fused", s);
+    const auto fused = [&](int phase, auto maxv, auto masked) {
+        constexpr int V = decltype(maxv)::value;
+        if (L.count[phase] > 0)
+            hipLaunchKernelGGL((batch_fused<V, decltype(masked)::value>), dim3(L.count[phase]), dim3(COMB_TILE),
+                               sizeof(float) * FUSE_PX * V, s, a, L.first[phase], getenv("NOXCD") ? 0 : L.count[phase]);
+    };
+    fused(IT_FUSE16, std::integral_constant<int, 16>{}, std::false_type{});
+    fused(IT_FUSE32, std::integral_constant<int, 32>{}, std::false_type{});
+    fused(IT_FUSE48, std::integral_constant<int, 48>{}, std::false_type{});
+    fused(IT_FUSE16M, std::integral_constant<int, 16>{}, std::true_type{});
+    fused(IT_FUSE32M, std::integral_constant<int, 32>{}, std::true_type{});
+    fused(IT_FUSE48M, std::integral_constant<int, 48>{}, std::true_type{});
+    if (std::any_of(L.st.begin(), L.st.end(), [](const StackLayout &l) { return l.slots != 0; }))
+        hipLaunchKernelGGL(batch_rejected, dim3(n), dim3(REJ_SLOTS), 0, s, a);
     return check_launch("reduce_stack_batch");
 }
 
