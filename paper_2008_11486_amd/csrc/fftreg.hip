@@ -491,84 +491,73 @@ __global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
 
 // ---- scores at the lags of the window --------------------------------------------------
 // S[f][j][m] = (1/P) sum_{k=0}^{N2} c_k Re(Z_j(k) e^{+2 pi i k m / P}), c_k = 1 at k = 0 and
-// k = N2, else 2; Z_j(k) the sum of the partials over bands in order.  One
-// workgroup per (lag j, frame f); lanes stride over k; the D sums over m are reduced
-// over the workgroup in a fixed order.  The twiddles of a pass over m0 .. m0 + EVAL_M - 1
-// come from one table value and a recurrence, w(k, m + 1) = w(k, m) w(k, 1): scattered
-// reads of the table for every (k, m) had bound the kernel by cache traffic.  A step adds
-// at most sqrt(5) eps (the product) + 2 eps (the table value w(k, 1)) of relative error, so
-// a twiddle is within 5 EVAL_M eps; the error bound of the decision below carries a term
-// of 8 EVAL_M eps for it.
-constexpr int EVAL_M = 16;  // lags m formed per pass
-
+// k = N2, else 2; Z_j(k) the sum of the partials over bands in order.  Only D of the P lags m
+// are asked for, so the sum is split by residues, k = a + A b with A = P / COL_L:
+//   sum_a e^{2 pi i a m / P} sum_b z(a + A b) e^{2 pi i b m / COL_L},
+// the inner sums 256-point transforms (as in the contraction, sixteen at a time, of which
+// half the inputs are zero) that give 256 consecutive lags, the outer one A products per lag.  A
+// workgroup takes one lag j (or, for A < 16, 16 / A of them) of a frame and, by blockIdx.z,
+// one of the ranges of 256 lags m.  Bound by the reads of the partials; with D products per k
+// and a recurrence for the twiddles, 131 lags of 15 frames at P = 8192 took 698 us, now 86, and
+// 35 lags of 85 frames at P = 512 to 4096 in six calls 202, now 66.
 template <int LOG2N2>
-__global__ __launch_bounds__(FFT_THREADS) void spec_eval(const double2 *__restrict__ Zp, int32_t n_part, int32_t D,
-                                                         int32_t PS, const double2 *__restrict__ tw,
-                                                         double *__restrict__ S)
+__global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_eval(const double2 *__restrict__ Zp, int32_t n_part, int32_t D,
+                                                   int32_t PS, const double2 *__restrict__ tw, double *__restrict__ S)
 {
-    constexpr int32_t N2 = 1 << LOG2N2, P = 2 * N2;
-    extern __shared__ __align__(16) double2 zs[];  // [N2 + 1]: c_k Z_j(k)
-    __shared__ double red[FFT_THREADS / 64][EVAL_M];
-    const int32_t j = blockIdx.x, f = blockIdx.y;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const double2 *z0 = Zp + (int64_t)f * n_part * D * PS + (int64_t)j * PS;
-    for (int32_t k = t; k <= N2; k += FFT_THREADS) {
-        // the partials added in order p = 0, 1, ...; eight loaded together at a time (a
-        // partial index past the last is clamped and its value not added)
-        double2 s = make_double2(0.0, 0.0);
-        for (int32_t p0 = 0; p0 < n_part; p0 += 8) {
-            double2 v[8];
+    constexpr int32_t N2 = 1 << LOG2N2, P = 2 * N2, A = P > COL_L ? P / COL_L : 1;
+    constexpr int SP = COL_L > P ? COL_L / P : 1;  // shorter spectra: every SP-th input
+    constexpr int AC = A < COL_KC ? A : COL_KC;  // residues per pass
+    static_assert(A % AC == 0, "whole passes");
+    __shared__ double2 z[COL_L * COL_KC], wl[COL_L];
+    const int t = threadIdx.x, col = t & (COL_KC - 1), r = t / COL_KC;
+    const int a0 = col % AC;
+    const int32_t j = blockIdx.x * (COL_KC / AC) + col / AC, f = blockIdx.y, m0 = blockIdx.z * COL_L;
+    const double2 *z0 = Zp + (int64_t)f * n_part * D * PS + (int64_t)min(j, D - 1) * PS;
+    const int64_t pstride = (int64_t)D * PS;
+    col_table(wl);
+    double acc[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = z0[(int64_t)min(p0 + u, n_part - 1) * D * PS + k];
+    for (int d = 0; d < 16; ++d) acc[d] = 0.0;
+    for (int32_t a = a0; a < A; a += AC) {
+        // inputs b = 16 i + r, zero above N2: b = 128 is k = N2 for the residue 0
+        double2 v[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (p0 + u < n_part) s = cadd(s, v[u]);
-        }
-        const double c = (k == 0 || k == N2) ? 1.0 : 2.0;
-        zs[k] = make_double2(c * s.x, c * s.y);
-    }
-    __syncthreads();
-    for (int32_t m0 = 0; m0 < D; m0 += EVAL_M) {
-        double acc[EVAL_M];
+        for (int i = 0; i < 16; ++i) v[i] = make_double2(0.0, 0.0);
+        for (int32_t p = 0; p < n_part; ++p) {
+            double2 u[8];
 #pragma unroll
-        for (int q = 0; q < EVAL_M; ++q) acc[q] = 0.0;
-        // EVAL_K values of k per iteration, their table values loaded together; a k past N2
-        // is clamped for the loads and its spectrum value taken as zero (adding 0 * w to a
-        // sum that started at +0 leaves it exact), so the sums are those of k in order
-        constexpr int EVAL_K = 4;
-#pragma unroll 1
-        for (int32_t k0 = t; k0 <= N2; k0 += EVAL_K * FFT_THREADS) {
-            double2 w[EVAL_K], w1[EVAL_K], z[EVAL_K];
-#pragma unroll
-            for (int e = 0; e < EVAL_K; ++e) {
-                const int32_t kc = min(k0 + e * FFT_THREADS, N2);
-                w[e] = tw[((int64_t)kc * m0) & (P - 1)];  // e^{-2 pi i k m / P} at m = m0
-                w1[e] = tw[kc & (P - 1)];                 // and at m = 1
-                z[e] = k0 + e * FFT_THREADS <= N2 ? zs[kc] : make_double2(0.0, 0.0);
+            for (int i = 0; i < 8; ++i) {
+                u[i] = z0[p * pstride + a + A * ((16 * i + r) / SP)];
+                if (SP > 1 && r % SP != 0) u[i] = make_double2(0.0, 0.0);
             }
 #pragma unroll
-            for (int e = 0; e < EVAL_K; ++e)
-#pragma unroll
-                for (int q = 0; q < EVAL_M; ++q) {
-                    acc[q] = fma(z[e].x, w[e].x, acc[q]);  // Re(z conj(w))
-                    acc[q] = fma(z[e].y, w[e].y, acc[q]);
-                    if (q + 1 < EVAL_M) w[e] = cmul(w[e], w1[e]);
-                }
+            for (int i = 0; i < 8; ++i) v[i] = cadd(v[i], u[i]);
+            if (a == 0 && r == 0) v[8] = cadd(v[8], z0[p * pstride + N2]);
         }
 #pragma unroll
-        for (int q = 0; q < EVAL_M; ++q) {
-            double v = acc[q];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0) red[wv][q] = v;
+        for (int i = 0; i < 8; ++i) {
+            const double c = a == 0 && i == 0 && r == 0 ? 1.0 : 2.0;
+            v[i] = make_double2(c * v[i].x, c * v[i].y);
         }
+        __syncthreads();  // the table is written; the last pass's second halves have read z
+        col_first_half<true>(v, z, wl, r, col);
         __syncthreads();
-        if (t < EVAL_M && m0 + t < D) {
-            double v = 0.0;
-            for (int i = 0; i < FFT_THREADS / 64; ++i) v += red[i][t];
-            S[((int64_t)f * D + j) * D + m0 + t] = v / (double)P;
+        col_second_read(v, z, r, col);
+        dft16<true>(v);
+#pragma unroll
+        for (int d = 0; d < 16; ++d) {
+            const double2 w = tw[(int32_t)((int64_t)a * (m0 + r + 16 * d)) & (P - 1)];
+            acc[d] = fma(v[d].x, w.x, acc[d]);  // Re(v conj(w))
+            acc[d] = fma(v[d].y, w.y, acc[d]);
         }
-        __syncthreads();
+    }
+#pragma unroll
+    for (int d = 0; d < 16; ++d) {
+        double v = acc[d];
+#pragma unroll
+        for (int off = AC / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        const int32_t m = m0 + r + 16 * d;
+        if (a0 == 0 && j < D && m < D) S[((int64_t)f * D + j) * D + m] = v / (double)P;
     }
 }
 
@@ -601,9 +590,10 @@ __global__ __launch_bounds__(PICK_THREADS) void spec_pick(const double *__restri
 // Decision per frame, one workgroup each.  Kept: the exact maximum is not on an inner
 // border, and it exceeds the best spectral score outside its +-1 window by more than the
 // bound on the spectral error
-//   bound = factor ||a||_F ||b||_F,  factor = 4 eps (10 log2(P/2) + c (124 + n_blk) + P + 18 + 2 EVAL_M),
+//   bound = factor ||a||_F ||b||_F,  factor = 4 eps (10 log2(P/2) + c (124 + n_blk) + P + 50),
 // (eps = 2^-53; ||a||_F over the frame rows, ||b||_F over the template rows; first-order
-// rounding of the row transforms, the contraction, the inverse sums and their twiddles).
+// rounding of the row transforms, the contraction, and, with room, the inverse sums: 5 eps per
+// radix-2 level, 3 for the outer twiddle and A additions).
 // The contraction's term: 5 eps per radix-2 level, 8 levels, of the transforms of a frame
 // block, of a template block and back, 4 eps for a product and n_blk additions, against
 // sum_b ||A_b|| ||B_b|| <= c ||a|| ||b||, c = ceil(COL_L / M) the blocks a frame row is in.  A kept frame
@@ -923,9 +913,10 @@ int spectral_search(const float *ref, const float *frames, int32_t W, int32_t H,
         {
             ProfScope p2("spec_eval", s);
             log2_dispatch(L.log2n2, [&](auto Lc) {
-                hipLaunchKernelGGL(spec_eval<decltype(Lc)::value>, dim3((unsigned)D, (unsigned)nf),
-                                   dim3(FFT_THREADS), sizeof(double2) * (L.N2 + 1), s, Zp, L.n_band, D, L.PS,
-                                   tw, Sf + (int64_t)f0 * D * D);
+                const int64_t lags = std::max<int64_t>(COL_KC / std::max<int64_t>(L.P / COL_L, 1), 1);  // per workgroup
+                hipLaunchKernelGGL(spec_eval<decltype(Lc)::value>,
+                                   dim3((unsigned)ceil_div(D, lags), (unsigned)nf, (unsigned)ceil_div(D, COL_L)),
+                                   dim3(COL_T), 0, s, Zp, L.n_band, D, L.PS, tw, Sf + (int64_t)f0 * D * D);
             });
         }
     }
@@ -938,7 +929,7 @@ int spectral_search(const float *ref, const float *frames, int32_t W, int32_t H,
                                                       mean, part_r, skip, s);
         const double eps = 1.1102230246251565e-16;  // 2^-53
         const double factor = 4.0 * eps * (10.0 * L.log2n2 + (double)ceil_div(COL_L, L.M) * (124.0 + L.n_blk) +
-                                           (double)L.P + 18.0 + 2.0 * EVAL_M);
+                                           (double)L.P + 50.0);
         hipLaunchKernelGGL(spec_settle, dim3((unsigned)N), dim3(PICK_THREADS), 0, s, part_r, n_tiles, cen, Sf, D, R,
                            rowsq_a, H, rowsq_b, th, factor, skip, out, fb, inf);
     }
