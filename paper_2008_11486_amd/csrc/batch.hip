@@ -101,11 +101,21 @@ struct BatchArgs {
     const StackDev *stacks;
 };
 
+// Counters of dropped values of a large stack (see add_dropped).
+constexpr int REJ_SLOTS = 64;
+constexpr int REJ_STRIDE = 8;    // 64 bytes apart
+constexpr int REJ_TILES = 4096;  // tiles from which on a stack has them
+static_assert(REJ_SLOTS <= CAL_BLOCK, "zeroed by one calibration workgroup");
+
 // ---- phase kernels: one workgroup per item ------------------------------------------------
 __global__ __launch_bounds__(CAL_BLOCK) void batch_cal(BatchArgs a, int32_t first)
 {
     const Item it = a.items[first + blockIdx.x];
     const StackDev &s = a.stacks[it.stack];
+    if (it.a == 0) {  // the counts of dropped values start at zero (a launch of its own took 4 us)
+        if (s.n_rej && threadIdx.x == 0) *s.n_rej = 0;
+        if (s.slots && threadIdx.x < REJ_SLOTS) s.slots[threadIdx.x * REJ_STRIDE] = 0;
+    }
     const int64_t i = (int64_t)it.a * CAL_BLOCK + threadIdx.x;
     if (s.W >= CAL_VEC)
         calibrate_group8(s.raw, s.rrp, s.rfp, s.bias, s.dark, s.flat, s.crp, s.cal, s.W, s.H, s.N, i);
@@ -379,9 +389,6 @@ __device__ __forceinline__ void aligned_unit(const StackDev &s, int32_t k, int32
 // the rest of the tile (16 masked frames of 6144x6160, 147000 tiles: 1820 us, of which
 // 1100 without it), so stacks of many tiles add into REJ_SLOTS counters, which batch_rejected
 // adds up after the launch.
-constexpr int REJ_SLOTS = 64;
-constexpr int REJ_STRIDE = 8;    // 64 bytes apart
-constexpr int REJ_TILES = 4096;  // tiles from which on a stack has them
 
 __device__ __forceinline__ void add_dropped(const StackDev &s, int32_t item, unsigned total)
 {
@@ -516,13 +523,6 @@ __global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(3, 3)
         if (threadIdx.x == 0 && total)
             atomicAdd(reinterpret_cast<unsigned long long *>(s.n_rej), (unsigned long long)total);
     }
-}
-
-__global__ __launch_bounds__(REJ_SLOTS) void batch_reset(BatchArgs a)
-{
-    const StackDev &s = a.stacks[blockIdx.x];
-    if (s.n_rej && threadIdx.x == 0) *s.n_rej = 0;
-    if (s.slots) s.slots[threadIdx.x * REJ_STRIDE] = 0;
 }
 
 // ---- host side ---------------------------------------------------------------------------
@@ -813,7 +813,6 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
     BatchArgs a;
     a.items = reinterpret_cast<const Item *>(base + L.items);
     a.stacks = reinterpret_cast<const StackDev *>(base + L.stacks);
-    hipLaunchKernelGGL(batch_reset, dim3(n), dim3(REJ_SLOTS), 0, s, a);
     if (L.count[IT_CAL] > 0)
         hipLaunchKernelGGL(batch_cal, dim3(L.count[IT_CAL]), dim3(CAL_BLOCK), 0, s, a, L.first[IT_CAL]);
     if (L.count[IT_MEANPART] > 0)

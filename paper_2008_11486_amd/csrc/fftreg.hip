@@ -39,7 +39,7 @@ int32_t register_small_scores(const RegPlan &p, const float *ref, const float *f
 void register_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
                      int32_t R, int32_t Rmax, const int32_t *centers, const int32_t *map, int32_t tx0, int32_t ty0,
                      int32_t tw, int32_t th, const double *mean, double *partial, double *sc, reduce_offset_t *out,
-                     hipStream_t s);
+                     hipStream_t s, const WindowMove &mv);
 
 constexpr int FFT_THREADS = 256;
 constexpr int32_t FFT_P_MAX = 8192;    // longest rows: P/2 = 4096 complex values in LDS (64 KB)
@@ -939,7 +939,7 @@ int spectral_search(const float *ref, const float *frames, int32_t W, int32_t H,
         for (int32_t r0 = 0; r0 < N; r0 += L.Ffull) {
             const int32_t n = std::min(L.Ffull, N - r0);
             register_scores(L.full, ref, frames, W, H, n, R, R, nullptr, fb + r0, tx0, ty0, tw_, th, mean,
-                            static_cast<double *>(at(L.part_f)), static_cast<double *>(at(L.sc_f)), out, s);
+                            static_cast<double *>(at(L.part_f)), static_cast<double *>(at(L.sc_f)), out, s, WindowMove{});
         }
     }
     return check_launch("search through row spectra");

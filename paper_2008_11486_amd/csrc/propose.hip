@@ -23,39 +23,12 @@ void register_mean(const float *ref, int32_t W, int32_t tx0, int32_t ty0, int32_
 void register_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
                      int32_t R, int32_t Rmax, const int32_t *centers, const int32_t *map, int32_t tx0, int32_t ty0,
                      int32_t tw, int32_t th, const double *mean, double *partial, double *sc, reduce_offset_t *out,
-                     hipStream_t s);
+                     hipStream_t s, const WindowMove &mv);
 
 // Partial-score budget of the fallback search: the number of frames it scores at once is
 // chosen so that their tile partials fit in this many bytes (at least one frame).
 constexpr size_t PROPOSE_FALLBACK_BYTES = size_t(256) << 20;
 constexpr int32_t PROPOSE_MAX_MOVES = 64;
-
-// The window maximum lies on a border strictly inside +-rmax (a border at +-rmax is also
-// the full search's border, where a move cannot help).
-__device__ __forceinline__ bool inner_border(const reduce_offset_t &o, int32_t rmax)
-{
-    const bool bx = (o.flags & REDUCE_EDGE_X) && o.dx > -rmax && o.dx < rmax;
-    const bool by = (o.flags & REDUCE_EDGE_Y) && o.dy > -rmax && o.dy < rmax;
-    return bx || by;
-}
-
-// One window move: a frame with an inner-border maximum gets its centre on that maximum
-// and its slot (map[k] = k); every other slot idles.
-__global__ void propose_walk(const reduce_offset_t *__restrict__ offs, int32_t N, int32_t rmax,
-                             int32_t *__restrict__ centres, int32_t *__restrict__ map, int32_t *__restrict__ info)
-{
-    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    const reduce_offset_t o = offs[k];
-    if (inner_border(o, rmax)) {
-        centres[2 * k] = min(max(o.dx, -rmax), rmax);
-        centres[2 * k + 1] = min(max(o.dy, -rmax), rmax);
-        map[k] = k;
-        info[k] += 1;
-    } else {
-        map[k] = -1;
-    }
-}
 
 // Fallback decision per frame (maximum still on an inner border, or a peak below
 // peak_ratio times the reference's own zero-offset score) and the flagged frames in
@@ -224,21 +197,21 @@ extern "C" int reduce_propose(const float *ref, const float *frames, int32_t W, 
     register_mean(ref, W, tx0, ty0, tw, th, mean_parts, mean, s);
     // the reference's own zero-offset score, and the narrowed search of every frame
     register_scores(L.zero, ref, ref, W, H, 1, 0, Rm, nullptr, nullptr, tx0, ty0, tw, th, mean,
-                    static_cast<double *>(at(L.part_0)), static_cast<double *>(at(L.sc_0)), auto_off, s);
+                    static_cast<double *>(at(L.part_0)), static_cast<double *>(at(L.sc_0)), auto_off, s, WindowMove{});
     double *part_s = static_cast<double *>(at(L.part_s));
     double *sc_s = static_cast<double *>(at(L.sc_s));
-    register_scores(L.small, ref, frames, W, H, N, R, Rm, cen, nullptr, tx0, ty0, tw, th, mean, part_s, sc_s, out, s);
-    // window moves: only the frames whose maximum is on an inner border are searched again
-    for (int32_t m = 0; m < max_moves; ++m) {
-        hipLaunchKernelGGL(propose_walk, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, s, out, N, Rm, cen, map, inf);
-        register_scores(L.small, ref, frames, W, H, N, R, Rm, cen, map, tx0, ty0, tw, th, mean, part_s, sc_s, out, s);
-    }
+    // window moves: only the frames whose maximum is on an inner border are searched again; the
+    // pick of one search makes the move for the next
+    const WindowMove mv{cen, map, inf};
+    for (int32_t m = 0; m <= max_moves; ++m)
+        register_scores(L.small, ref, frames, W, H, N, R, Rm, cen, m == 0 ? nullptr : map, tx0, ty0, tw, th, mean, part_s,
+                        sc_s, out, s, m < max_moves ? mv : WindowMove{});
     // fallback: the full window for the flagged frames, F of them per round
     hipLaunchKernelGGL(propose_flag, dim3(1), dim3(64), 0, s, out, N, Rm, (double)peak_ratio, auto_off, list, inf);
     for (int32_t r0 = 0; r0 < N; r0 += L.F) {
         const int32_t n = std::min(L.F, N - r0);
         register_scores(L.full, ref, frames, W, H, n, Rm, Rm, nullptr, list + r0, tx0, ty0, tw, th, mean,
-                        static_cast<double *>(at(L.part_f)), static_cast<double *>(at(L.sc_f)), out, s);
+                        static_cast<double *>(at(L.part_f)), static_cast<double *>(at(L.sc_f)), out, s, WindowMove{});
     }
     hipLaunchKernelGGL(propose_mark, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, s, list, N, out);
     return check_launch("reduce_propose");

@@ -40,6 +40,34 @@ __global__ __launch_bounds__(512) void score_tiles(ScoreArgs a)
     score_tile<K>(a, xcd_logical_id((int32_t)blockIdx.x, total), smem);
 }
 
+// The same for the slots of a map of which most or all are idle (the full search of the frames
+// that a narrower one left): as many workgroups as are resident at once deal the tiles of the
+// slots in use out among themselves, so an idle slot costs a look at the map and no
+// workgroups (idle launches over 10 frames of 4096x4096 or 19 of 1020x1020 took 14 us, now 5).
+constexpr int32_t SCORE_CUS = 256, SCORE_WAVES = 20;  // compute units; waves on each at the kernels' registers
+constexpr size_t SCORE_LDS = 160 * 1024;
+
+template <int K>
+__global__ __launch_bounds__(512) void score_tiles_list(ScoreArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int32_t per = a.n_tiles * a.G, wgs = (int32_t)gridDim.x;
+    int32_t i = (int32_t)blockIdx.x;  // this workgroup's next tile, counted from the current slot's first
+    const int lane = threadIdx.x & 63;
+    for (int32_t k0 = 0; k0 < a.N; k0 += 64) {
+        // the slots in use of 64, the same in every wave
+        uint64_t used = __ballot(k0 + lane < a.N && a.map[min(k0 + lane, a.N - 1)] >= 0);
+        for (; used; used &= used - 1) {
+            const int32_t k = k0 + __builtin_ctzll(used);
+            for (; i < per; i += wgs) {
+                score_tile<K>(a, k * per + i, smem);
+                __syncthreads();  // LDS is reused
+            }
+            i -= per;
+        }
+    }
+}
+
 // Scores of each frame from its tile partials (64 candidates per workgroup).
 // Slot k works on frame map[k] (nothing when negative), or on frame k without a map;
 // centres and offsets are indexed by frame, partials and scores by slot.
@@ -69,6 +97,45 @@ __global__ __launch_bounds__(256) void pick_offsets(const double *__restrict__ s
     if (kf < 0) return;
     const int32_t cx = centers ? centers[2 * kf] : 0, cy = centers ? centers[2 * kf + 1] : 0;
     pick_frame(scores + (int64_t)k * D * D, D, R, Rmax, cx, cy, out + kf, scratch);
+}
+
+// One window move: a frame whose maximum lies on an inner border gets its centre on that
+// maximum and its slot (map[k] = k); every other slot idles.
+__device__ __forceinline__ void move_window(const reduce_offset_t &o, int32_t k, int32_t Rmax, const WindowMove &mv)
+{
+    const bool move = inner_border(o, Rmax);
+    if (move) {
+        mv.centres[2 * k] = min(max(o.dx, -Rmax), Rmax);
+        mv.centres[2 * k + 1] = min(max(o.dy, -Rmax), Rmax);
+        mv.info[k] += 1;
+    }
+    mv.map[k] = move ? k : -1;
+}
+
+// Sums, argmax and, for a search in moving windows, the move, for windows of at most 64
+// candidates: one workgroup per slot and one launch instead of three of 4 to 5 us each.
+__global__ __launch_bounds__(64 * SUM_WAVES) void sum_pick(const double *__restrict__ partial, int32_t n_tiles, int32_t D,
+                                                           int32_t R, int32_t Rmax, const int32_t *centers,
+                                                           const int32_t *map, double *__restrict__ scores,
+                                                           reduce_offset_t *__restrict__ out, WindowMove mv)
+{
+    __shared__ double part[SUM_WAVES][64];
+    __shared__ Best scratch[SUM_WAVES];
+    const int32_t k = blockIdx.x;
+    const int32_t kf = map ? map[k] : k;
+    if (kf < 0) return;
+    const int32_t cx = centers ? centers[2 * kf] : 0, cy = centers ? centers[2 * kf + 1] : 0;
+    double *sc = scores + (int64_t)k * D * D;
+    sum_candidate_block(partial + (int64_t)k * n_tiles * D * D, n_tiles, D, R, Rmax, cx, cy, 0, sc, part);
+    pick_frame(sc, D, R, Rmax, cx, cy, out + kf, scratch);
+    if (mv.map && threadIdx.x == 0) move_window(out[kf], kf, Rmax, mv);
+}
+
+// The move alone, for larger windows.
+__global__ void move_windows(const reduce_offset_t *__restrict__ offs, int32_t N, int32_t Rmax, WindowMove mv)
+{
+    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < N) move_window(offs[k], k, Rmax, mv);
 }
 
 // ---- host side ---------------------------------------------------------------------
@@ -125,6 +192,13 @@ template <int K>
 static void launch_score(const ScoreArgs &a, const RegPlan &p, hipStream_t s)
 {
     ProfScope prof("score_tiles", s);
+    if (a.map) {
+        const int64_t per_cu = std::max<int64_t>(std::min<int64_t>(SCORE_LDS / std::max<size_t>(p.lds, 1),
+                                                                   SCORE_WAVES * 64 / p.threads), 1);
+        const int64_t wgs = std::min<int64_t>((int64_t)a.n_tiles * a.G * a.N, SCORE_CUS * per_cu);
+        hipLaunchKernelGGL(score_tiles_list<K>, dim3((unsigned)wgs), dim3(p.threads), p.lds, s, a);
+        return;
+    }
     hipLaunchKernelGGL(score_tiles<K>, dim3((unsigned)((int64_t)a.n_tiles * a.G * a.N)), dim3(p.threads), p.lds, s,
                        a);
 }
@@ -174,7 +248,7 @@ int32_t register_small_scores(const RegPlan &p, const float *ref, const float *f
 void register_scores(const RegPlan &p, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
                      int32_t R, int32_t Rmax, const int32_t *centers, const int32_t *map, int32_t tx0, int32_t ty0,
                      int32_t tw, int32_t th, const double *mean, double *partial, double *sc, reduce_offset_t *out,
-                     hipStream_t s)
+                     hipStream_t s, const WindowMove &mv)
 {
     ScoreArgs a =
         make_score_args(p, ref, frames, centers, mean, partial, W, H, N, R, Rmax, tx0, ty0, tw, th, 0x7fffffff);
@@ -191,9 +265,16 @@ void register_scores(const RegPlan &p, const float *ref, const float *frames, in
     default: launch_score<22>(a, p, s); break;
     }
     }
+    if (p.D * p.D <= 64) {
+        hipLaunchKernelGGL(sum_pick, dim3(N), dim3(64 * SUM_WAVES), 0, s, partial, a.n_tiles, p.D, R, Rmax, centers, map,
+                           sc, out, mv);
+        return;
+    }
     hipLaunchKernelGGL(sum_tiles, dim3((unsigned)ceil_div((int64_t)p.D * p.D, 64), N), dim3(64 * SUM_WAVES), 0, s,
                        partial, a.n_tiles, p.D, R, Rmax, centers, map, sc);
     hipLaunchKernelGGL(pick_offsets, dim3(N), dim3(256), 0, s, sc, p.D, R, Rmax, centers, map, out);
+    if (mv.map)
+        hipLaunchKernelGGL(move_windows, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, s, out, N, Rmax, mv);
 }
 
 int register_launch(const float *ref, const float *frames, int32_t W, int32_t H, int32_t N, int32_t R,
@@ -208,7 +289,8 @@ int register_launch(const float *ref, const float *frames, int32_t W, int32_t H,
     double *partial = reinterpret_cast<double *>(base + L.partial);
     double *sc = scores ? scores : reinterpret_cast<double *>(base + L.scores);
     register_mean(ref, W, tx0, ty0, tw, th, mean_parts, mean, s);
-    register_scores(p, ref, frames, W, H, N, R, Rmax, centers, nullptr, tx0, ty0, tw, th, mean, partial, sc, out, s);
+    register_scores(p, ref, frames, W, H, N, R, Rmax, centers, nullptr, tx0, ty0, tw, th, mean, partial, sc, out, s,
+                    WindowMove{});
     return check_launch("reduce_register");
 }
 

@@ -32,6 +32,12 @@ constexpr int MEAN_THREADS = 256;  // logical threads of the template-mean reduc
 constexpr int MEAN_ROWS = 2;       // template rows per mean part
 constexpr int MEAN_U = 4;          // columns per thread loaded together
 
+// Window moves of a search in narrowed windows (none: map NULL): centres [N][2], map [N],
+// info [N] (its number of moves counted up), by frame.
+struct WindowMove {
+    int32_t *centres, *map, *info;
+};
+
 struct ScoreArgs {
     const float *ref;
     const float *frames;     // frame k at frames + (k + (k >= skip)) * W * H
@@ -522,6 +528,15 @@ __device__ __forceinline__ void sum_candidate_block(const double *__restrict__ p
         scores_k[cand] = inside ? tot : -INFINITY;
     }
     __syncthreads();
+}
+
+// The window maximum lies on a border strictly inside +-rmax (a border at +-rmax is also
+// the full search's border, where a move cannot help).
+__device__ __forceinline__ bool inner_border(const reduce_offset_t &o, int32_t rmax)
+{
+    const bool bx = (o.flags & REDUCE_EDGE_X) && o.dx > -rmax && o.dx < rmax;
+    const bool by = (o.flags & REDUCE_EDGE_Y) && o.dy > -rmax && o.dy < rmax;
+    return bx || by;
 }
 
 // ---- scores of one frame from its partials ------------------------------------------------
