@@ -40,34 +40,6 @@ __global__ __launch_bounds__(512) void score_tiles(ScoreArgs a)
     score_tile<K>(a, xcd_logical_id((int32_t)blockIdx.x, total), smem);
 }
 
-// The same for the slots of a map of which most or all are idle (the full search of the frames
-// that a narrower one left): as many workgroups as are resident at once deal the tiles of the
-// slots in use out among themselves, so an idle slot costs a look at the map and no
-// workgroups (idle launches over 10 frames of 4096x4096 or 19 of 1020x1020 took 14 us, now 5).
-constexpr int32_t SCORE_CUS = 256, SCORE_WAVES = 20;  // compute units; waves on each at the kernels' registers
-constexpr size_t SCORE_LDS = 160 * 1024;
-
-template <int K>
-__global__ __launch_bounds__(512) void score_tiles_list(ScoreArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int32_t per = a.n_tiles * a.G, wgs = (int32_t)gridDim.x;
-    int32_t i = (int32_t)blockIdx.x;  // this workgroup's next tile, counted from the current slot's first
-    const int lane = threadIdx.x & 63;
-    for (int32_t k0 = 0; k0 < a.N; k0 += 64) {
-        // the slots in use of 64, the same in every wave
-        uint64_t used = __ballot(k0 + lane < a.N && a.map[min(k0 + lane, a.N - 1)] >= 0);
-        for (; used; used &= used - 1) {
-            const int32_t k = k0 + __builtin_ctzll(used);
-            for (; i < per; i += wgs) {
-                score_tile<K>(a, k * per + i, smem);
-                __syncthreads();  // LDS is reused
-            }
-            i -= per;
-        }
-    }
-}
-
 // Scores of each frame from its tile partials (64 candidates per workgroup).
 // Slot k works on frame map[k] (nothing when negative), or on frame k without a map;
 // centres and offsets are indexed by frame, partials and scores by slot.
@@ -192,13 +164,6 @@ template <int K>
 static void launch_score(const ScoreArgs &a, const RegPlan &p, hipStream_t s)
 {
     ProfScope prof("score_tiles", s);
-    if (a.map) {
-        const int64_t per_cu = std::max<int64_t>(std::min<int64_t>(SCORE_LDS / std::max<size_t>(p.lds, 1),
-                                                                   SCORE_WAVES * 64 / p.threads), 1);
-        const int64_t wgs = std::min<int64_t>((int64_t)a.n_tiles * a.G * a.N, SCORE_CUS * per_cu);
-        hipLaunchKernelGGL(score_tiles_list<K>, dim3((unsigned)wgs), dim3(p.threads), p.lds, s, a);
-        return;
-    }
     hipLaunchKernelGGL(score_tiles<K>, dim3((unsigned)((int64_t)a.n_tiles * a.G * a.N)), dim3(p.threads), p.lds, s,
                        a);
 }

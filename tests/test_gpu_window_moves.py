@@ -1,6 +1,5 @@
 """The narrowed search's rounds on the device (sum, pick and move in one launch for windows of at
-most 64 candidates, by themselves for larger ones; the full search of the flagged frames by a
-bounded number of workgroups) against the same decisions taken on the host, byte for byte:
+most 64 candidates, by themselves for larger ones) against the same decisions taken on the host, byte for byte:
 windows on both sides of 64 candidates, no moves and several, most frames flagged and few."""
 import numpy as np
 import pytest
