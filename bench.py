@@ -854,7 +854,7 @@ def streaming_wide(torch, rd, inp, reps=10, traffic_path=os.path.join(ROOT, "pro
     res = {"workload": f"{N} frames {W}x{H} at their true shifts (+-64 px), overlap {w}x{h}, bad pixels 0.1%; "
                        f"deep combine: {ND} frames {SD}x{SD}; timed after 0.5 s of warm-up"}
     byts = {"calibrate": N * W * H * (2 + 4) + 8 * W * H, "shift": N * w * h * (4 + 4), "combine": N * w * h * 4 + w * h * 4,
-            # rows: frame read, row-pass result written; columns: that result read, output written
+            # one pass: frame read, output written
             "shift_spline": N * 4 * (H * W + h * w), "combine_deep": (ND + 1) * SD * SD * 4,
             # the map (from L2 after the first frame) and the marked values
             "mask_shifted": H * W + int(torch.isnan(al).sum()) * 4, "combine_missing": N * w * h * 4 + w * h * 4}
