@@ -153,7 +153,8 @@ __global__ __launch_bounds__(BATCH_THREADS) void batch_score(BatchArgs a, int32_
     score_tile<K>(s.sa, it.a, smem);
 }
 
-__global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void batch_score_small(BatchArgs a, int32_t first)
+__global__ __launch_bounds__(SMALL_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void batch_score_small(
+    BatchArgs a, int32_t first)
 {
     __shared__ double red[SMALL_LDS_DOUBLES];
     const Item it = a.items[first + blockIdx.x];
@@ -408,7 +409,8 @@ __global__ __launch_bounds__(REJ_SLOTS) void batch_rejected(BatchArgs a)
 }
 
 template <int MAXV, bool MASK>
-__global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(MAXV == 16 ? (MASK ? 7 : 8) : 5))) void batch_fused(BatchArgs a, int32_t first, int32_t count)
+__global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(MAXV == 16 ? (MASK ? 7 : 8) : 5)))
+void batch_fused(BatchArgs a, int32_t first, int32_t count)
 {
     extern __shared__ float tile[];  // [MAXV][FUSE_ROWS][FUSE_COLS]
     __shared__ int32_t queue[FUSE_PX];  // pixels that drop values
@@ -510,7 +512,8 @@ __global__ __launch_bounds__(256) void batch_mask(BatchArgs a, int32_t first, in
 // Stacks of 49 - 128 frames (MISS: with a bad-pixel map): the block's columns with all their
 // values in registers (see combine_deep); MAXV covers the deepest stack of the phase.
 template <int MAXV, bool MISS>
-__global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(3, 3))) void batch_comb_deep(BatchArgs a, int32_t first)
+__global__ __launch_bounds__(COMB_TILE) __attribute__((amdgpu_waves_per_eu(3, 3))) void batch_comb_deep(
+    BatchArgs a, int32_t first)
 {
     const Item it = a.items[first + blockIdx.x];
     const StackDev &s = a.stacks[it.stack];
@@ -593,8 +596,9 @@ static int validate(const reduce_stack_t *stacks, int32_t n)
 // asked for, or where reduce_register takes them for its N - 1 searched frames.
 static bool spectral(const reduce_stack_t &s)
 {
-    return s.N > 1 && (s.search == REDUCE_SEARCH_SPECTRAL || (spectra_pay(s.W, s.H, s.N - 1, s.radius) &&
-                                                              spectral_ws(s.W, s.H, s.N - 1, s.radius, SPEC_ROUND_BYTES) != 0));
+    return s.N > 1 && (s.search == REDUCE_SEARCH_SPECTRAL ||
+                       (spectra_pay(s.W, s.H, s.N - 1, s.radius) &&
+                        spectral_ws(s.W, s.H, s.N - 1, s.radius, SPEC_ROUND_BYTES) != 0));
 }
 
 static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)

@@ -405,8 +405,8 @@ __device__ __forceinline__ void col_table(double2 *wl)
 
 // Transforms of the template's blocks: workgroup (column tile, block); B holds the row
 // spectra of the th template rows.
-__global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_tmpl(ColArgs a, const double2 *__restrict__ B,
-                                                                                     int32_t th)
+__global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_tmpl(
+    ColArgs a, const double2 *__restrict__ B, int32_t th)
 {
     __shared__ double2 z[COL_L * COL_KC], wl[COL_L];
     const int t = threadIdx.x, col = t & (COL_KC - 1), r = t / COL_KC;
@@ -501,8 +501,9 @@ __global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) v
 // and a recurrence for the twiddles, 131 lags of 15 frames at P = 8192 took 698 us, now 86, and
 // 35 lags of 85 frames at P = 512 to 4096 in six calls 202, now 66.
 template <int LOG2N2>
-__global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_eval(const double2 *__restrict__ Zp, int32_t n_part, int32_t D,
-                                                   int32_t PS, const double2 *__restrict__ tw, double *__restrict__ S)
+__global__ __launch_bounds__(COL_T) __attribute__((amdgpu_waves_per_eu(2, 2))) void spec_eval(
+    const double2 *__restrict__ Zp, int32_t n_part, int32_t D, int32_t PS, const double2 *__restrict__ tw,
+    double *__restrict__ S)
 {
     constexpr int32_t N2 = 1 << LOG2N2, P = 2 * N2, A = P > COL_L ? P / COL_L : 1;
     constexpr int SP = COL_L > P ? COL_L / P : 1;  // shorter spectra: every SP-th input

@@ -114,7 +114,8 @@ bool reg_plan_from_shape(int32_t W, int32_t H, int32_t R, int32_t Rmax, const Re
 
 bool reg_plan_small(int32_t W, int32_t H, int32_t R, int32_t Rmax, RegPlan *out)
 {
-    constexpr int32_t COLS = 256, CH = 15, ROWS = 240;  // columns and most rows of a tile (SMALL_COLS, SMALL_ROWS); rows in steps of CH
+    // columns and most rows of a tile (SMALL_COLS, SMALL_ROWS), rows in steps of CH
+    constexpr int32_t COLS = 256, CH = 15, ROWS = 240;
     RegPlan p{};
     p.D = 2 * R + 1;
     if (p.D > 5) return false;
@@ -129,7 +130,7 @@ bool reg_plan_small(int32_t W, int32_t H, int32_t R, int32_t Rmax, RegPlan *out)
     p.threads = COLS;
     p.TX = COLS;
     p.NXB = 1;
-    p.TY = CH;  // rows per staged chunk
+    p.TY = CH;
     // tile rows: the most (shorter tiles were measured slower, single-frame calls included)
     p.n_xchunks = (int32_t)ceil_div(tw, COLS);
     p.BR = ROWS;
