@@ -123,7 +123,7 @@ KERNEL_SYMBOLS = {"batch_score": "batch_score", "batch_shift": "batch_shift", "b
                   "calibrate": "calibrate_",
                   "shift": "shift_kernel",
                   # a list: every part must appear in the kernel name
-                  "combine": ["combine_cols<", "false>"], "combine_deep": "combine_deep<false>",
+                  "combine": ["combine_cols<", "false>"], "combine_deep": ["combine_deep<", "false>"],
                   "combine_missing": ["combine_cols<", "true>"], "mask_shifted": "mask_shifted",
                   "shift_spline": ("spline_rows", "spline_cols")}  # one call = both passes
 # counter runs of builds that do the same in one kernel
