@@ -29,7 +29,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -879,7 +878,7 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
         constexpr int V = decltype(maxv)::value;
         if (L.count[phase] > 0)
             hipLaunchKernelGGL((batch_fused<V, decltype(masked)::value>), dim3(L.count[phase]), dim3(COMB_TILE),
-                               sizeof(float) * FUSE_PX * V, s, a, L.first[phase], getenv("NOXCD") ? 0 : L.count[phase]);
+                               sizeof(float) * FUSE_PX * V, s, a, L.first[phase], L.count[phase]);
     };
     fused(IT_FUSE16, std::integral_constant<int, 16>{}, std::false_type{});
     fused(IT_FUSE32, std::integral_constant<int, 32>{}, std::false_type{});
