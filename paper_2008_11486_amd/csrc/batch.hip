@@ -535,6 +535,8 @@ static int64_t fuse_tiles(int32_t W, int32_t H) { return ceil_div(W, FUSE_COLS) 
 
 struct StackLayout {
     RegPlan plan;
+    bool spec;      // registers through row spectra, laid out as fft
+    FftLayout fft;
     size_t cal, al, mean_parts, mean, partial, scores, soffs, rect, slots;  // slots: 0 for none
     int32_t count[N_PHASES];
 };
@@ -591,15 +593,10 @@ static int validate(const reduce_stack_t *stacks, int32_t n)
     return REDUCE_OK;
 }
 
-// The stack registers through row spectra (a stack of one frame has nothing to register):
-// asked for, or where reduce_register takes them for its N - 1 searched frames.
-static bool spectral(const reduce_stack_t &s)
-{
-    return s.N > 1 && (s.search == REDUCE_SEARCH_SPECTRAL ||
-                       (spectra_pay(s.W, s.H, s.N - 1, s.radius) &&
-                        spectral_ws(s.W, s.H, s.N - 1, s.radius, SPEC_ROUND_BYTES) != 0));
-}
-
+// A stack registers through row spectra where it asks for them, or where reduce_register takes
+// them for its N - 1 searched frames (a stack of one frame has nothing to register).  The rule and the
+// launch shapes read the tuner's table, which another thread may change at any time, so they
+// are settled here once per call and everything that follows goes by the layout.
 static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
 {
     BatchLayout L;
@@ -625,13 +622,14 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
         off += al(sizeof(double) * n_mean_parts);
         sl.mean = off;
         off += 256;
-        const bool spec = spectral(s);
-        const int32_t ndir = spec ? 0 : nreg;  // frames of the direct search
+        sl.spec = nreg > 0 && (s.search == REDUCE_SEARCH_SPECTRAL || spectra_pay(s.W, s.H, nreg, s.radius)) &&
+                  fft_layout(s.W, s.H, nreg, s.radius, SPEC_ROUND_BYTES, &sl.fft);
+        const int32_t ndir = sl.spec ? 0 : nreg;  // frames of the direct search
         sl.partial = off;
         off += al(sizeof(double) * (size_t)std::max(ndir, 0) * p.n_tiles * p.D * p.D);
         sl.scores = off;
         off += al(sizeof(double) * (size_t)std::max(ndir, 0) * p.D * p.D);
-        if (spec) L.spec_ws = std::max(L.spec_ws, spectral_ws(s.W, s.H, s.N - 1, s.radius, SPEC_ROUND_BYTES));
+        if (sl.spec) L.spec_ws = std::max(L.spec_ws, sl.fft.total);
         sl.soffs = off;
         off += al(sizeof(float) * 2 * s.N);
         sl.rect = off;
@@ -843,12 +841,12 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
     // the stacks that register through row spectra, one after the other in the shared space
     for (int32_t i = 0; i < n; ++i) {
         const reduce_stack_t &st = stacks[i];
-        if (!spectral(st)) continue;
+        if (!L.st[i].spec) continue;
         ProfScope prof("batch_spectral", s);
         const float *cal = reinterpret_cast<const float *>(base + L.st[i].cal);
-        const int rc = spectral_search(cal + (int64_t)st.ref_index * st.W * st.H, cal, st.W, st.H, st.N - 1,
-                                       st.radius, st.ref_index, st.offsets, nullptr, nullptr, base + L.spec,
-                                       SPEC_ROUND_BYTES, s);
+        const int rc = spectral_search(L.st[i].fft, cal + (int64_t)st.ref_index * st.W * st.H, cal, st.W, st.H,
+                                       st.N - 1, st.radius, st.ref_index, st.offsets, nullptr, nullptr,
+                                       base + L.spec, s);
         if (rc != REDUCE_OK) return rc;
     }
     hipLaunchKernelGGL(batch_rect, dim3(L.count[IT_RECT]), dim3(64), 0, s, a, L.first[IT_RECT]);
@@ -917,10 +915,13 @@ extern "C" int reduce_stack_batch(const reduce_stack_t *stacks, int32_t n, void 
         return fail(REDUCE_ERR_WORKSPACE, "reduce_stack_batch: workspace needs " + std::to_string(L.total) + " bytes");
     hipStream_t s = as_stream(stream);
 
-    // the host image of the descriptors is rebuilt only when the stacks or their launch
-    // shapes change; it is uploaded into the workspace on every call
+    // the host image of the descriptors is rebuilt only when the stacks, their launch
+    // shapes or their searches change; it is uploaded into the workspace on every call
     uint64_t h = fnv1a(stacks, sizeof(reduce_stack_t) * (size_t)n);
-    for (const StackLayout &sl : L.st) h = fnv1a(&sl.plan, sizeof(RegPlan), h);
+    for (const StackLayout &sl : L.st) {
+        h = fnv1a(&sl.plan, sizeof(RegPlan), h);
+        h = fnv1a(&sl.spec, sizeof(sl.spec), h);
+    }
     h = fnv1a(&L.total, sizeof(L.total), h);
     std::lock_guard<std::mutex> lk(g_batch_mu);
     BatchEntry &e = g_entries[ws];

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include "reduce.h"
+#include "register_plan.h"
 
 namespace rd {
 
@@ -20,12 +21,24 @@ constexpr size_t SPEC_ROUND_BYTES_PLAIN = size_t(512) << 20;
 // planes asked for) of N frames goes through row spectra.
 bool spectra_pay(int32_t W, int32_t H, int32_t N, int32_t R);
 
-// Workspace bytes of spectral_search (0: not for these sizes).
-size_t spectral_ws(int32_t W, int32_t H, int32_t N, int32_t R, size_t round_bytes);
+// Sizes, launch plans and workspace offsets of one search.  The plans come from the tuner's
+// table, which another thread may change at any time, so a call makes its layout once, checks
+// its workspace against it and searches with it.
+struct FftLayout {
+    int32_t P, N2, log2n2, PS, D, Dg, n_grp, M, n_blk, bpb, n_band, n_kt, F;
+    RegPlan refine, full;
+    int32_t Ffull;
+    size_t tw, mean_parts, mean, Bt, rowsq_b, A, rowsq_a, Zp, S_fft, cen, info, fb;
+    size_t part_r, part_f, sc_f, total;
+};
+
+// The layout of a search of N frames (false: not for these sizes).
+bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, size_t round_bytes, FftLayout *L);
 
 // N frames k + (k >= skip), k < N, of `frames` against ref; out and info are indexed by frame,
-// scores by k.  Sizes as spectral_ws accepts them, ws of that many bytes.
-int spectral_search(const float *ref, const float *frames, int32_t W, int32_t H, int32_t N, int32_t R, int32_t skip,
-                    reduce_offset_t *out, double *scores, int32_t *info, void *ws, size_t round_bytes, hipStream_t s);
+// scores by k.  L as fft_layout made it for these sizes, ws of L.total bytes.
+int spectral_search(const FftLayout &L, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
+                    int32_t R, int32_t skip, reduce_offset_t *out, double *scores, int32_t *info, void *ws,
+                    hipStream_t s);
 
 }  // namespace rd

@@ -706,21 +706,14 @@ __global__ __launch_bounds__(PICK_THREADS) void spec_settle(const double *__rest
 // ---- host side ---------------------------------------------------------------------------
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-struct FftLayout {
-    int32_t P, N2, log2n2, PS, D, Dg, n_grp, M, n_blk, bpb, n_band, n_kt, F;
-    RegPlan refine, full;
-    int32_t Ffull;
-    size_t tw, mean_parts, mean, Bt, rowsq_b, A, rowsq_a, Zp, S_fft, cen, info, fb;
-    size_t part_r, part_f, sc_f, total;
-};
-
-static bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, size_t round_bytes, FftLayout *L)
+bool fft_layout(int32_t W, int32_t H, int32_t N, int32_t R, size_t round_bytes, FftLayout *L)
 {
-    const int32_t tw = W - 2 * R, th = H - 2 * R;
-    if (tw < 1 || th < 1) return false;
+    if (W < 1 || H < 1 || N < 1 || N > 65535 || R < 1 || W - 2 * R < 1 || H - 2 * R < 1 || W > FFT_P_MAX ||
+        2 * R + 1 > 1024)
+        return false;
+    const int32_t th = H - 2 * R;
     int32_t P = 64;
     while (P < W) P <<= 1;
-    if (P > FFT_P_MAX) return false;
     L->P = P;
     L->N2 = P / 2;
     L->log2n2 = 0;
@@ -836,21 +829,10 @@ bool spectra_pay(int32_t W, int32_t H, int32_t N, int32_t R)
     return direct > 1.25 * spectral;
 }
 
-size_t spectral_ws(int32_t W, int32_t H, int32_t N, int32_t R, size_t round_bytes)
+int spectral_search(const FftLayout &L, const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
+                    int32_t R, int32_t skip, reduce_offset_t *out, double *scores, int32_t *info, void *ws,
+                    hipStream_t s)
 {
-    if (W < 1 || H < 1 || N < 1 || N > 65535 || R < 1 || W - 2 * R < 1 || H - 2 * R < 1 || W > FFT_P_MAX ||
-        2 * R + 1 > 1024)
-        return 0;
-    FftLayout L;
-    return fft_layout(W, H, N, R, round_bytes, &L) ? L.total : 0;
-}
-
-int spectral_search(const float *ref, const float *frames, int32_t W, int32_t H, int32_t N, int32_t R, int32_t skip,
-                    reduce_offset_t *out, double *scores, int32_t *info, void *ws, size_t round_bytes, hipStream_t s)
-{
-    FftLayout L;
-    if (!fft_layout(W, H, N, R, round_bytes, &L))
-        return fail(REDUCE_ERR_UNSUPPORTED, "search through row spectra: no launch shape for these sizes");
     unsigned char *b = static_cast<unsigned char *>(ws);
     auto at = [&](size_t off) { return static_cast<void *>(b + off); };
     double2 *tw = static_cast<double2 *>(at(L.tw));
@@ -952,7 +934,8 @@ using namespace rd;
 
 extern "C" size_t reduce_register_fft_ws(int32_t W, int32_t H, int32_t N, int32_t radius)
 {
-    return spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES);
+    FftLayout L;
+    return fft_layout(W, H, N, radius, SPEC_ROUND_BYTES, &L) ? L.total : 0;
 }
 
 extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_t W, int32_t H, int32_t N,
@@ -962,10 +945,10 @@ extern "C" int reduce_register_fft(const float *ref, const float *frames, int32_
     if (!ref || !frames || !out) return fail(REDUCE_ERR_NULL, "reduce_register_fft: NULL buffer");
     const int c = fft_check(W, H, N, radius, "reduce_register_fft");
     if (c != REDUCE_OK) return c;
-    const size_t need = spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES);
-    if (need == 0) return fail(REDUCE_ERR_UNSUPPORTED, "reduce_register_fft: no launch shape for these sizes");
-    if (!ws || ws_bytes < need)
-        return fail(REDUCE_ERR_WORKSPACE, "reduce_register_fft: workspace needs " + std::to_string(need) + " bytes");
-    return spectral_search(ref, frames, W, H, N, radius, 0x7fffffff, out, scores, info, ws, SPEC_ROUND_BYTES,
-                           as_stream(stream));
+    FftLayout L;
+    if (!fft_layout(W, H, N, radius, SPEC_ROUND_BYTES, &L))
+        return fail(REDUCE_ERR_UNSUPPORTED, "reduce_register_fft: no launch shape for these sizes");
+    if (!ws || ws_bytes < L.total)
+        return fail(REDUCE_ERR_WORKSPACE, "reduce_register_fft: workspace needs " + std::to_string(L.total) + " bytes");
+    return spectral_search(L, ref, frames, W, H, N, radius, 0x7fffffff, out, scores, info, ws, as_stream(stream));
 }

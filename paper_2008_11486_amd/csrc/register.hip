@@ -272,8 +272,10 @@ extern "C" size_t reduce_register_ws(int32_t W, int32_t H, int32_t N, int32_t ra
     const RegPlan p = reg_plan(W, H, radius, radius_max);
     if (p.D == 0) return 0;
     size_t need = register_ws_bytes(p, N);
-    if (radius == radius_max && spectra_pay(W, H, N, radius))
-        need = std::max(need, spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES_PLAIN));
+    FftLayout L;
+    if (radius == radius_max && spectra_pay(W, H, N, radius) &&
+        fft_layout(W, H, N, radius, SPEC_ROUND_BYTES_PLAIN, &L))
+        need = std::max(need, L.total);
     return need;
 }
 
@@ -319,10 +321,11 @@ extern "C" int reduce_register(const float *ref, const float *frames, int32_t W,
     // other templates are summed directly, and so is a call whose workspace holds the
     // direct search only.
     if (!scores && !centers && !tmpl && radius == radius_max && spectra_pay(W, H, N, radius)) {
-        const size_t spec = spectral_ws(W, H, N, radius, SPEC_ROUND_BYTES_PLAIN);
-        if (spec != 0 && ws_bytes >= spec && (reinterpret_cast<uintptr_t>(ws) & 15u) == 0)
-            return spectral_search(ref, frames, W, H, N, radius, 0x7fffffff, out, nullptr, nullptr, ws,
-                                   SPEC_ROUND_BYTES_PLAIN, as_stream(stream));
+        FftLayout L;
+        if (fft_layout(W, H, N, radius, SPEC_ROUND_BYTES_PLAIN, &L) && ws_bytes >= L.total &&
+            (reinterpret_cast<uintptr_t>(ws) & 15u) == 0)
+            return spectral_search(L, ref, frames, W, H, N, radius, 0x7fffffff, out, nullptr, nullptr, ws,
+                                   as_stream(stream));
     }
     return register_launch(ref, frames, W, H, N, radius, radius_max, centers, t[0], t[1], t[2], t[3], out, scores,
                            ws, p, as_stream(stream));
