@@ -270,7 +270,9 @@ int reduce_combine(const float *aligned, int32_t w, int32_t h, int32_t N, float 
  * bad-pixel map masks its aligned values as reduce_mask_shifted and combines with
  * missing = 1.  A stack with search = REDUCE_SEARCH_SPECTRAL (radius >= 1, W <= 8192)
  * registers as reduce_register_fft of its calibrated frames, whatever its size, instead of
- * as reduce_register (the same offsets; the choice is the caller's or the tuner's).  The stack
+ * as reduce_register (the same offsets; the choice is the caller's or the tuner's).  A
+ * workspace that holds the direct sums only is accepted and the other stacks searched with
+ * them.  The stack
  * descriptors are copied into the workspace at every call (the host image is kept
  * per workspace and rebuilt, after synchronising `stream`, when the descriptors
  * change).  Calls sharing one workspace must not overlap.  Errors: as the stage-wise

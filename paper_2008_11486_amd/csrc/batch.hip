@@ -34,6 +34,7 @@
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "calibrate_core.h"
@@ -593,11 +594,12 @@ static int validate(const reduce_stack_t *stacks, int32_t n)
     return REDUCE_OK;
 }
 
-// A stack registers through row spectra where it asks for them, or where reduce_register takes
-// them for its N - 1 searched frames (a stack of one frame has nothing to register).  The rule and the
-// launch shapes read the tuner's table, which another thread may change at any time, so they
-// are settled here once per call and everything that follows goes by the layout.
-static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
+// A stack registers through row spectra where it asks for them and, by_rule, where
+// reduce_register takes them for its N - 1 searched frames (a stack of one frame has nothing to
+// register).  The rule and the launch shapes read the tuner's table, which another thread may change at
+// any time, so they are settled here once per call and everything that follows goes by the
+// layout.
+static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n, bool by_rule)
 {
     BatchLayout L;
     size_t off = 0;
@@ -622,7 +624,8 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n)
         off += al(sizeof(double) * n_mean_parts);
         sl.mean = off;
         off += 256;
-        sl.spec = nreg > 0 && (s.search == REDUCE_SEARCH_SPECTRAL || spectra_pay(s.W, s.H, nreg, s.radius)) &&
+        sl.spec = nreg > 0 &&
+                  (s.search == REDUCE_SEARCH_SPECTRAL || (by_rule && spectra_pay(s.W, s.H, nreg, s.radius))) &&
                   fft_layout(s.W, s.H, nreg, s.radius, SPEC_ROUND_BYTES, &sl.fft);
         const int32_t ndir = sl.spec ? 0 : nreg;  // frames of the direct search
         sl.partial = off;
@@ -897,7 +900,7 @@ extern "C" size_t reduce_stack_batch_ws(const reduce_stack_t *stacks, int32_t n)
 {
     if (!stacks || n < 1) return 0;
     if (validate(stacks, n) != REDUCE_OK) return 0;
-    return layout_of(stacks, n).total;
+    return layout_of(stacks, n, true).total;
 }
 
 extern "C" int reduce_stack_batch(const reduce_stack_t *stacks, int32_t n, void *ws, size_t ws_bytes, void *stream)
@@ -906,7 +909,11 @@ extern "C" int reduce_stack_batch(const reduce_stack_t *stacks, int32_t n, void 
     if (n < 1) return fail(REDUCE_ERR_SHAPE, "reduce_stack_batch: no stacks");
     const int v = validate(stacks, n);
     if (v != REDUCE_OK) return v;
-    const BatchLayout L = layout_of(stacks, n);
+    BatchLayout L = layout_of(stacks, n, true);
+    if (ws_bytes < L.total) {  // one that holds the direct sums is searched with them, as by reduce_register
+        BatchLayout direct = layout_of(stacks, n, false);
+        if (direct.total < L.total) L = std::move(direct);
+    }
     if (L.n_items < 0) return fail(REDUCE_ERR_UNSUPPORTED, "reduce_stack_batch: too many work items");
     for (int q = 0; q < N_PHASES; ++q)
         if (L.count[q] > 0x7fffffff / 2) return fail(REDUCE_ERR_UNSUPPORTED, "reduce_stack_batch: too many items");

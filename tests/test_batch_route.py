@@ -45,3 +45,17 @@ def test_a_table_cleared_during_the_call_changes_nothing(tmp_path):
     rec.rec_on_copy(hook)
     assert call() == tuned
     """)
+
+
+def test_a_workspace_of_the_direct_sums_is_accepted(tmp_path):
+    launch_recorder.run(tmp_path, SETUP.format(path=str(tmp_path / "t.json"), rows=1) + """
+    direct = int(L.reduce_stack_batch_ws(arr, 2))  # with the tuned shape
+    rd.tune_clear()
+    assert direct < int(L.reduce_stack_batch_ws(arr, 2))
+    assert L.reduce_stack_batch(arr, 2, ctypes.c_void_p(b), direct, None) == rd.OK, L.reduce_last_error()
+    assert launches() == tuned
+    assert L.reduce_stack_batch(arr, 2, ctypes.c_void_p(b), direct - 1, None) == rd.ERR_WORKSPACE
+    assert str(direct).encode() in L.reduce_last_error() and launches() == []
+    arr[1].search = 1  # asked for: its workspace is needed
+    assert L.reduce_stack_batch(arr, 2, ctypes.c_void_p(b), direct, None) == rd.ERR_WORKSPACE
+    """)
