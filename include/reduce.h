@@ -263,7 +263,8 @@ int reduce_combine(const float *aligned, int32_t w, int32_t h, int32_t N, float 
  *   out       device float, room for W*H values; the combined image, dense [h][w]
  *   out_rect  device int32[4] {x0, y0, w, h} of the overlap in reference pixels
  *   offsets   device reduce_offset_t [N]
- *   n_rej     device int64[1] (values dropped by the clip) or NULL
+ *   n_rej     device int64[1] (values dropped by the clip; stacks that share one get their
+ *             sum) or NULL
  * ws: device workspace of reduce_stack_batch_ws(stacks, n) bytes (calibrated frames,
  * partial scores, the work-item table); query again after tuning.  The stack
  * A stack with a bias frame calibrates as reduce_calibrate with it; a stack with a

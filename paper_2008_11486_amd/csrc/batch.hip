@@ -405,7 +405,8 @@ __global__ __launch_bounds__(REJ_SLOTS) void batch_rejected(BatchArgs a)
     unsigned long long v = s.slots[threadIdx.x * REJ_STRIDE];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (threadIdx.x == 0) *s.n_rej = (int64_t)v;
+    // added: stacks may share a count (all are zeroed before any of them adds)
+    if (threadIdx.x == 0 && v) atomicAdd(reinterpret_cast<unsigned long long *>(s.n_rej), v);
 }
 
 template <int MAXV, bool MASK>
