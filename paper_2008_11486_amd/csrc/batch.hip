@@ -875,19 +875,21 @@ static int launch_phases(const reduce_stack_t *stacks, int32_t n, void *ws, cons
                                    dim3(COMB_TILE), 0, s, a, L.first[IT_COMBMISS]);
             });
     }
-    ProfScope prof("batch_fused", s);
-    const auto fused = [&](int phase, auto maxv, auto masked) {
-        constexpr int V = decltype(maxv)::value;
-        if (L.count[phase] > 0)
-            hipLaunchKernelGGL((batch_fused<V, decltype(masked)::value>), dim3(L.count[phase]), dim3(COMB_TILE),
-                               sizeof(float) * FUSE_PX * V, s, a, L.first[phase], L.count[phase]);
-    };
-    fused(IT_FUSE16, std::integral_constant<int, 16>{}, std::false_type{});
-    fused(IT_FUSE32, std::integral_constant<int, 32>{}, std::false_type{});
-    fused(IT_FUSE48, std::integral_constant<int, 48>{}, std::false_type{});
-    fused(IT_FUSE16M, std::integral_constant<int, 16>{}, std::true_type{});
-    fused(IT_FUSE32M, std::integral_constant<int, 32>{}, std::true_type{});
-    fused(IT_FUSE48M, std::integral_constant<int, 48>{}, std::true_type{});
+    if (std::any_of(L.count + IT_FUSE16, L.count + N_PHASES, [](int32_t c) { return c > 0; })) {
+        ProfScope prof("batch_fused", s);
+        const auto fused = [&](int phase, auto maxv, auto masked) {
+            constexpr int V = decltype(maxv)::value;
+            if (L.count[phase] > 0)
+                hipLaunchKernelGGL((batch_fused<V, decltype(masked)::value>), dim3(L.count[phase]), dim3(COMB_TILE),
+                                   sizeof(float) * FUSE_PX * V, s, a, L.first[phase], L.count[phase]);
+        };
+        fused(IT_FUSE16, std::integral_constant<int, 16>{}, std::false_type{});
+        fused(IT_FUSE32, std::integral_constant<int, 32>{}, std::false_type{});
+        fused(IT_FUSE48, std::integral_constant<int, 48>{}, std::false_type{});
+        fused(IT_FUSE16M, std::integral_constant<int, 16>{}, std::true_type{});
+        fused(IT_FUSE32M, std::integral_constant<int, 32>{}, std::true_type{});
+        fused(IT_FUSE48M, std::integral_constant<int, 48>{}, std::true_type{});
+    }
     if (std::any_of(L.st.begin(), L.st.end(), [](const StackLayout &l) { return l.slots != 0; }))
         hipLaunchKernelGGL(batch_rejected, dim3(n), dim3(REJ_SLOTS), 0, s, a);
     return check_launch("reduce_stack_batch");
