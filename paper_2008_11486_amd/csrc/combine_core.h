@@ -127,25 +127,6 @@ __device__ __forceinline__ unsigned clip_tile(const float *tile, int64_t p0, int
     return dropped_here;
 }
 
-// Dispatch on the lanes per column; MAXV covers N <= COMB_MAX_N.
-template <typename F>
-__device__ __forceinline__ void lanes_dispatch(int L, int32_t N, F &&f)
-{
-    switch (L) {
-    case 1:
-        if (N <= 16) f(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
-        else if (N <= 32) f(std::integral_constant<int, 1>{}, std::integral_constant<int, 32>{});
-        else f(std::integral_constant<int, 1>{}, std::integral_constant<int, 48>{});
-        break;
-    case 2: f(std::integral_constant<int, 2>{}, std::integral_constant<int, 24>{}); break;
-    case 4: f(std::integral_constant<int, 4>{}, std::integral_constant<int, 12>{}); break;
-    case 8: f(std::integral_constant<int, 8>{}, std::integral_constant<int, 6>{}); break;
-    case 16: f(std::integral_constant<int, 16>{}, std::integral_constant<int, 3>{}); break;
-    case 32: f(std::integral_constant<int, 32>{}, std::integral_constant<int, 2>{}); break;
-    default: f(std::integral_constant<int, 64>{}, std::integral_constant<int, 1>{}); break;
-    }
-}
-
 // Sum of one unsigned per thread over a 256-thread workgroup.
 __device__ __forceinline__ unsigned block_sum_u32(unsigned v)
 {
@@ -309,8 +290,13 @@ __device__ __forceinline__ void clip_narrow(ClipState &c, double m, double thr)
     c.lo = fmaxf(c.lo, -clip_end(-m, thr));
 }
 
-// First iteration of a column: true, with the mean, when it settles there (nothing drops, or
-// no iterations are asked for).
+// The clip of one column, its values read through x(i).  The arithmetic is that of clip_column
+// with one lane (sums in frame order in double, m = s / n, q = sum of (x - m)^2, threshold
+// ksigma * sqrt(q / n), drop |x - m| > threshold); when an iteration drops nothing (the
+// largest |x - m| tells) its own mean is the final mean.
+//
+// First iteration: true, with the mean, when the column settles there (nothing drops, or no
+// iterations are asked for).
 template <int MAXV, bool MISS, typename X>
 __device__ __forceinline__ bool clip_first(X x, int32_t N, double ksigma, int32_t max_iters, ClipState &c,
                                            double &m, double &thr)
@@ -327,7 +313,7 @@ __device__ __forceinline__ bool clip_first(X x, int32_t N, double ksigma, int32_
 }
 
 // The rest of the clip of a column whose first iteration (mean m, threshold thr, all values
-// present in c) drops values.
+// present in c) drops values.  c.lo, c.hi bound the kept values afterwards.
 template <int MAXV, typename X>
 __device__ __forceinline__ float clip_rest(X x, int32_t N, double ksigma, int32_t max_iters, ClipState &c, double m,
                                            double thr, unsigned &dropped)
@@ -347,20 +333,6 @@ __device__ __forceinline__ float clip_rest(X x, int32_t N, double ksigma, int32_
     return (float)m;
 }
 
-// The whole clip of one column, its values read through x(i).  The arithmetic is that of
-// clip_column with one lane (sums in frame order in double, m = s / n, q = sum of
-// (x - m)^2, threshold ksigma * sqrt(q / n), drop |x - m| > threshold); when an iteration
-// drops nothing (the largest |x - m| tells) its own mean is the final mean.  c.lo, c.hi
-// bound the kept values.
-template <int MAXV, bool MISS, typename X>
-__device__ __forceinline__ float clip_values(X x, int32_t N, double ksigma, int32_t max_iters, ClipState &c,
-                                             unsigned &dropped)
-{
-    double m, thr;
-    if (clip_first<MAXV, MISS>(x, N, ksigma, max_iters, c, m, thr)) return (float)m;
-    return clip_rest<MAXV>(x, N, ksigma, max_iters, c, m, thr, dropped);
-}
-
 // Values in registers.  Each read goes through an empty asm statement that marks the value
 // as changed, so every pass converts it to double again instead of holding the column's
 // converted values across the passes (twice the registers; with them a compute unit holds
@@ -376,13 +348,6 @@ struct RegColumn {
     }
 };
 
-template <int MAXV, bool MISS = false>
-__device__ __forceinline__ float clip_registers(const float (&x)[MAXV], int32_t N, double ksigma, int32_t max_iters,
-                                                ClipState &c, unsigned &dropped)
-{
-    return clip_values<MAXV, MISS>(RegColumn<MAXV>{x}, N, ksigma, max_iters, c, dropped);
-}
-
 // PX adjacent pixel columns per thread: each frame's PX values come in as one vector
 // load (frame k's plane starts at aligned + k * pstride; pstride >= plane, and pstride
 // and the pointers aligned to PX floats; with PX = 4 an even pstride is enough, a frame
@@ -396,7 +361,7 @@ __device__ __forceinline__ float clip_registers(const float (&x)[MAXV], int32_t 
 // 0.71 ms loading them again, 2.05 holding them until the queue is written); columns of
 // 49 - 128 values are built for three waves per SIMD and hold them (a quarter of 97-frame
 // columns drop a value).
-// Every result is that of clip_registers on the column.  Columns at or past `plane` are
+// Columns at or past `plane` are
 // neither written nor counted.  The whole workgroup must call this (it synchronises).
 template <int MAXV, int PX, bool MISS = false, int QCAP = (MAXV <= 32 ? 128 : MAXV <= 48 ? 0 : 96)>
 __device__ __forceinline__ unsigned combine_cols_block(const float *__restrict__ aligned, int64_t plane,

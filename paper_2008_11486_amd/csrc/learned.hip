@@ -42,12 +42,6 @@ __device__ __forceinline__ bf16x8 load8(const uint16_t *p)
     return __builtin_bit_cast(bf16x8, v);
 }
 
-__device__ __forceinline__ bf16x8 zero8()
-{
-    const uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    return __builtin_bit_cast(bf16x8, v);
-}
-
 // ---- network input: 4x4 block mean, standardisation, asinh, bfloat16 --------------------
 constexpr int DS_BLOCK = 256;
 

@@ -482,19 +482,6 @@ __device__ __forceinline__ void small_dispatch(int D, F &&f)
     }
 }
 
-template <typename F>
-__device__ __forceinline__ void score_dispatch(int K, F &&f)
-{
-    switch (K) {
-    case 5: f(std::integral_constant<int, 5>{}); break;
-    case 9: f(std::integral_constant<int, 9>{}); break;
-    case 12: f(std::integral_constant<int, 12>{}); break;
-    case 17: f(std::integral_constant<int, 17>{}); break;
-    case 18: f(std::integral_constant<int, 18>{}); break;
-    default: f(std::integral_constant<int, 22>{}); break;
-    }
-}
-
 // ---- sum of tile partials ------------------------------------------------------------------
 // Candidates 64*cblock .. +63 of one frame, by a workgroup of 64*SUM_WAVES threads: wave w
 // sums tiles w, w + SUM_WAVES, ... in order, then the SUM_WAVES partial sums are added in
@@ -537,19 +524,6 @@ __device__ __forceinline__ bool inner_border(const reduce_offset_t &o, int32_t r
     const bool bx = (o.flags & REDUCE_EDGE_X) && o.dx > -rmax && o.dx < rmax;
     const bool by = (o.flags & REDUCE_EDGE_Y) && o.dy > -rmax && o.dy < rmax;
     return bx || by;
-}
-
-// ---- scores of one frame from its partials ------------------------------------------------
-// Sum over tiles in tile order; -inf outside the clipped window.
-__device__ __forceinline__ double candidate_score(const double *partial_k, int32_t n_tiles, int32_t D, int32_t R,
-                                                  int32_t Rmax, int32_t cx, int32_t cy, int32_t cand)
-{
-    const int32_t jj = cand / D, ii = cand - jj * D;
-    const int32_t dx = cx - R + ii, dy = cy - R + jj;
-    if (dx < -Rmax || dx > Rmax || dy < -Rmax || dy > Rmax) return -INFINITY;
-    double s = 0.0;
-    for (int32_t tI = 0; tI < n_tiles; ++tI) s += partial_k[(int64_t)tI * D * D + cand];
-    return s;
 }
 
 // ---- argmax, runner-up, parabola -------------------------------------------------
