@@ -374,6 +374,20 @@ def spectra_bytes(specs):
     return total
 
 
+def spectral_stacks(rd, batch):
+    """For each stack of a batch whether its search goes through row spectra: a stack that does
+    so by itself needs the workspace of one that asks for it."""
+    out = []
+    for d in batch.descs:
+        need = []
+        for search in (d.search, rd.SEARCH_SPECTRAL):
+            one = (rd.StackDesc * 1)(d)
+            one[0].search = search
+            need.append(int(rd.lib().reduce_stack_batch_ws(one, 1)))
+        out.append(d.N > 1 and need[0] == need[1])
+    return out
+
+
 def search_flops(specs):
     """Algorithmic flops of the full-window search of every non-reference frame: one FMA
     (2 flop) per template pixel (the interior shrunk by the radius) per candidate offset."""
@@ -999,26 +1013,31 @@ def main():
 
     kern = {name: rd.prof_query(name) for name in ("score_tiles", "calibrate", "shift", "combine", "batch_score",
                                                    "batch_fused", "batch_comb", "batch_shift", "batch_spectral",
-                                                   "fft_rows", "spec_corr", "spec_eval", "fft_refine")}
+                                                   "register_fft", "fft_rows", "spec_corr", "spec_eval", "fft_refine")}
     batched = args.path == "batched"
     rd.prof_enable(False)
 
     score_ms, score_n = kern["batch_score" if batched else "score_tiles"]
-    if batched and score_n == 0:
-        # the searches went through row spectra: the position of their largest kernel
+    # the searches by direct sums and those through row spectra (the stage-wise workloads are of one size);
+    # the position of the larger of their largest kernels
+    through = spectral_stacks(rd, pipe.batch) if batched else [kern["fft_rows"][1] > 0] * len(specs)
+    spec_specs = [sp for sp, t in zip(specs, through) if t]
+    direct_specs = [sp for sp, t in zip(specs, through) if not t]
+    if spec_specs and (not direct_specs or kern["fft_rows"][0] > score_ms):
         ms, n = kern["fft_rows"]
-        gbs = spectra_bytes(specs) / (ms / args.steps / 1e3) / 1e9
+        gbs = spectra_bytes(spec_specs) / (ms / args.steps / 1e3) / 1e9
+        search_ms = kern["batch_spectral" if batched else "register_fft"][0]
         roofline = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "fft_rows",
                     "avg_launch_ms": round(ms / n, 4), "launches_per_step": round(n / args.steps, 3),
-                    "bytes_per_step": spectra_bytes(specs),
-                    "search_share_of_step": round(kern["batch_spectral"][0] / args.steps / ms_per_step, 4)}
+                    "bytes_per_step": spectra_bytes(spec_specs),
+                    "search_share_of_step": round(search_ms / args.steps / ms_per_step, 4)}
     else:
         score_avg_s = score_ms / score_n / 1e3
         launches_per_step = score_n / args.steps
         # batched: the flops of the step's searches spread over its search dispatches (one per
         # group of stacks that share a launch shape); stage-wise: one stack's search per launch
-        flops = search_flops(specs) / launches_per_step if batched else search_flops(specs[:1])
+        flops = search_flops(direct_specs) / launches_per_step if batched else search_flops(specs[:1])
         achieved = flops / score_avg_s / 1e12
         kname = "batch_score" if batched else "score_tiles"
         traffic = recorded_traffic(args.traffic, kname, "many" if args.workload == 2 else None)
