@@ -215,13 +215,14 @@ int reduce_mask_shifted(const uint8_t *mask, float *out, int32_t W, int32_t H, i
  * tridiagonal system per image row or column): out[k][v][u] = S_k(x0 + u + sx_k,
  * y0 + v + sy_k), S_k the tensor-product natural cubic spline through frame k's pixels
  * on the integer grid (second derivative zero at both ends of every row and column).
- * Positions are clamped into the frame.  FP32 arithmetic; two passes (rows into the
- * workspace, then columns).
+ * Positions are clamped into the frame.  FP32 arithmetic; one pass (row and column
+ * splines of a strip of columns in one kernel).
  *   in    device float [N][H][W];  out  device float dense [N][h][w]
  *   offs  device float [N][2];     rect host int32 {x0, y0, w, h}
- *   ws    device workspace of at least reduce_shift_spline_ws(W, H, N) bytes
- *         (the row pass's result, N * H rows of w floats at a pitch of w rounded up
- *         to 64 floats, so that the column pass reads whole 256-byte segments)
+ *   ws    device workspace of at least reduce_shift_spline_ws(W, H, N) bytes (N * H
+ *         rows of w floats at a pitch of w rounded up to 64 floats); it is neither read
+ *         nor written, so calls on several streams may share one, or any other memory
+ *         of that size
  * Errors: an empty or oversized rect -> SHAPE; N or H above 65535 -> UNSUPPORTED;
  * small ws -> WORKSPACE. */
 size_t reduce_shift_spline_ws(int32_t W, int32_t H, int32_t N);
@@ -420,7 +421,11 @@ int reduce_render_frames(const float *stars, int32_t S, const int64_t *keys, int
  * Launch shapes (tiles, workgroup sizes, lanes per pixel) are chosen per problem
  * size by timing candidates on the caller's data with HIP events; the winner is
  * cached in the process and used by every later call of that size (including the
- * batched path).  Tuning calls synchronise `stream`.
+ * batched path).  So a tuned search shape keeps reduce_register, and stacks with
+ * search = REDUCE_SEARCH_DIRECT, with the direct sums, also for sizes that go through row
+ * spectra by themselves and are faster there; reduce_tune_search tells which search is, and
+ * reduce_register_fft or REDUCE_SEARCH_SPECTRAL takes it.  Tuning calls synchronise
+ * `stream`.
  *   reduce_tune_register: candidates of the correlation search for (W, H, radius,
  *     radius_max), each run reps times on ref/frames, then the fastest three and the
  *     fastest with other tile heights timed again in three interleaved rounds (least

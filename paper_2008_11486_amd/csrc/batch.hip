@@ -390,7 +390,6 @@ __device__ __forceinline__ void aligned_unit(const StackDev &s, int32_t k, int32
 // the rest of the tile (16 masked frames of 6144x6160, 147000 tiles: 1820 us, of which
 // 1100 without it), so stacks of many tiles add into REJ_SLOTS counters, which batch_rejected
 // adds up after the launch.
-
 __device__ __forceinline__ void add_dropped(const StackDev &s, int32_t item, unsigned total)
 {
     unsigned long long *n = s.slots ? s.slots + item % REJ_SLOTS * REJ_STRIDE
@@ -613,8 +612,7 @@ static BatchLayout layout_of(const reduce_stack_t *stacks, int32_t n, bool by_ru
         const RegPlan &p = sl.plan;
         const int64_t fp = (int64_t)s.W * s.H;
         const int32_t nreg = s.N - 1;
-        // a stack of up to 48 frames without a bad-pixel map takes the fused phase (no
-        // aligned frames in the workspace)
+        // a stack of up to 48 frames takes the fused phase (no aligned frames in the workspace)
         const bool fuse = s.N <= 48;
         sl.cal = off;
         off += al(sizeof(float) * fp * s.N);

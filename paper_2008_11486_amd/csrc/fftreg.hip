@@ -181,7 +181,7 @@ __device__ __forceinline__ void dft16(double2 (&v)[16])
 // N2 <= 256) and a third time for the partners of the unpacking.  Radix-4 passes moved a row
 // of 4096 through LDS seven times and read 18 thousand twiddles for it, which bound the
 // kernel at half the copy rate (3.45 ms for 16 frames of 6144x6160 and their template, 9.4 GB
-// moved, now 2.20; 11 frames of 4096x4096 0.79 -> 0.50 ms, at the copy rate); here the
+// moved, now 2.02, at the copy rate); here the
 // second pass's twiddles come from a table of 256 in LDS, the last one's are products of
 // four table values.  LDS index i sits at i + i / 16: a
 // pass's stores are 16 values apart from lane to lane, which would fall on one bank.
@@ -347,9 +347,10 @@ __global__ __launch_bounds__(FFT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
 // The sum over blocks stays in the transform domain: one inverse per workgroup, and COL_L /
 // M times one transform per frame value instead of Dg multiply-adds (direct sums over the
 // lags in registers took 11.8 of the 21.8 ms of a call over 16 frames of 6144x6160 at R = 65,
-// bound by FP64 issue; the blocks take 3.05, and for the six stacks of 91 frames of 512x512
-// to 4096x4096 at R = 17 0.92 ms instead of 2.15).  Windows of more than COL_LAGS lags take
-// several passes of equal width, pass g on the frame rows g Dg further down.
+// bound by FP64 issue; the blocks take 2.58 and the template's 0.21, and for six stacks of 91
+// frames of 512x512 to 4096x4096 at R = 17 0.80 and 0.10 ms instead of 2.15).  Windows of more
+// than COL_LAGS lags take several passes of equal width, pass g on the frame rows g Dg
+// further down.
 //
 // The template's block transforms are made once (spec_tmpl) and read by every frame.  A
 // workgroup takes COL_KC columns (256-byte row pieces) and a band of blocks of one frame; a
@@ -805,7 +806,9 @@ static void launch_fft_rows(const FftLayout &L, const RowSrc &src, int32_t rows_
 bool spectra_pay(int32_t W, int32_t H, int32_t N, int32_t R)
 {
     if (R < 1 || N < 1 || N > 65535 || W > FFT_P_MAX || 2 * R + 1 > 1024 || W - 2 * R < 1 || H - 2 * R < 1) return false;
-    // a launch shape tuned for these sizes is what later calls of them use
+    // a launch shape tuned for these sizes is what later calls of them use, so tuning keeps the
+    // direct sums also where the spectra are faster (three stacks of 10 frames of 1024x1024 at R = 21 2.1
+    // ms tuned, 0.53 untuned); reduce_tune_search times both
     RegShape tuned;
     if (tuned_reg_shape(W, H, R, R, &tuned)) return false;
     // Microseconds of both, from measured calls.  Direct sums: 23 - 40 TFLOP/s (512x512 x 16 at
@@ -813,8 +816,10 @@ bool spectra_pay(int32_t W, int32_t H, int32_t N, int32_t R)
     // less half of that), so the estimate is a low one.  Spectra: 100 us of dependent small
     // launches and 6.5 us per million row values of the padded frames and the template (the
     // same calls: 130, 206, 599), of which the contraction's part grows with its passes and
-    // with the rows its blocks read twice.  Near the line the two are within 30% of each
-    // other: 700x650 x 4 at R = 17 170 and 114, 512x512 x 4 at R = 17 123 and 105.
+    // with the rows its blocks read twice.  The estimates are cautious at the line: 30 shapes
+    // drawn at 1.25 to 1.6 times the spectra's estimate took 0.28 - 0.61 of the direct
+    // sums' time through spectra, and batches of 11 to 54 equal stacks of them, whose direct tiles share one
+    // launch and whose spectral searches run one after the other, 0.36 - 0.65.
     const double D = 2.0 * R + 1.0, T = (double)(W - 2 * R) * (H - 2 * R);
     const double direct = 2.0 * N * T * D * D / 40e6;
     int32_t P = 64;

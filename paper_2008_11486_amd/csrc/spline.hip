@@ -18,7 +18,7 @@
 // position takes f[0] or f[L-1].
 //
 // One pass, FP32 arithmetic: a workgroup walks down a strip of columns, forms the row
-// splines of 64 frame rows at a time at the shifted x of its columns, keeps them in LDS and
+// splines of 32 frame rows at a time at the shifted x of its columns, keeps them in LDS and
 // takes the column splines of those at the shifted y.  The shift is the same for the whole
 // frame, so output u sits on knot x0 + fx + u (before clamping) with the same fraction: a
 // thread that owns a run of knots holds in registers everything its run's outputs need.
@@ -330,7 +330,8 @@ __global__ __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 
 using namespace rd;
 
-// row pitch of the workspace: whole 256-byte segments for the column pass's loads
+// The one pass needs no workspace.  The entry point keeps the one that its interface asks for
+// (N * H rows of w floats at a pitch of whole 256-byte segments) and touches none of it.
 static int32_t spline_pitch(int32_t w) { return (w + 63) & ~63; }
 
 extern "C" size_t reduce_shift_spline_ws(int32_t W, int32_t H, int32_t N)
